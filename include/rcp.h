@@ -221,14 +221,14 @@ rcp_status rcp_render(rcp_scene* scene, const rcp_camera* base_camera, int W, in
  * HIP graph capture, tight serving loops, harnesses that forbid allocation.
  * Same arguments, validation and results as rcp_render (always the chain
  * engine); the call allocates nothing.  Its working memory (the launch's
- * view table, work counters, tile scores and order, and traversal stack
- * overflow) is a fixed area of rcp_render_noalloc_scratch_bytes() = 64 MiB
+ * view table, work counters, tile scores and order, entry lists, and
+ * traversal stack overflow) is a fixed area of rcp_render_noalloc_scratch_bytes() = 64 MiB
  * inside the library's device code, one per GPU, held until the process
  * ends.  Views of up to 2^16 tiles of 64 pixels (1440p and below) are
  * rendered in the cost order of the tile_order tuning, larger ones in screen
  * order (the order changes the speed only).  The launch uses as many
  * persistent workgroups as that area's overflow part holds for the scene's
- * tree (at most the occupancy limit, reached by trees of up to 15 inner
+ * tree (at most the occupancy limit, reached by trees of up to 13 inner
  * levels; the count changes the speed only); RCP_ERR_INVALID_ARGUMENT if it
  * cannot hold one workgroup per compute unit (a tree over 85 levels deep).
  * All calls on one GPU share the area
@@ -257,7 +257,9 @@ rcp_status rcp_render_pass(rcp_scene* scene, const rcp_camera* base_camera, int 
                            float* out_rgb, int32_t* out_ids, float* out_aux, void* hip_stream);
 
 /* rcp_render plus traversal counters (a separate instrumented kernel; not
- * for timing).  counts: HOST [K][6] uint64 per pass: rays traced, inner
+ * for timing).  That kernel starts every ray at the tree's root and traces
+ * every pass whose inputs changed, so its counts are those of the method; the
+ * timed kernel of the chain engine skips part of both.  counts: HOST [K][6] uint64 per pass: rays traced, inner
  * nodes visited, triangles tested, rays continued to the next pass, inner
  * nodes read from the LDS copy of the tree's top levels (chain engine), and
  * traversal stack entries spilled from LDS to the global overflow area.
@@ -332,12 +334,15 @@ void rcp_graph_destroy(rcp_graph* graph);
  *                                    colour changed are compacted into a list
  *                                    in HBM for the next pass
  *                  rcp_render_pass always runs one pass launch.
- *   top_levels     levels of the 4-wide BVH the chain engine copies into
- *                  each workgroup's LDS and reads from there (0..4, default
- *                  4; at most 80 nodes)
- *   stack_entries  traversal stack entries per lane kept in LDS by the chain
- *                  engine's colour-mode kernel (8 or 16, default 16); deeper
- *                  entries go to a global overflow area
+ *   top_levels     levels of the 4-wide BVH that launches whose rays start at
+ *                  the root copy into each workgroup's LDS and read from
+ *                  there (0..4, default 4; at most 80 nodes): the
+ *                  instrumented kernel and launches without room for entry
+ *                  lists
+ *   stack_entries  traversal stack entries per lane that those launches keep
+ *                  in LDS in the colour mode (8 or 16, default 16; launches
+ *                  with entry lists keep 8); deeper entries go to a global
+ *                  overflow area
  *   block_size     that kernel's workgroup size (256 or 512, default 256)
  *   tile_order     single renders of the chain engine (rcp_render,
  *                  rcp_render_stats, graphs): 1 (default) hands out each
@@ -350,8 +355,8 @@ void rcp_graph_destroy(rcp_graph* graph);
  *                  view follows it too (a server slot only up to 2^18
  *                  tiles, rcp_render_noalloc up to 2^16); batches of more
  *                  views always use the screen order.
- * The instrumented kernel and the depth and normal modes always use 16
- * stack entries and workgroups of 256. */
+ * The instrumented kernel always uses 16 stack entries, and it and the depth
+ * and normal modes workgroups of 256. */
 #define RCP_ENGINE_CHAIN 0
 #define RCP_ENGINE_PASSES 1
 typedef struct {

@@ -21,6 +21,11 @@
 // its youngest chain: longest work first, which shortens the launch's tail
 // (the last pixels handed out start chains of up to K passes).
 //
+// Between setup rounds the wave's rays start in their tile group's entry list
+// (below) and put the leaves they reach into a queue that all lanes work off
+// (trav_queue).  The instrumented kernel, and launches without room for the
+// lists, start at the root and test each leaf in its ray's lane (trav_step).
+//
 // The same kernel serves rcp_render and rcp_render_batch.  Views are read
 // from a device table, by each lane, or with scalar loads when the launch
 // holds one view; a single render's one-entry table is written by a setup
@@ -29,6 +34,7 @@
 // the compiler hoist its uniform float math into vector registers for the
 // whole loop, costing occupancy.)
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -43,10 +49,16 @@ struct ViewDev {
     Camera cam;
     int W, H, K, tiles_x, tile_log2w;
     int super_log2;        // log2 of the super-tile side in tiles (0: plain tile rows)
+    int super_rows;        // super-tiles per column (batches take them column by column)
     float hw;              // half_width(cam.th, W, H)
     float le, ld, z0;
     float* out;            // [K][H][W][3]
     int32_t* ids;          // [K][H][W] or NULL
+    // entry lists (below): one per group of 2^kGroupLog2 x 2^kGroupLog2 tiles
+    uint32_t entry_base;   // the view's first list
+    uint32_t entries_x;    // groups per row
+    float spread_dir;      // bounds of lambda_dir w and lambda_eye w along each camera axis over
+    float spread_eye;      // all passes; spread_dir < 0: no useful bound, the lists cull nothing
 };
 
 static_assert(sizeof(ViewDev) + 2 * sizeof(uint32_t) + 64 <= kViewBytes, "one-entry view table");
@@ -68,8 +80,39 @@ struct ChainArgs {
     unsigned long long* stats;   // [K][kStatCols] (STATS): rays, inner nodes, triangles, rays continued,
                                  // LDS node reads, stack entries spilled
     const uint32_t* order;       // single view, or NULL: item i is pixel (i & 63) of tile order[i >> 6]
+    const float4* entries;       // entry lists of the views' tile groups (ENTRY kernels)
 };
 
+// ---- Entry lists --------------------------------------------------------------
+// All rays of a tile group's pixels, in every pass, lie in one narrow pyramid:
+// the group's rectangle of the image plane, widened by the largest
+// displacement (at most lambda_dir along each camera axis in the colour
+// mode), seen from the eye (moved by at most lambda_eye).  Every one of those
+// rays would walk the same top levels of the tree, past boxes that the
+// pyramid misses anyway.  So before the launch each group gets a list of
+// up to kEntryItems subtrees: those that the pyramid meets, opened as far
+// as that many items allow, nearest first.  A ray tests all items of its
+// group's list when it is set up -- a setup round runs with most lanes of the
+// wave, and they read the same LDS words -- keeps a bit mask of those it
+// meets, and takes its next subtree from the mask whenever its stack is
+// empty.  The items' boxes are the exact boxes of the tree's nodes, and only
+// boxes that no ray of the group can meet are left out, so the closest hit
+// stays the same.
+//
+// On the 1080p terrain frame (1M triangles, K = 6) a ray visits 9.4 nodes and
+// tests 16 items, against 18 nodes from the root.  Measured (frame ms): 16
+// items 1.09; 32 items 1.18 (fewer visits, 7.6, but twice the tests, and a
+// workgroup less per CU); groups of 2 x 2 tiles 1.09, one tile 1.14, 8 x 8
+// tiles 1.10; two lists per wave 1.11 (more rays without one).
+constexpr int kEntryItems = 16;
+// A list in HBM (kEntryStride float4): the six planes of four items (as in a
+// node) each, the links, then the number of used quads of items.
+constexpr uint32_t kEntryF4 = 7 * kEntryItems / 4;     // planes and links, the part held in LDS
+constexpr uint32_t kEntryLinks = 6 * kEntryItems / 4;  // first float4 of the links
+static_assert(kEntryF4 < kEntryStride && kEntryStride <= 64, "one load per lane copies a list");
+constexpr int kGroupLog2 = 2;             // groups of 4 x 4 tiles
+constexpr int kEntrySlots = 3;            // lists a wave holds in LDS
+constexpr int kEntryStack = 8;            // LDS stack entries next to them
 
 // Lanes waiting for a setup round that start one once the bands are used up
 // (measured on the terrain frame: 1 -- a round for every waiting lane --
@@ -81,12 +124,12 @@ constexpr uint32_t kDrainedRound = 8;
 // vector-memory path, which the traversal keeps busy.
 typedef __attribute__((address_space(4))) ViewDev ConstView;
 
-template <bool STATS, int MODE, bool ONE, int STACK, int BLOCK>
+template <bool STATS, int MODE, bool ONE, bool ENTRY, int STACK, int BLOCK>
 __device__ inline void chain_body(const ChainArgs& a) {
     constexpr bool AUX = MODE != RCP_MODE_COLOR;
-    // LDS: the staged top levels (128-byte nodes, as in HBM, so the same
-    // plane offsets serve both), then the stack area, the stats and the view
-    // starts
+    // LDS: the waves' entry lists, or the staged top levels (128-byte nodes, as
+    // in HBM, so the same plane offsets serve both), then the stack area, the
+    // stats and the view starts
     extern __shared__ float4 smem[];
     float4* top = smem;
     // the traversal reads staged node i at LDS byte address 128 i: the
@@ -99,9 +142,13 @@ __device__ inline void chain_body(const ChainArgs& a) {
     }
     // (the stack directly after the nodes: its column addresses then carry no
     // constant offset, which the paired LDS writes of a push could not encode)
-    char* lds = (char*)(smem + 8 * (size_t)a.sc.top_count);
+    char* lds = (char*)(smem + (ENTRY ? (BLOCK / 64) * kEntrySlots * kEntryF4 : 8u * a.sc.top_count));
     int32_t* stack_area = (int32_t*)lds;                                  // STACK * BLOCK
     lds += sizeof(int32_t) * STACK * BLOCK;
+    // ENTRY: the wave's ray records and leaf queue
+    const uint32_t wave_lds =
+        __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(const LdsI32*)(int32_t*)lds + (threadIdx.x >> 6) * kQueueBytes);
+    if (ENTRY) lds += (BLOCK / 64) * kQueueBytes;
     unsigned long long* lstats = (unsigned long long*)lds;                // STATS: kStatCols * kMaxPasses
     if (STATS) lds += sizeof(unsigned long long) * kStatCols * kMaxPasses;
     uint32_t* vbegin = (uint32_t*)lds;                                    // n_views + 1
@@ -109,8 +156,9 @@ __device__ inline void chain_body(const ChainArgs& a) {
     const ConstView* views = (const ConstView*)a.views;
     if (!ONE)
         for (int i = threadIdx.x; i <= a.n_views; i += BLOCK) vbegin[i] = a.begin[i];
-    for (uint32_t i = threadIdx.x; i < 8u * a.sc.top_count; i += BLOCK)
-        if ((i & 7u) != 7u) top[i] = a.sc.nodes[i];   // the zero padding is never read
+    if (!ENTRY)
+        for (uint32_t i = threadIdx.x; i < 8u * a.sc.top_count; i += BLOCK)
+            if ((i & 7u) != 7u) top[i] = a.sc.nodes[i];   // the zero padding is never read
     if (STATS)
         for (int i = threadIdx.x; i < kStatCols * kMaxPasses; i += BLOCK) lstats[i] = 0ull;
     __syncthreads();
@@ -131,6 +179,17 @@ __device__ inline void chain_body(const ChainArgs& a) {
     uint32_t part = blockIdx.x % kFetchParts;   // wave-uniform: the band fetched from
     uint32_t parts_done = 0;                    // wave-uniform: bands found used up
     int k = 0, x = 0, y = 0;
+    // ENTRY: slot i of the wave's LDS holds the list of group tag[i], with
+    // quads[i] used quads (wave-uniform); `slot` is the lane's slot
+    // (kEntrySlots: none, its rays start at the root)
+    const uint32_t slot0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (kEntrySlots * kEntryF4 * 16u);
+    uint32_t tag[kEntrySlots], quads[kEntrySlots];
+#pragma unroll
+    for (int i = 0; i < kEntrySlots; ++i) {
+        tag[i] = 0xFFFFFFFFu;
+        quads[i] = 0u;
+    }
+    uint32_t slot = kEntrySlots;
     float pr = 0.5f, pg = 0.5f, pb = 0.5f;              // previous colour (the seed I_0 at pass 0)
     float pa[4] = {INFINITY, 0.0f, 0.0f, 0.0f};         // previous hit data: view depth, unit normal
     TravCount cnt;                                      // STATS: counters of the current ray
@@ -158,6 +217,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
                     float rgb[3];
                     float na[4] = {INFINITY, 0.0f, 0.0f, 0.0f};
                     int32_t hid = -1;
+                    if (ENTRY) recorded_hit(tv.h, wave_lds);
                     if (tv.h.id != INT_MAX) {
                         const float4 c = a.sc.shade[2 * (size_t)tv.h.slot + (tv.h.front ? 0 : 1)];
                         rgb[0] = c.x; rgb[1] = c.y; rgb[2] = c.z;
@@ -225,6 +285,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
             const bool fetch = !drained && n_idle > 0u;
             if (fetch) wave_fetch(a.fetch, n_items, n_idle, part, parts_done, drained, base, lim);
             bool init = pending;
+            uint32_t group = 0xFFFFFFFFu;   // ENTRY: tile group of a new pixel
             if (fetch && !alive && !pending) {
                 const uint32_t item = base + lanes_below(idle);
                 if (item < lim) {
@@ -241,14 +302,58 @@ __device__ inline void chain_body(const ChainArgs& a) {
                                                : item - vbegin[v];
                     {
                         const ConstView& vw = views[ONE ? 0 : v];
-                        tile_pixel(local, (uint32_t)vw.tiles_x, (uint32_t)vw.tile_log2w, (uint32_t)vw.super_log2, x, y);
+                        tile_pixel(local, (uint32_t)vw.tiles_x, (uint32_t)vw.tile_log2w, (uint32_t)vw.super_log2, x, y,
+                                   ONE ? 0u : (uint32_t)vw.super_rows);
                         if (x < vw.W && y < vw.H) {
                             k = 0;
                             pr = 0.5f; pg = 0.5f; pb = 0.5f;
                             pa[0] = INFINITY; pa[1] = 0.0f; pa[2] = 0.0f; pa[3] = 0.0f;
                             init = true;
+                            if (ENTRY) {
+                                const uint32_t gx = (uint32_t)x >> (vw.tile_log2w + kGroupLog2);
+                                const uint32_t gy = (uint32_t)y >> (6 - vw.tile_log2w + kGroupLog2);
+                                group = vw.entry_base + gy * vw.entries_x + gx;
+                            }
                         }
                     }
+                }
+            }
+            if (ENTRY) {
+                // the entry lists of the new pixels' groups (two at most: the
+                // items are consecutive): already in a slot, or copied into
+                // one that no live lane uses.  Without a free slot the pixels
+                // start at the scene's root.
+                unsigned long long todo = wave_ballot(group != 0xFFFFFFFFu);
+                if (todo != 0ull) {
+                    uint32_t busy = 0;
+#pragma unroll
+                    for (int i = 0; i < kEntrySlots; ++i)
+                        if (wave_ballot((alive || pending) && slot == (uint32_t)i) != 0ull) busy |= 1u << i;
+                    do {
+                        const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)group, __builtin_ctzll(todo));
+                        uint32_t got = kEntrySlots;
+#pragma unroll
+                        for (int i = 0; i < kEntrySlots; ++i)
+                            if (got == kEntrySlots && tag[i] == g) got = i;
+                        if (got == kEntrySlots) {
+                            const uint32_t l = threadIdx.x & 63u;
+#pragma unroll
+                            for (int i = 0; i < kEntrySlots; ++i)
+                                if (got == kEntrySlots && ((busy >> i) & 1u) == 0u) {
+                                    got = i;
+                                    tag[i] = g;
+                                    const float4 q = a.entries[(size_t)g * kEntryStride + (l < kEntryStride ? l : kEntryF4)];
+                                    quads[i] = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(q.x), kEntryF4);
+                                    const V4 qv = {q.x, q.y, q.z, q.w};
+                                    if (l < kEntryF4) *(LdsV4*)(size_t)(slot0 + (kEntryF4 * i + l) * 16u) = qv;
+                                }
+                        }
+                        if (got != kEntrySlots) busy |= 1u << got;
+                        const bool mine = group == g;
+                        if (mine) slot = got;
+                        todo &= ~wave_ballot(mine);
+                    } while (todo != 0ull);
+                    wave_lds_fence();
                 }
             }
             {
@@ -271,6 +376,19 @@ __device__ inline void chain_body(const ChainArgs& a) {
                 float o[3], d[3];
                 make_ray<MODE>(vw.cam, vw.hw, vw.W, vw.H, x, y, pr, pg, pb, pa, vw.z0, vw.le, vw.ld, o, d);
                 trav_init(tv, a.sc, o, d, st);
+                tv.todo = 0u;
+                tv.items = 0u;
+                if (ENTRY) record_ray(tv.rw, wave_lds);
+                if (ENTRY && slot < (uint32_t)kEntrySlots) {
+                    // the items the ray meets, in the order of the list
+                    uint32_t n = 0;
+#pragma unroll
+                    for (int i = 0; i < kEntrySlots; ++i) n = slot == (uint32_t)i ? quads[i] : n;
+                    uint32_t at = slot0 + slot * (kEntryF4 * 16u);
+                    tv.items = at + kEntryLinks * 16u;
+                    for (uint32_t j = 0; j < n; ++j, at += 96u) tv.todo |= meet4(tv, at) << (4u * j);
+                    tv.node = next_node<true>(tv, st);
+                }
                 if (STATS) cnt = TravCount();
                 alive = true;
                 pending = false;
@@ -282,7 +400,14 @@ __device__ inline void chain_body(const ChainArgs& a) {
         }
 
         // ---- one traversal step -------------------------------------------------
-        if (alive && tv.node != -1) trav_step<STATS>(tv, a.sc, st, a.exit_lanes, cnt);
+        if (ENTRY) {
+            // until the next setup round can start
+            const uint32_t dead = popc_u32(wave_ballot(!alive));
+            const uint32_t enough = drained ? (dead + kDrainedRound < 64u ? dead + kDrainedRound : 64u) : (uint32_t)a.refill_min;
+            trav_queue(tv, a.sc, st, wave_lds, a.exit_lanes, enough);
+        } else if (alive && tv.node != -1) {
+            trav_step<STATS, false>(tv, a.sc, st, a.exit_lanes, cnt);
+        }
 
         if (alive && tv.node == -1) {   // the pass is traced: finish it in the next round
             alive = false;
@@ -304,14 +429,14 @@ __device__ inline void chain_body(const ChainArgs& a) {
 // and BLOCK (workgroup size) are launch parameters the autotuner chooses
 // among for the colour mode's timed kernel; the instrumented kernel and the
 // depth and normal modes use kStack and kBlock.
-template <bool STATS, bool ONE, int STACK, int BLOCK>
+template <bool STATS, bool ONE, bool ENTRY, int STACK, int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void k_chain(ChainArgs a) {
-    chain_body<STATS, RCP_MODE_COLOR, ONE, STACK, BLOCK>(a);
+    chain_body<STATS, RCP_MODE_COLOR, ONE, ENTRY, STACK, BLOCK>(a);
 }
 
-template <bool STATS, int MODE, bool ONE>
+template <bool STATS, int MODE, bool ONE, bool ENTRY>
 __global__ __launch_bounds__(kBlock) void k_chain_aux(ChainArgs a) {
-    chain_body<STATS, MODE, ONE, kStack, kBlock>(a);
+    chain_body<STATS, MODE, ONE, ENTRY, ENTRY ? kEntryStack : kStack, kBlock>(a);
 }
 
 // Zero the work counters (kFetchParts per launch) and the stats.
@@ -352,14 +477,14 @@ constexpr uint32_t kScoreBins = 256;
 
 constexpr uint32_t kScoreBlock = 256;
 
-__global__ __launch_bounds__(kScoreBlock) void k_tile_scores(ViewDev v, OccGrid g, uint32_t n_tiles, uint32_t* score) {
-    extern __shared__ uint32_t occ[];
+__device__ inline void tile_scores(const ViewDev& v, const OccGrid& g, uint32_t n_tiles, uint32_t* score, uint32_t block,
+                                   uint32_t* occ) {
     for (uint32_t i = threadIdx.x; i < g.words; i += kScoreBlock) occ[i] = g.bits[i];
     __syncthreads();
     // eight neighbouring threads per tile: the quadrant in the low two bits,
     // the half of the ray's walk in the third; every thread reaches the
     // shuffles at the end
-    const uint32_t gt = blockIdx.x * kScoreBlock + threadIdx.x;
+    const uint32_t gt = block * kScoreBlock + threadIdx.x;
     const uint32_t t = gt >> 3, sub = gt & 3u, half = (gt >> 2) & 1u;
     const uint32_t tw = 1u << (uint32_t)v.tile_log2w, th = 64u >> (uint32_t)v.tile_log2w;
     int x0 = 0, y0 = 0, x = 0, y = 0;
@@ -442,6 +567,240 @@ __global__ __launch_bounds__(kScoreBlock) void k_tile_scores(ViewDev v, OccGrid 
     if (sub == 0u && half == 0u && t < n_tiles) score[t] = count;
 }
 
+// The entry list of a tile group, by one wave.  The items are opened in
+// rounds, all of the list at once: four lanes load one item's node and test a
+// child each against the group's pyramid, and the openings are accepted in
+// the order of the items' box areas (those that do not add items first)
+// while at most kEntryItems items result.  About six rounds of one dependent
+// node load each on the terrain frame.
+constexpr uint32_t kEntryGroups = kScoreBlock / 64;   // lists per workgroup
+constexpr int kEntryChunks = kEntryItems / 16;        // items per group of four lanes
+
+struct EntryLds {
+    // items in two buffers: six planes of 32, links; the list is then laid
+    // out in the buffer not in use
+    float buf[2][7 * kEntryItems];
+    uint32_t key[kEntryItems];
+};
+
+// Four planes through the pyramid's sides and one through the eye, as
+// n . P >= c for points P that any of the group's rays may reach.
+struct Pyramid {
+    float n[5][3], c[5];
+    bool cull;
+
+    // Whether the box may hold such a point: its farthest corner along each
+    // plane's normal.  False for the NaN planes of an unused slot.
+    __device__ inline bool meets(const float lo[3], const float hi[3]) const {
+        bool in = lo[0] <= hi[0];
+        if (cull) {
+#pragma unroll
+            for (int p = 0; p < 5; ++p) {
+                float e = n[p][0] * (n[p][0] > 0.0f ? hi[0] : lo[0]);
+                e = __builtin_fmaf(n[p][1], n[p][1] > 0.0f ? hi[1] : lo[1], e);
+                e = __builtin_fmaf(n[p][2], n[p][2] > 0.0f ? hi[2] : lo[2], e);
+                in = in && e >= c[p];
+            }
+        }
+        return in;
+    }
+};
+
+template <class View>
+__device__ inline Pyramid group_pyramid(const View& v, uint32_t local, float radius) {
+    // the group's rectangle of pixels, and its pyramid's slopes along right
+    // and up, widened for the displacement and for the rounding of the rays
+    // and of the camera's basis (at most 1e-5 from orthonormal)
+    const int gw = 1 << (v.tile_log2w + kGroupLog2), gh = 1 << (6 - v.tile_log2w + kGroupLog2);
+    const int x0 = (int)(local % v.entries_x) * gw, y0 = (int)(local / v.entries_x) * gh;
+    const int x1 = min(x0 + gw, v.W) - 1, y1 = min(y0 + gh, v.H) - 1;
+    Pyramid r;
+    r.cull = v.spread_dir >= 0.0f;
+    const float ds = r.cull ? v.spread_dir : 0.0f;
+    const float th = v.cam.th;
+    const float eps = 4e-5f * (1.0f + v.hw + th) / (1.0f - ds);
+    float lo_s = ((float)(2 * x0 + 1) / (float)v.W - 1.0f) * v.hw - ds;
+    float hi_s = ((float)(2 * x1 + 1) / (float)v.W - 1.0f) * v.hw + ds;
+    float lo_t = (1.0f - (float)(2 * y1 + 1) / (float)v.H) * th - ds;
+    float hi_t = (1.0f - (float)(2 * y0 + 1) / (float)v.H) * th + ds;
+    const float near_s = 1.0f / (1.0f + ds), far_s = 1.0f / (1.0f - ds);   // 1 / (forward component)
+    lo_s = fminf(lo_s * near_s, lo_s * far_s);
+    lo_t = fminf(lo_t * near_s, lo_t * far_s);
+    hi_s = fmaxf(hi_s * near_s, hi_s * far_s);
+    hi_t = fmaxf(hi_t * near_s, hi_t * far_s);
+    lo_s -= eps * (1.0f + fabsf(lo_s));
+    lo_t -= eps * (1.0f + fabsf(lo_t));
+    hi_s += eps * (1.0f + fabsf(hi_s));
+    hi_t += eps * (1.0f + fabsf(hi_t));
+    // margins: the eye's displacement, and 2^-16 of the largest coordinates
+    // (the traversal widens its boxes by 2^-18 of them)
+    const float eye_max = fmaxf(fmaxf(fabsf(v.cam.eye[0]), fabsf(v.cam.eye[1])), fabsf(v.cam.eye[2]));
+    const float size = (radius + eye_max + 2.0f * v.spread_eye) * 1.52587890625e-5f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        r.n[0][a] = v.cam.right[a] - lo_s * v.cam.forward[a];
+        r.n[1][a] = hi_s * v.cam.forward[a] - v.cam.right[a];
+        r.n[2][a] = v.cam.up[a] - lo_t * v.cam.forward[a];
+        r.n[3][a] = hi_t * v.cam.forward[a] - v.cam.up[a];
+        r.n[4][a] = v.cam.forward[a];
+    }
+    const float slope[5] = {lo_s, hi_s, lo_t, hi_t, 0.0f};
+#pragma unroll
+    for (int p = 0; p < 5; ++p) {
+        const float l1 = fabsf(r.n[p][0]) + fabsf(r.n[p][1]) + fabsf(r.n[p][2]);
+        const float ne = r.n[p][0] * v.cam.eye[0] + r.n[p][1] * v.cam.eye[1] + r.n[p][2] * v.cam.eye[2];
+        r.c[p] = ne - (v.spread_eye * 1.001f * (1.0f + fabsf(slope[p])) + size * l1);
+    }
+    return r;
+}
+
+template <class View>
+__device__ inline void entry_list(const View& v, uint32_t local, const DevScene& sc, float4* __restrict__ out, EntryLds& m) {
+    constexpr int N = kEntryItems, C = kEntryChunks;
+    const int lane = (int)(threadIdx.x & 63u), child = lane & 3;
+    const Pyramid py = group_pyramid(v, local, sc.radius);
+    int cur = 0, count = 1;
+    if (lane == 0) {   // the root
+#pragma unroll
+        for (int a = 0; a < 6; ++a) m.buf[0][N * a] = 0.0f;
+        m.buf[0][6 * N] = __int_as_float(0);
+    }
+    for (int round = 0; round < 64; ++round) {
+        wave_lds_fence();
+        const float* b = m.buf[cur];
+        float box[C][7];       // the lane's child of each of its items, with its link
+        bool cand[C], in[C];
+        uint32_t key[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int item = (lane >> 2) + 16 * c;
+            const int32_t link = item < count ? __float_as_int(b[6 * N + item]) : -1;
+            cand[c] = link >= 0;   // an inner node
+            in[c] = false;
+            float area = 0.0f;
+            if (cand[c]) {
+                const float* g = (const float*)(sc.nodes + 8 * (size_t)link) + child;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    box[c][a] = g[8 * a];
+                    box[c][3 + a] = g[8 * a + 4];
+                }
+                box[c][6] = g[24];
+                const float ex = b[3 * N + item] - b[item], ey = b[4 * N + item] - b[N + item],
+                            ez = b[5 * N + item] - b[2 * N + item];
+                area = ex * ey + ey * ez + ez * ex;
+                in[c] = py.meets(box[c], box[c] + 3);
+            }
+            const uint32_t kids = (uint32_t)__builtin_popcount((uint32_t)(wave_ballot(in[c]) >> (lane & 60)) & 15u);
+            // rank of the opening: its area's bits, above those the items it
+            // adds plus one; the item's number breaks ties
+            key[c] = cand[c] ? ((kids <= 1u ? 0x7F800000u : (__float_as_uint(area) & 0x7FFFFFFFu)) & ~7u) | kids : 1u;
+            if (child == 0) m.key[item] = key[c];
+        }
+        wave_lds_fence();
+        int sum[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) sum[c] = count + (int)(key[c] & 7u) - 1;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t kj = m.key[j];
+            const int add = (int)(kj & 7u) - 1;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                sum[c] += ((kj >> 3) > (key[c] >> 3) || ((kj >> 3) == (key[c] >> 3) && j < (lane >> 2) + 16 * c)) ? add : 0;
+        }
+        // the next round's items: the children in place of the opened ones
+        float* w = m.buf[cur ^ 1];
+        int next = 0;
+        bool opened = false;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int item = (lane >> 2) + 16 * c;
+            const bool accept = cand[c] && sum[c] <= N;
+            opened = opened || accept;
+            const bool give = accept ? in[c] : (item < count && child == 0);
+            const unsigned long long all = wave_ballot(give);
+            if (give) {
+                const int pos = next + (int)lanes_below(all);
+#pragma unroll
+                for (int a = 0; a < 7; ++a) w[N * a + pos] = accept ? box[c][a] : b[N * a + item];
+            }
+            next += (int)popc_u32(all);
+        }
+        if (wave_ballot(opened) == 0ull) break;
+        cur ^= 1;
+        count = next;
+    }
+    wave_lds_fence();
+    // the list, nearest item first: unused slots have NaN planes, which no ray meets
+    const float nan = __int_as_float(0x7FC00000);
+    float b[7] = {nan, nan, nan, nan, nan, nan, __int_as_float(-1)};
+    float depth = INFINITY;
+    if (lane < count) {
+#pragma unroll
+        for (int a = 0; a < 7; ++a) b[a] = m.buf[cur][a * N + lane];
+        depth = v.cam.forward[0] * (b[0] + b[3]) + v.cam.forward[1] * (b[1] + b[4]) + v.cam.forward[2] * (b[2] + b[5]);
+    }
+    // (boxes of infinite extent are the only way to a NaN: then the order of arrival)
+    if (wave_ballot(depth != depth) != 0ull) depth = (float)lane;
+    if (lane < N) m.key[lane] = __float_as_uint(depth);
+    wave_lds_fence();
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const float dj = __uint_as_float(m.key[j]);
+        rank += (dj < depth || (dj == depth && j < lane)) ? 1 : 0;
+    }
+    float* w = m.buf[cur ^ 1];
+    if (lane < N) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            w[24 * (rank >> 2) + 8 * a + (rank & 3)] = b[a];
+            w[24 * (rank >> 2) + 8 * a + 4 + (rank & 3)] = b[3 + a];
+        }
+        w[6 * N + rank] = b[6];
+    }
+    wave_lds_fence();
+    if (lane < (int)kEntryF4) out[lane] = ((const float4*)w)[lane];
+    if (lane == 0) out[kEntryF4] = make_float4(__int_as_float((count + 3) / 4), 0.0f, 0.0f, 0.0f);
+}
+
+// Everything a single render needs before its chain launch that does not
+// depend on the order: tile scores (workgroups below score_blocks), entry
+// lists (the next entry_blocks) and, without a cost order, the setup (one
+// more).
+__global__ __launch_bounds__(kScoreBlock) void k_prepare(ViewDev v, OccGrid g, DevScene sc, uint32_t n_tiles, uint32_t* score,
+                                                         uint32_t score_blocks, float4* entries, uint32_t n_entries,
+                                                         uint32_t entry_blocks, ViewDev* table, uint32_t* begin,
+                                                         uint32_t n_items, uint32_t* fetch, unsigned long long* stats) {
+    extern __shared__ float4 prep_lds[];
+    if (blockIdx.x < score_blocks) {
+        tile_scores(v, g, n_tiles, score, blockIdx.x, (uint32_t*)prep_lds);
+    } else if (blockIdx.x < score_blocks + entry_blocks) {
+        const uint32_t sub = threadIdx.x >> 6, e = (blockIdx.x - score_blocks) * kEntryGroups + sub;
+        if (e < n_entries)
+            entry_list(v, e, sc, entries + (size_t)e * kEntryStride, ((EntryLds*)prep_lds)[sub]);
+    } else {
+        setup_single(v, table, begin, n_items, fetch, stats);
+    }
+}
+
+// The entry lists of a batch: one workgroup per kEntryGroups lists, the view
+// of each found in the table.
+__global__ __launch_bounds__(kScoreBlock) void k_batch_entries(const ViewDev* __restrict__ views, int n_views, DevScene sc,
+                                                               float4* entries, uint32_t n_entries) {
+    extern __shared__ float4 prep_lds[];
+    const uint32_t sub = threadIdx.x >> 6, e = blockIdx.x * kEntryGroups + sub;
+    if (e >= n_entries) return;
+    int lo = 0, hi = n_views;   // the last view with entry_base <= e
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (views[mid].entry_base <= e) lo = mid; else hi = mid;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    entry_list(views[lo], e - views[lo].entry_base, sc, entries + (size_t)e * kEntryStride, ((EntryLds*)prep_lds)[sub]);
+}
+
 // One workgroup per band: a counting sort of the band's tiles by decreasing
 // score (order within a score is the order of arrival, which only moves
 // work in time).  Every tile of the band lands in exactly one slot of the
@@ -483,48 +842,61 @@ __global__ __launch_bounds__(1024) void k_band_order(const uint32_t* __restrict_
     }
 }
 
-__global__ void k_setup_single(ViewDev v, ViewDev* table, uint32_t* begin, uint32_t n_items, uint32_t* fetch,
-                               unsigned long long* stats) {
-    setup_single(v, table, begin, n_items, fetch, stats);
-}
-
 // A chain kernel instantiation with its workgroup size and stack depth.
 struct ChainKernel {
     const void* fn;
     int block;
     int stack;
+    bool entry;      // rays start in entry lists
 };
 
-template <bool STATS, bool ONE>
+// (the deeper of the two stacks is kEntryStack entries next to the entry
+// lists: six workgroups still fit a CU's LDS)
+template <bool STATS, bool ONE, bool ENTRY>
 ChainKernel colour_kernel(int stack, int block) {
+    constexpr int D = ENTRY ? kEntryStack : kStack;
     if constexpr (!STATS) {
-        if (stack == 8 && block == 512) return {(const void*)k_chain<false, ONE, 8, 512>, 512, 8};
-        if (stack == 8) return {(const void*)k_chain<false, ONE, 8, kBlock>, kBlock, 8};
-        if (block == 512) return {(const void*)k_chain<false, ONE, kStack, 512>, 512, kStack};
+        if (stack == 8 && block == 512) return {(const void*)k_chain<false, ONE, ENTRY, 8, 512>, 512, 8, ENTRY};
+        if (stack == 8) return {(const void*)k_chain<false, ONE, ENTRY, 8, kBlock>, kBlock, 8, ENTRY};
+        if (block == 512) return {(const void*)k_chain<false, ONE, ENTRY, D, 512>, 512, D, ENTRY};
     }
-    return {(const void*)k_chain<STATS, ONE, kStack, kBlock>, kBlock, kStack};
+    return {(const void*)k_chain<STATS, ONE, ENTRY, D, kBlock>, kBlock, D, ENTRY};
+}
+
+template <bool STATS, bool ONE, bool ENTRY>
+ChainKernel chain_kernel2(int mode, const Launch& lp) {
+    switch (mode) {
+        case RCP_MODE_DEPTH:
+            return {(const void*)k_chain_aux<STATS, RCP_MODE_DEPTH, ONE, ENTRY>, kBlock, ENTRY ? kEntryStack : kStack,
+                    ENTRY};
+        case RCP_MODE_NORMAL:
+            return {(const void*)k_chain_aux<STATS, RCP_MODE_NORMAL, ONE, ENTRY>, kBlock, ENTRY ? kEntryStack : kStack,
+                    ENTRY};
+        default: return colour_kernel<STATS, ONE, ENTRY>(lp.stack, lp.block);
+    }
 }
 
 template <bool STATS, bool ONE>
-ChainKernel chain_kernel1(int mode, const Launch& lp) {
-    switch (mode) {
-        case RCP_MODE_DEPTH: return {(const void*)k_chain_aux<STATS, RCP_MODE_DEPTH, ONE>, kBlock, kStack};
-        case RCP_MODE_NORMAL: return {(const void*)k_chain_aux<STATS, RCP_MODE_NORMAL, ONE>, kBlock, kStack};
-        default: return colour_kernel<STATS, ONE>(lp.stack, lp.block);
-    }
+ChainKernel chain_kernel1(int mode, const Launch& lp, bool entry) {
+    return entry ? chain_kernel2<STATS, ONE, true>(mode, lp) : chain_kernel2<STATS, ONE, false>(mode, lp);
 }
 
 // The kernel of a launch over n_views views in `mode` (the single-view
-// kernels when n_views == 1).
-ChainKernel chain_kernel(bool stats, int n_views, int mode, const Launch& lp) {
-    if (stats) return n_views == 1 ? chain_kernel1<true, true>(mode, lp) : chain_kernel1<true, false>(mode, lp);
-    return n_views == 1 ? chain_kernel1<false, true>(mode, lp) : chain_kernel1<false, false>(mode, lp);
+// kernels when n_views == 1), with or without entry lists.
+ChainKernel chain_kernel(bool stats, int n_views, int mode, const Launch& lp, bool entry) {
+    // The instrumented kernel always starts at the root, so that its counts are
+    // those of the tree, the same in both engines.
+    if (stats)
+        return n_views == 1 ? chain_kernel2<true, true, false>(mode, lp) : chain_kernel2<true, false, false>(mode, lp);
+    return n_views == 1 ? chain_kernel1<false, true>(mode, lp, entry) : chain_kernel1<false, false>(mode, lp, entry);
 }
 
-// LDS of a workgroup: the staged top levels, the stack area and the view
-// starts (and the stats).
+// LDS of a workgroup: the waves' entry lists or the staged top levels, the
+// stack area and the view starts (and the stats).
 size_t chain_smem(const Launch& lp, const ChainKernel& k, bool stats, int n_views) {
-    size_t b = kNodeBytes * (size_t)lp.top_count + sizeof(int32_t) * (size_t)k.stack * (size_t)k.block +
+    size_t b = (k.entry ? (size_t)(k.block / 64) * kEntrySlots * kEntryF4 * 16 : kNodeBytes * (size_t)lp.top_count) +
+               sizeof(int32_t) * (size_t)k.stack * (size_t)k.block +
+               (k.entry ? (size_t)(k.block / 64) * kQueueBytes : 0) +
                sizeof(uint32_t) * (size_t)((n_views + 4) & ~3);
     if (stats) b += sizeof(unsigned long long) * kStatCols * kMaxPasses;
     return b;
@@ -563,8 +935,8 @@ struct ChainGrid {
     uint32_t threads() const { return (uint32_t)blocks * (uint32_t)k.block; }
 };
 
-rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, ChainGrid& g) {
-    g.k = chain_kernel(stats, n_views, mode, lp);
+rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool entry, ChainGrid& g) {
+    g.k = chain_kernel(stats, n_views, mode, lp, entry);
     g.smem = chain_smem(lp, g.k, stats, n_views);
     int per_cu = 0, cus = 0;
     const rcp_status st = occupancy(g.k, g.smem, per_cu, cus);
@@ -590,7 +962,46 @@ size_t spill_depth_of(const rcp_scene* s, const ChainKernel& k) {
     return spill_per_thread(s->dev, k.stack);
 }
 
-ViewDev view_of(const Camera& cam, int W, int H, int K, const Disp& d, float* out, int32_t* ids, int tile_log2w) {
+// Groups of tiles of a view (one entry list each).
+uint64_t view_entries(int W, int H, int tile_log2w, uint32_t* per_row = nullptr) {
+    const uint64_t gw = 1ull << (tile_log2w + kGroupLog2), gh = 1ull << (6 - tile_log2w + kGroupLog2);
+    const uint64_t x = ((uint64_t)W + gw - 1) / gw, y = ((uint64_t)H + gh - 1) / gh;
+    if (per_row) *per_row = (uint32_t)x;
+    return x * y;
+}
+
+// Bounds of the displacements lambda w of a view's rays along each camera
+// axis, over all passes: |2c - 1| <= 1 for every shaded colour (clamped to
+// [0, 1]) and as the background says; times the largest |z - z0| of a hit
+// in the depth mode (z over the scene's box); 1 in the normal mode (a
+// product of unit vectors).  spread_dir < 0 where the rays' pyramid would not
+// be one (lambda_dir w as long as the focal distance) or the numbers leave
+// the range in which single precision holds the test's margins.
+void view_spread(const rcp_scene* s, const Camera& cam, float hw, const Disp& d, float& dir, float& eye) {
+    double w = 1.0;
+    if (d.mode != RCP_MODE_NORMAL)
+        for (int a = 0; a < 3; ++a) w = std::max(w, std::fabs(2.0 * s->dev.bg[a] - 1.0));
+    double far = s->dev.radius;
+    for (int a = 0; a < 3; ++a) far = std::max(far, std::fabs((double)cam.eye[a]));
+    if (d.mode == RCP_MODE_DEPTH) {
+        double lo = 0.0, hi = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double p = (double)s->occ.lo[a] - cam.eye[a];
+            const double q = p + (double)s->occ.cell[a] * s->occ.n[a];
+            lo += std::min(p * cam.forward[a], q * cam.forward[a]);
+            hi += std::max(p * cam.forward[a], q * cam.forward[a]);
+        }
+        w *= std::max(std::fabs(lo - d.z0), std::fabs(hi - d.z0)) * 1.0001 + 1e-4 * far;
+    }
+    w *= 1.0001;
+    const double wd = w * d.ld, we = w * d.le;
+    const bool fine = wd <= 0.5 && we <= 1e12 && far <= 1e12 && hw <= 1e4f && cam.th <= 1e4f;
+    dir = fine ? (float)wd : -1.0f;
+    eye = fine ? (float)we : 0.0f;
+}
+
+ViewDev view_of(const rcp_scene* s, const Camera& cam, int W, int H, int K, const Disp& d, float* out, int32_t* ids,
+                int tile_log2w) {
     ViewDev v{};
     v.cam = cam;
     v.W = W; v.H = H; v.K = K;
@@ -598,9 +1009,13 @@ ViewDev view_of(const Camera& cam, int W, int H, int K, const Disp& d, float* ou
     v.tile_log2w = tile_log2w;
     v.tiles_x = (W + (1 << tile_log2w) - 1) >> tile_log2w;
     v.super_log2 = super_log2_for(W, H, tile_log2w);
+    const int tiles_y = (H + (64 >> tile_log2w) - 1) / (64 >> tile_log2w);
+    v.super_rows = (tiles_y + (1 << v.super_log2) - 1) >> v.super_log2;
     v.le = d.le; v.ld = d.ld; v.z0 = d.z0;
     v.out = out;
     v.ids = ids;
+    (void)view_entries(W, H, tile_log2w, &v.entries_x);
+    view_spread(s, cam, v.hw, d, v.spread_dir, v.spread_eye);
     return v;
 }
 
@@ -617,24 +1032,48 @@ size_t order_entries(int W, int H, int tile_log2w) {
 
 rcp_status prepare_chain(rcp_scene* s, Workspace& ws, int W, int H, int mode, hipStream_t stream) {
     const Launch lp = launch_params(s, chain_ordered(s));
-    ChainGrid g1, g2;
-    rcp_status st = chain_grid(lp, false, 1, mode, g1);
-    if (st == RCP_OK) st = chain_grid(lp, true, 1, mode, g2);
+    size_t need = 0;
+    for (const auto& [stats, entry] : {std::pair(false, false), std::pair(false, true), std::pair(true, false)}) {
+        ChainGrid g;
+        RCP_TRY_STATUS(chain_grid(lp, stats, 1, mode, entry, g));
+        need = std::max(need, spill_depth_of(s, g.k) * g.threads());
+    }
+    rcp_status st = ensure_workspace(s, ws, 0, 0, need, stream);
     if (st != RCP_OK) return st;
-    const size_t need = std::max(spill_depth_of(s, g1.k) * g1.threads(), spill_depth_of(s, g2.k) * g2.threads());
-    st = ensure_workspace(s, ws, 0, 0, need, stream);
-    if (st != RCP_OK) return st;
-    return ensure_order(ws, order_entries(W, H, lp.tile_log2w), stream);
+    return ensure_tiles(ws, order_entries(W, H, lp.tile_log2w), view_entries(W, H, lp.tile_log2w), stream);
 }
 
 namespace {
 
-// Enqueue the setup kernel and the chain launch of one view on a workspace
+// The kernels before a one-view chain launch: tile scores and entry lists
+// (where there is room for them), then the cost order, or the setup alone.
+rcp_status launch_prepare(const rcp_scene* s, const ViewDev& view, uint32_t n_items, uint32_t* order, float4* entries,
+                          ViewDev* table, uint32_t* begin, uint32_t* fetch, unsigned long long* stats,
+                          hipStream_t stream) {
+    const uint32_t n_tiles = n_items >> 6;
+    // tile scores in the second half of the order buffer, the order in the first
+    uint32_t* score = order ? order + n_tiles : nullptr;
+    const uint32_t score_blocks = order ? (8 * n_tiles + kScoreBlock - 1) / kScoreBlock : 0u;
+    const uint32_t n_entries = entries ? (uint32_t)view_entries(view.W, view.H, view.tile_log2w) : 0u;
+    const uint32_t entry_blocks = (n_entries + kEntryGroups - 1) / kEntryGroups;
+    size_t smem = order ? sizeof(uint32_t) * s->occ.words : 0;
+    if (entries) smem = std::max(smem, sizeof(EntryLds) * kEntryGroups);
+    hipLaunchKernelGGL(k_prepare, dim3(score_blocks + entry_blocks + (order ? 0u : 1u)), dim3(kScoreBlock), smem, stream,
+                       view, s->occ, s->dev, n_tiles, score, score_blocks, entries, n_entries, entry_blocks, table, begin,
+                       n_items, fetch, stats);
+    if (order)
+        hipLaunchKernelGGL(k_band_order, dim3(kFetchParts + 1), dim3(1024), 0, stream, (const uint32_t*)score, n_items,
+                           order, view, table, begin, fetch, stats);
+    RCP_CHECK_LAUNCH();
+    return RCP_OK;
+}
+
+// Enqueue the setup kernels and the chain launch of one view on a workspace
 // that already fits the grid.
 rcp_status launch_one_view(rcp_scene* s, Workspace& w, const Launch& lp, const ChainGrid& g, const Camera& cam,
                            int W, int H, int K, const Disp& disp, float* out_images, int32_t* out_ids, bool stats,
                            hipStream_t stream) {
-    const ViewDev view = view_of(cam, W, H, K, disp, out_images, out_ids, lp.tile_log2w);
+    const ViewDev view = view_of(s, cam, W, H, K, disp, out_images, out_ids, lp.tile_log2w);
     ChainArgs a{};
     a.sc = s->dev;
     a.sc.top_count = lp.top_count;
@@ -648,23 +1087,19 @@ rcp_status launch_one_view(rcp_scene* s, Workspace& w, const Launch& lp, const C
     a.spill = w.spill;
     a.spill_stride = g.threads();
     a.stats = stats ? w.stats : nullptr;
-    a.order = nullptr;
     const uint32_t n_tiles = a.n_items >> 6;
-    if (s->tuning.tile_order && s->occ.bits && w.order && w.order_cap >= 2 * (size_t)n_tiles && n_tiles > 0) {
-        // tile scores in the second half of the buffer, the order in the first
-        uint32_t* score = w.order + n_tiles;
-        hipLaunchKernelGGL(k_tile_scores, dim3((8 * n_tiles + kScoreBlock - 1) / kScoreBlock), dim3(kScoreBlock),
-                           sizeof(uint32_t) * s->occ.words, stream, view, s->occ, n_tiles, score);
-        hipLaunchKernelGGL(k_band_order, dim3(kFetchParts + 1), dim3(1024), 0, stream, (const uint32_t*)score,
-                           a.n_items, w.order, view, (ViewDev*)a.views, (uint32_t*)a.begin, w.counters, a.stats);
-        RCP_CHECK_LAUNCH();
-        a.order = w.order;
-    } else {
-        hipLaunchKernelGGL(k_setup_single, dim3(1), dim3(256), 0, stream, view, (ViewDev*)a.views,
-                           (uint32_t*)a.begin, a.n_items, w.counters, a.stats);
-        RCP_CHECK_LAUNCH();
-    }
+    const bool ordered = s->tuning.tile_order && s->occ.bits && w.order && w.order_cap >= 2 * (size_t)n_tiles && n_tiles > 0;
+    a.order = ordered ? w.order : nullptr;
+    a.entries = g.k.entry ? w.entries : nullptr;
+    RCP_TRY_STATUS(launch_prepare(s, view, a.n_items, ordered ? w.order : nullptr, g.k.entry ? w.entries : nullptr,
+                                  (ViewDev*)a.views, (uint32_t*)a.begin, w.counters, a.stats, stream));
     return launch_chain(g, stream, a);
+}
+
+// Whether a view's rays can start in entry lists held by a buffer of `cap`
+// float4.
+bool entries_fit(const rcp_scene* s, const float4* buf, size_t cap, uint64_t n) {
+    return s->dev.n_nodes > 0 && buf && cap >= kEntryStride * n;
 }
 
 }  // namespace
@@ -673,12 +1108,13 @@ rcp_status render_chain(rcp_scene* s, Workspace& w, const Camera& cam, int W, in
                         float* out_images, int32_t* out_ids, unsigned long long* host_counts, hipStream_t stream) {
     const bool stats = host_counts != nullptr;
     const Launch lp = launch_params(s, chain_ordered(s));
+    const uint64_t n_entries = view_entries(W, H, lp.tile_log2w);
+    rcp_status st = ensure_tiles(w, order_entries(W, H, lp.tile_log2w), n_entries, stream);
+    if (st != RCP_OK) return st;
     ChainGrid g;
-    rcp_status st = chain_grid(lp, stats, 1, disp.mode, g);
+    st = chain_grid(lp, stats, 1, disp.mode, !stats && entries_fit(s, w.entries, w.entry_cap, n_entries), g);
     if (st != RCP_OK) return st;
     st = ensure_workspace(s, w, 0, 0, spill_depth_of(s, g.k) * g.threads(), stream);
-    if (st != RCP_OK) return st;
-    st = ensure_order(w, order_entries(W, H, lp.tile_log2w), stream);
     if (st != RCP_OK) return st;
     st = launch_one_view(s, w, lp, g, cam, W, H, K, disp, out_images, out_ids, stats, stream);
     if (st != RCP_OK) return st;
@@ -697,16 +1133,28 @@ rcp_status render_chain_fixed(rcp_scene* s, Workspace& w, const Camera& cam, int
     const bool ordered = chain_ordered(s) && w.order &&
                          w.order_cap >= order_entries(W, H, launch_params(s, true).tile_log2w);
     const Launch lp = launch_params(s, ordered);
-    ChainGrid g;
-    rcp_status st = chain_grid(lp, false, 1, disp.mode, g);
-    if (st != RCP_OK) return st;
     int dev = 0, cus = 0;
     RCP_HIP(hipGetDevice(&dev));
     RCP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     // as many workgroups as the overflow area holds (the grid size changes
-    // the speed only), but at least one per compute unit
-    const size_t per_block = spill_depth_of(s, g.k) * (size_t)g.k.block;
-    const size_t fit = w.spill_cap / per_block;
+    // the speed only), but at least one per compute unit.  The kernel with
+    // entry lists keeps fewer stack entries in LDS and needs more of the area:
+    // it is taken where four workgroups per compute unit fit.
+    // (The area for the lists lies right before the overflow area, and is
+    // added to it when there are none.)
+    ChainGrid g;
+    size_t per_block = 0, fit = 0;
+    for (const bool entry : {true, false}) {
+        if (entry && !entries_fit(s, w.entries, w.entry_cap, view_entries(W, H, lp.tile_log2w))) continue;
+        if (!entry && w.entries) {
+            w.spill = (int32_t*)w.entries;
+            w.spill_cap += w.entry_cap * (sizeof(float4) / sizeof(int32_t));
+        }
+        RCP_TRY_STATUS(chain_grid(lp, false, 1, disp.mode, entry, g));
+        per_block = spill_depth_of(s, g.k) * (size_t)g.k.block;
+        fit = w.spill_cap / per_block;
+        if (entry && fit * g.k.block >= 4 * (size_t)cus * kBlock) break;
+    }
     if (fit < (size_t)cus) {
         set_error("the scene's traversal stack needs %zu bytes of overflow area per compute unit's workgroup; "
                   "the preallocated scratch holds %zu for %d compute units",
@@ -743,12 +1191,12 @@ rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views
     const Launch lp = launch_params(s);
     size_t spill_need = 0;
     for (int mode = 0; mode < 3; ++mode)
-        for (int nv : {1, 2}) {
-            ChainGrid g;
-            rcp_status st = chain_grid(lp, false, nv, mode, g);
-            if (st != RCP_OK) return st;
-            spill_need = std::max(spill_need, spill_depth_of(s, g.k) * g.threads());
-        }
+        for (int nv : {1, 2})
+            for (const bool entry : {false, true}) {
+                ChainGrid g;
+                RCP_TRY_STATUS(chain_grid(lp, false, nv, mode, entry, g));
+                spill_need = std::max(spill_need, spill_depth_of(s, g.k) * g.threads());
+            }
     rcp_status st = RCP_OK;
     if ((size_t)n_views > ws.view_cap || !ws.views) {
         stream_free(ws.views, stream);
@@ -770,6 +1218,11 @@ rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views
         }
         RCP_HIP(hipHostMalloc(&ws.staging, view_table_bytes((size_t)n_views), hipHostMallocDefault));
     }
+    if (st == RCP_OK && with_staging && ws.entry_cap < kEntryStride * kServerEntries) {
+        // without room for entry lists the rays start at the root
+        const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * kServerEntries, sizeof(float4), stream);
+        if (se != RCP_OK && se != RCP_ERR_OUT_OF_MEMORY) st = se;
+    }
     return st;
 }
 
@@ -784,7 +1237,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     std::vector<uint32_t> hb((size_t)n_views + 3);   // begin arrays of the groups, back to back
     struct Group { int mode, first, count; size_t bofs; uint32_t items; };
     std::vector<Group> groups;
-    uint64_t items = 0;
+    uint64_t items = 0, n_entries = 0;
     size_t bofs = 0;
     for (int j = 0; j < n_views; ++j) {
         const rcp_view& vi = views[order[(size_t)j]];
@@ -805,7 +1258,9 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         }
         c.th = vi.camera.tan_half_fovy;
         const Disp d{vi.disp.lambda_eye, vi.disp.lambda_dir, vi.disp.z0, vi.disp.mode};
-        hv[(size_t)j] = view_of(c, vi.W, vi.H, vi.K, d, vi.out_images, vi.out_ids, lp.tile_log2w);
+        hv[(size_t)j] = view_of(s, c, vi.W, vi.H, vi.K, d, vi.out_images, vi.out_ids, lp.tile_log2w);
+        hv[(size_t)j].entry_base = (uint32_t)std::min<uint64_t>(n_entries, 0xFFFFFFFFull);
+        n_entries += view_entries(vi.W, vi.H, lp.tile_log2w);
         hb[bofs++] = (uint32_t)items;
         items += view_items(hv[(size_t)j]);
         if (items >= (1ull << 32) - (1ull << 24)) {   // headroom for fetches past the end
@@ -818,10 +1273,17 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     hb[bofs++] = (uint32_t)items;
     groups.back().items = (uint32_t)items;
 
+    // entry lists for all views, up to kMaxBatchEntries (a server slot: as many
+    // as it was sized for); without room for them the rays start at the root
+    if (!ws.staging && n_entries <= kMaxBatchEntries && ws.entry_cap < kEntryStride * n_entries) {
+        const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * (size_t)n_entries, sizeof(float4), stream);
+        if (se != RCP_OK && se != RCP_ERR_OUT_OF_MEMORY) return se;
+    }
+    const bool entry = entries_fit(s, ws.entries, ws.entry_cap, n_entries);
     size_t spill_need = 0;
     std::vector<ChainGrid> grids(groups.size());
     for (size_t g = 0; g < groups.size(); ++g) {
-        rcp_status st = chain_grid(lp, false, groups[g].count, groups[g].mode, grids[g]);
+        rcp_status st = chain_grid(lp, false, groups[g].count, groups[g].mode, entry, grids[g]);
         if (st != RCP_OK) return st;
         spill_need = std::max(spill_need, spill_depth_of(s, grids[g].k) * grids[g].threads());
     }
@@ -864,18 +1326,10 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
             return st;
     }
     const Launch lpr = ordered1 ? launch_params(s, true) : lp;
-    if (ordered1) {
-        uint32_t* score = ws.order + n_tiles1;
-        hipLaunchKernelGGL(k_tile_scores, dim3((8 * n_tiles1 + kScoreBlock - 1) / kScoreBlock), dim3(kScoreBlock),
-                           sizeof(uint32_t) * s->occ.words, stream, hv[0], s->occ, n_tiles1, score);
-        hipLaunchKernelGGL(k_band_order, dim3(kFetchParts + 1), dim3(1024), 0, stream, (const uint32_t*)score,
-                           groups[0].items, ws.order, hv[0], d_views, d_begin, ws.fetch,
-                           (unsigned long long*)nullptr);
-    } else if (n_views == 1) {
-        // the setup kernel writes the view's table from the by-value
-        // argument, with no host copy
-        hipLaunchKernelGGL(k_setup_single, dim3(1), dim3(256), 0, stream, hv[0], d_views, d_begin,
-                           groups[0].items, ws.fetch, (unsigned long long*)nullptr);
+    if (n_views == 1) {
+        // the view's table is written from the by-value argument, with no host copy
+        RCP_TRY_STATUS(launch_prepare(s, hv[0], groups[0].items, ordered1 ? ws.order : nullptr,
+                                      entry ? ws.entries : nullptr, d_views, d_begin, ws.fetch, nullptr, stream));
     } else if (ws.staging) {
         // a server slot: copy from its pinned table (the slot's previous
         // launch, the last reader, has finished)
@@ -893,6 +1347,10 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         hipLaunchKernelGGL(k_clear_chain, dim3(1), dim3(64), 0, stream, ws.fetch, (int)groups.size(),
                            (unsigned long long*)nullptr);
     }
+    if (entry && n_views > 1)
+        hipLaunchKernelGGL(k_batch_entries, dim3((unsigned)((n_entries + kEntryGroups - 1) / kEntryGroups)),
+                           dim3(kScoreBlock), sizeof(EntryLds) * kEntryGroups, stream, (const ViewDev*)d_views, n_views,
+                           s->dev, ws.entries, (uint32_t)n_entries);
     RCP_CHECK_LAUNCH();
     for (size_t g = 0; g < groups.size(); ++g) {
         ChainArgs a{};
@@ -908,6 +1366,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         a.spill = ws.spill;
         a.spill_stride = grids[g].threads();
         a.order = ordered1 ? ws.order : nullptr;
+        a.entries = entry ? ws.entries : nullptr;
         rcp_status st2 = launch_chain(grids[g], stream, a);
         if (st2 != RCP_OK) return st2;
     }
@@ -916,6 +1375,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
 
 void free_batch_workspace(BatchWorkspace& ws, hipStream_t stream) {
     stream_free(ws.order, stream);
+    stream_free(ws.entries, stream);
     stream_free(ws.views, stream);
     stream_free(ws.fetch, stream);
     stream_free(ws.spill, stream);

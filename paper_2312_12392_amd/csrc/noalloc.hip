@@ -17,6 +17,9 @@
 //   [kOrderOfs, +kOrderBytes)     tile scores and the cost order of views of
 //                                 up to kOrderTiles tiles (written before each
 //                                 launch; larger views take the screen order)
+//   [kEntryOfs, +kEntryBytes)     entry lists of views of up to kEntryLists tile
+//                                 groups, likewise (larger views start their
+//                                 rays at the scene's root)
 //   [kSpillOfs, kScratchBytes)    traversal stack overflow, one column per
 //                                 thread of the grid
 // Every call on a GPU shares that GPU's array and leaves its contents behind:
@@ -34,7 +37,10 @@ constexpr size_t kCountersBytes = 4096;
 constexpr size_t kOrderOfs = kCountersOfs + kCountersBytes;
 constexpr size_t kOrderTiles = size_t(1) << 16;   // 1080p and 1440p frames, with their padding
 constexpr size_t kOrderBytes = 2 * kOrderTiles * sizeof(uint32_t);
-constexpr size_t kSpillOfs = kOrderOfs + kOrderBytes;
+constexpr size_t kEntryOfs = kOrderOfs + kOrderBytes;
+constexpr size_t kEntryLists = 4608;              // 1440p: 80 x 45 groups
+constexpr size_t kEntryBytes = kEntryLists * kEntryStride * sizeof(float4);
+constexpr size_t kSpillOfs = kEntryOfs + kEntryBytes;
 
 static_assert(kViewBytes <= kCountersOfs, "the view table fits before the counters");
 
@@ -83,6 +89,8 @@ rcp_status render_noalloc(rcp_scene* s, const Camera& cam, int W, int H, int K, 
     w.counters = (uint32_t*)((char*)base + kCountersOfs);
     w.order = (uint32_t*)((char*)base + kOrderOfs);
     w.order_cap = kOrderBytes / sizeof(uint32_t);
+    w.entries = (float4*)((char*)base + kEntryOfs);
+    w.entry_cap = kEntryBytes / sizeof(float4);
     w.spill = (int32_t*)((char*)base + kSpillOfs);
     w.spill_cap = (kScratchBytes - kSpillOfs) / sizeof(int32_t);
     return render_chain_fixed(s, w, cam, W, H, K, disp, out_images, out_ids, stream);

@@ -141,8 +141,10 @@ struct OccGrid {
 struct Workspace {
     float4* state[2] = {nullptr, nullptr};    // compact {pix, rgb} lists
     float4* aux[2] = {nullptr, nullptr};      // their {view depth, normal} (depth and normal modes)
-    uint32_t* order = nullptr;                 // chain engine: tile scores, then the tile order
+    uint32_t* order = nullptr;                 // chain engine: the tile order, then the tile scores
     size_t order_cap = 0;                      // uint32 entries
+    float4* entries = nullptr;                 // chain engine: entry lists (kEntryStride float4 each)
+    size_t entry_cap = 0;                      // float4 entries
     size_t aux_cap = 0;
     size_t state_cap = 0;                      // entries per list
     uint32_t* counters = nullptr;              // kCounterWords
@@ -156,9 +158,9 @@ struct Workspace {
 
 // Release a workspace's buffers on `stream` (stream-ordered).
 void free_workspace(Workspace& w, hipStream_t stream);
-// Room for `entries` uint32 of tile scores and order in a growable workspace
-// (fixed and external workspaces are left as they are).
-rcp_status ensure_order(Workspace& w, size_t entries, hipStream_t stream);
+// Room for `order` uint32 of tile scores and order and for `lists` entry lists
+// in a growable workspace (fixed and external workspaces are left as they are).
+rcp_status ensure_tiles(Workspace& w, size_t order, size_t lists, hipStream_t stream);
 
 constexpr size_t kViewBytes = 512;
 
@@ -209,12 +211,22 @@ struct BatchWorkspace {
     void* staging = nullptr;      // pinned host copy of the view table (servers only), view_cap views
     uint32_t* order = nullptr;    // a one-view batch's tile order and scores (chain engine, cost order)
     size_t order_cap = 0;         // uint32 entries
+    float4* entries = nullptr;    // entry lists
+    size_t entry_cap = 0;         // float4 entries
 };
 
 // Tiles of the largest one-view batch a server slot hands out in cost order
 // (2^18 tiles: 16.8M pixels, a 4K view with room to spare); larger views keep
 // the screen order, since a slot's buffers never grow.
 constexpr size_t kServerOrderTiles = size_t(1) << 18;
+
+// Entry lists of the chain engine (float4 each): one per 1024 pixels.  A server
+// slot holds kServerEntries (34 MB, 67M pixels in one launch); a batch allocates
+// what it needs, up to kMaxBatchEntries (537 MB, 10^9 pixels).  Larger
+// launches start their rays at the scene's root.
+constexpr size_t kEntryStride = 32;
+constexpr size_t kServerEntries = size_t(1) << 16;
+constexpr uint64_t kMaxBatchEntries = uint64_t(1) << 20;
 
 struct Tuning {
     int refill_min = -1;          // < 0: the library default for the launch

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
         }
 
         // ---- one traversal step -------------------------------------------
-        if (alive && tv.node != -1) trav_step<STATS>(tv, a.sc, st, a.exit_lanes, cnt);
+        if (alive && tv.node != -1) trav_step<STATS, false>(tv, a.sc, st, a.exit_lanes, cnt);
 
         // ---- finished rays: shade, write, compact ----------------------------
         const bool done = alive && tv.node == -1;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void k_trace_rays(DevScene sc, const float*
         Trav tv;
         trav_init(tv, sc, o, d, st);
         TravCount cnt;
-        while (tv.node != -1) trav_step<false>(tv, sc, st, 0u, cnt);
+        while (tv.node != -1) trav_step<false, false>(tv, sc, st, 0u, cnt);
         const bool hit = tv.h.id != INT_MAX;
         out_t[r] = hit ? tv.h.t : INFINITY;
         out_id[r] = hit ? tv.h.id : -1;
@@ -372,9 +372,21 @@ rcp_status ensure_workspace(rcp_scene* s, Workspace& w, size_t n_state, size_t n
     return RCP_OK;
 }
 
-rcp_status ensure_order(Workspace& w, size_t entries, hipStream_t stream) {
-    if (w.fixed || w.external) return RCP_OK;   // renders without room for it keep the screen order
-    return grow_buffer(&w.order, w.order_cap, entries, stream);
+rcp_status ensure_tiles(Workspace& w, size_t order, size_t lists, hipStream_t stream) {
+    if (w.fixed || w.external) return RCP_OK;   // renders use what fits
+    if (w.entries && order <= w.order_cap && kEntryStride * lists <= w.entry_cap) return RCP_OK;
+    // one allocation, the lists first
+    stream_free(w.entries, stream);
+    w.entries = nullptr;
+    w.order = nullptr;
+    w.entry_cap = w.order_cap = 0;
+    void* p = nullptr;
+    RCP_TRY_STATUS(stream_alloc(&p, sizeof(float4) * kEntryStride * lists + sizeof(uint32_t) * order, stream));
+    w.entries = (float4*)p;
+    w.entry_cap = kEntryStride * lists;
+    w.order = (uint32_t*)(w.entries + w.entry_cap);
+    w.order_cap = order;
+    return RCP_OK;
 }
 
 void free_workspace(Workspace& w, hipStream_t stream) {
@@ -390,7 +402,7 @@ void free_workspace(Workspace& w, hipStream_t stream) {
     stream_free(w.spill, stream);
     stream_free(w.stats, stream);
     stream_free(w.view, stream);
-    stream_free(w.order, stream);
+    stream_free(w.entries, stream);   // and the order
     w = Workspace{};
 }
 

@@ -101,6 +101,9 @@ __device__ inline void wave_fetch(uint32_t* ctr, uint32_t n_items, uint32_t n_id
 // keep plain tile rows (super_log2 = 0).  (Measured on the terrain frame:
 // 8 x 8 tiles 1.8% faster than plain tile rows, 16 x 16 3.5%; super-tiles
 // clipped to the image instead of padded were 2% slower than padded ones.)
+// Batches take the super-tiles column by column (super_rows of them each): a
+// band then holds sky and ground of its views in equal parts.  (16 views: 6%
+// faster; single renders, whose bands are sorted by cost, 6% slower.)
 constexpr int kSuperLog2 = 4;
 
 inline int super_log2_for(int W, int H, int tile_log2w) {
@@ -118,13 +121,14 @@ inline uint64_t view_tile_items(int W, int H, int tile_log2w, int super_log2) {
 }
 
 __device__ inline void tile_pixel(uint32_t local, uint32_t tiles_x, uint32_t tile_log2w, uint32_t super_log2, int& x,
-                                  int& y) {
+                                  int& y, uint32_t super_rows = 0) {
     const uint32_t tile = local >> 6, l = local & 63u;
     const uint32_t tw = 1u << tile_log2w;
     const uint32_t sl = super_log2, sm = (1u << sl) - 1u;
     const uint32_t st = tile >> (2u * sl), w = tile & ((1u << (2u * sl)) - 1u);
     const uint32_t sx = (tiles_x + sm) >> sl;   // super-tiles per row
-    const uint32_t tx = ((st % sx) << sl) + (w & sm), ty = ((st / sx) << sl) + (w >> sl);
+    const uint32_t bx = super_rows ? st / super_rows : st % sx, by = super_rows ? st % super_rows : st / sx;
+    const uint32_t tx = (bx << sl) + (w & sm), ty = (by << sl) + (w >> sl);
     x = (int)(tx * tw + (l & (tw - 1u)));
     y = (int)(ty * (64u >> tile_log2w) + (l >> tile_log2w));
 }
@@ -369,6 +373,8 @@ struct Trav {
                             // the exit plane is at off ^ 16
     int32_t node;           // >= 0 inner node, other negative: leaf link, -1: finished
     uint32_t budget;
+    uint32_t todo;          // entry lists (chain engine): items the ray has still to visit, nearest first,
+    uint32_t items;         // and the LDS byte address of their links
     float lim;              // h.t * kSlack
     Hit h;
 };
@@ -451,7 +457,19 @@ __device__ inline float4 f4(V4 v) { return make_float4(v.x, v.y, v.z, v.w); }
 // The 16 bytes at LDS byte address `byte` of the workgroup.
 __device__ inline float4 lds_f4(uint32_t byte) { return f4(*(const LdsV4*)(size_t)byte); }
 
-template <bool STATS, class Stack>
+// The ray's next node: the newest stack entry or, with entry lists (ENTRY,
+// chain engine), the nearest item of its list not taken yet; -1 when the
+// ray is finished.
+template <bool ENTRY, class Stack>
+__device__ inline int32_t next_node(Trav& tv, Stack& st) {
+    const int32_t n = st.pop();
+    if (!ENTRY || n != -1 || tv.todo == 0u) return n;
+    const uint32_t i = (uint32_t)__builtin_ctz(tv.todo);
+    tv.todo &= tv.todo - 1u;
+    return *(const LdsI32*)(size_t)(tv.items + 4u * i);
+}
+
+template <bool STATS, bool ENTRY, class Stack>
 __device__ inline int32_t visit_inner4(Trav& tv, int32_t node, const DevScene& sc, Stack& st, TravCount& cnt) {
     // byte offsets of the entry and exit planes of the three axes (the
     // node array is limited to 4 GB, so offsets fit 32 bits), the same in
@@ -460,7 +478,8 @@ __device__ inline int32_t visit_inner4(Trav& tv, int32_t node, const DevScene& s
     const uint32_t e0 = base + tv.off[0], e1 = base + tv.off[1], e2 = base + tv.off[2];
     const uint32_t f0 = e0 ^ 16u, f1 = e1 ^ 16u, f2 = e2 ^ 16u;
     float4 n0, x0, n1, x1, n2, x2, lk;
-    if ((uint32_t)node < sc.top_count) {
+    const bool in_lds = !ENTRY && (uint32_t)node < sc.top_count;
+    if (in_lds) {
         // the top levels, staged in LDS: LDS reads do not use the vector
         // memory address path (the compiler barrier keeps the two paths from
         // being merged into flat loads)
@@ -478,7 +497,7 @@ __device__ inline int32_t visit_inner4(Trav& tv, int32_t node, const DevScene& s
     }
     if (STATS) {
         ++cnt.nodes;
-        if ((uint32_t)node < sc.top_count) ++cnt.lds;
+        if (in_lds) ++cnt.lds;
     }
     const float lim = tv.lim;
     uint32_t key[4];    // entry distance bits of hit children (t >= 0), all ones for the rest
@@ -510,7 +529,7 @@ __device__ inline int32_t visit_inner4(Trav& tv, int32_t node, const DevScene& s
     order2(key[0], val[0], key[2], val[2]);
     order2(key[1], val[1], key[3], val[3]);
     order2(key[1], val[1], key[2], val[2]);
-    if (!any) return st.pop();
+    if (!any) return next_node<ENTRY>(tv, st);
     if (key[1] != 0xFFFFFFFFu) {   // two hits or more: push all but the nearest
         const bool h2 = key[2] != 0xFFFFFFFFu, h3 = key[3] != 0xFFFFFFFFu;
         const int32_t e0 = h3 ? val[3] : (h2 ? val[2] : val[1]);
@@ -518,6 +537,29 @@ __device__ inline int32_t visit_inner4(Trav& tv, int32_t node, const DevScene& s
         st.push_up_to_3(e0, e1, val[1], 1u + (h2 ? 1u : 0u) + (h3 ? 1u : 0u), cnt.spill);
     }
     return val[0];
+}
+
+// The boxes of four items of an entry list, laid out like a node's planes at
+// LDS byte address `at`: a bit for each one the ray meets (the rules of
+// visit_inner4; no hit bounds the ray yet).
+__device__ inline uint32_t meet4(const Trav& tv, uint32_t at) {
+    const uint32_t e0 = at + tv.off[0], e1 = at + tv.off[1], e2 = at + tv.off[2];
+    const uint32_t f0 = at + (tv.off[0] ^ 16u), f1 = at + (tv.off[1] ^ 16u), f2 = at + (tv.off[2] ^ 16u);
+    const float4 n0 = lds_f4(e0), x0 = lds_f4(f0), n1 = lds_f4(e1), x1 = lds_f4(f1), n2 = lds_f4(e2), x2 = lds_f4(f2);
+    uint32_t mask = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a0 = __builtin_fmaf(lane_of(n0, i), tv.inv[0], -tv.ent[0]);
+        const float b0 = __builtin_fmaf(lane_of(x0, i), tv.inv[0], -tv.ext[0]);
+        const float a1 = __builtin_fmaf(lane_of(n1, i), tv.inv[1], -tv.ent[1]);
+        const float b1 = __builtin_fmaf(lane_of(x1, i), tv.inv[1], -tv.ext[1]);
+        const float a2 = __builtin_fmaf(lane_of(n2, i), tv.inv[2], -tv.ent[2]);
+        const float b2 = __builtin_fmaf(lane_of(x2, i), tv.inv[2], -tv.ext[2]);
+        const float tmin = fmaxf(fmaxf(a0, a1), fmaxf(a2, 0.0f));
+        const float tmax = fminf(fminf(b0, b1), b2);
+        mask |= tmin <= tmax ? 1u << i : 0u;   // (an unused item's NaN planes: false)
+    }
+    return mask;
 }
 
 // Test the triangles of leaf `link` against the ray, keeping the closest hit.
@@ -561,7 +603,7 @@ __device__ inline void visit_leaf(Trav& tv, int32_t link, const DevScene& sc, Tr
 // threshold and 5% faster at the new default of 16.)
 constexpr int kMaxDescent = 256;   // node visits of one step (the step ends, the ray goes on)
 
-template <bool STATS, class Stack>
+template <bool STATS, bool ENTRY, class Stack>
 __device__ inline void trav_step(Trav& tv, const DevScene& sc, Stack& st, uint32_t exit_lanes, TravCount& cnt) {
     if (--tv.budget == 0u) {
         // only a malformed tree gets here: end the ray and raise the scene's
@@ -573,7 +615,7 @@ __device__ inline void trav_step(Trav& tv, const DevScene& sc, Stack& st, uint32
     int32_t node = tv.node;
     int32_t leaf = -1;
     for (int it = 0; it < kMaxDescent; ++it) {
-        if (node < -1 && leaf == -1) { leaf = node; node = st.pop(); }
+        if (node < -1 && leaf == -1) { leaf = node; node = next_node<ENTRY>(tv, st); }
         // (the ballot of each compare alone maps onto one VALU compare; a
         // ballot of their conjunction was materialised through a select)
         const unsigned long long holding = wave_ballot(leaf != -1);
@@ -583,9 +625,168 @@ __device__ inline void trav_step(Trav& tv, const DevScene& sc, Stack& st, uint32
         // theirs (every searching lane has advanced one node this step)
         const uint32_t n_search = popc_u32(searching);
         if (it > 0 && n_search <= exit_lanes && popc_u32(holding) >= n_search) break;
-        if (node >= 0) node = visit_inner4<STATS>(tv, node, sc, st, cnt);
+        if (node >= 0) node = visit_inner4<STATS, ENTRY>(tv, node, sc, st, cnt);
     }
     if (leaf != -1) visit_leaf<STATS>(tv, leaf, sc, cnt);
+    tv.node = node;
+}
+
+// ---- traversal with a leaf queue ------------------------------------------------
+// A wave's rays put the leaves they reach into a queue in LDS and go on; the
+// queue is worked off by all 64 lanes of the wave, whichever rays the leaves
+// belong to, so a lane without a ray, or with a ray that has just missed, tests
+// triangles for the others.  (When each lane tested its own leaf, a triangle
+// test ran with 17 of 64 lanes on the 1080p terrain frame: two tests per leaf,
+// and leaves in a quarter of the lanes.)  What the triangle test needs of a ray
+// lies in LDS, and so does its best hit, as one 64-bit word (t, triangle index):
+// the least word is the nearest hit and, at equal t, the lowest index, so lanes
+// that test leaves of one ray at the same time combine with a 64-bit minimum.
+constexpr uint32_t kQueueLen = 128;          // entries; at most 63 wait when up to 64 are added
+// byte offsets in the wave's part of LDS, one word per lane each
+constexpr uint32_t kRecS = 0, kRecO = 768;   // Sx, Sy, Sz; ox, oy, oz
+constexpr uint32_t kRecBase = 1536;          // tri_base, bit 31: d[kz] < 0
+constexpr uint32_t kRecKey = 1792;           // best hit: index, t bits (8 bytes per lane)
+constexpr uint32_t kRecSlot = 2304;          // its packed triangle index, bit 31: front
+constexpr uint32_t kQueueLink = 2560;        // leaf links
+constexpr uint32_t kQueueOwner = kQueueLink + 4 * kQueueLen;   // their rays' lanes (bytes)
+constexpr uint32_t kQueueBytes = kQueueOwner + kQueueLen;      // 3200 per wave
+
+typedef __attribute__((address_space(3))) uint32_t LdsU32;
+typedef __attribute__((address_space(3))) float LdsF32;
+typedef __attribute__((address_space(3))) unsigned long long LdsU64;
+typedef __attribute__((address_space(3))) uint8_t LdsU8;
+
+__device__ inline float lds_get_f(uint32_t at) { return *(const LdsF32*)(size_t)at; }
+__device__ inline void lds_put_f(uint32_t at, float v) { *(LdsF32*)(size_t)at = v; }
+__device__ inline uint32_t lds_get_u(uint32_t at) { return *(const LdsU32*)(size_t)at; }
+__device__ inline void lds_put_u(uint32_t at, uint32_t v) { *(LdsU32*)(size_t)at = v; }
+
+// Orders one wave's LDS writes before its other lanes' reads: LDS serves a
+// wave's accesses in order, and the compiler must keep that order too.
+__device__ inline void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Ray constants and an empty hit in the lane's record (wave: byte address of
+// the wave's part).
+__device__ inline void record_ray(const RayW& r, uint32_t wave) {
+    const uint32_t at = wave + 4u * (threadIdx.x & 63u);
+    lds_put_f(at + kRecS, r.Sx);
+    lds_put_f(at + kRecS + 256, r.Sy);
+    lds_put_f(at + kRecS + 512, r.Sz);
+    lds_put_f(at + kRecO, r.ox);
+    lds_put_f(at + kRecO + 256, r.oy);
+    lds_put_f(at + kRecO + 512, r.oz);
+    lds_put_u(at + kRecBase, r.tri_base | (r.swap ? 0x80000000u : 0u));
+    *(LdsU64*)(size_t)(wave + kRecKey + 8u * (threadIdx.x & 63u)) =
+        ((unsigned long long)0x7F800000u << 32) | (uint32_t)INT_MAX;
+}
+
+// The lane's best hit so far.
+__device__ inline void recorded_hit(Hit& h, uint32_t wave) {
+    const unsigned long long key = *(const LdsU64*)(size_t)(wave + kRecKey + 8u * (threadIdx.x & 63u));
+    const uint32_t s = lds_get_u(wave + kRecSlot + 4u * (threadIdx.x & 63u));
+    h.t = __uint_as_float((uint32_t)(key >> 32));
+    h.id = (int32_t)(uint32_t)key;
+    h.slot = s & 0x7FFFFFFFu;
+    h.front = (s >> 31) != 0u;
+}
+
+// Test the newest n (<= 64) queued leaves, one per lane; the whole wave.
+__device__ inline void test_leaves(const DevScene& sc, uint32_t wave, uint32_t first, uint32_t n) {
+    const uint32_t l = threadIdx.x & 63u;
+    unsigned long long mine = ~0ull;
+    uint32_t slot = 0, owner = 0;
+    if (l < n) {
+        const uint32_t link = lds_get_u(wave + kQueueLink + 4u * (first + l));
+        owner = *(const LdsU8*)(size_t)(wave + kQueueOwner + first + l);
+        const uint32_t at = wave + 4u * owner;
+        RayW r;
+        r.Sx = lds_get_f(at + kRecS);
+        r.Sy = lds_get_f(at + kRecS + 256);
+        r.Sz = lds_get_f(at + kRecS + 512);
+        r.ox = lds_get_f(at + kRecO);
+        r.oy = lds_get_f(at + kRecO + 256);
+        r.oz = lds_get_f(at + kRecO + 512);
+        const uint32_t base = lds_get_u(at + kRecBase);
+        r.tri_base = base & 0x7FFFFFFFu;
+        r.swap = (base >> 31) != 0u;
+        const uint32_t tri = (link >> 3) & 0x0FFFFFFFu, count = (link & 7u) + 1u;
+        for (uint32_t j = 0; j < count; ++j) {
+            const float4* tp = sc.tris + 3 * (size_t)(r.tri_base + tri + j);
+            const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+            float t;
+            bool front;
+            if (hit_triangle(r, v0, v1, v2, t, front)) {
+                const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | __float_as_uint(v0.w);
+                if (key < mine) {
+                    mine = key;
+                    slot = (tri + j) | (front ? 0x80000000u : 0u);
+                }
+            }
+        }
+    }
+    LdsU64* best = (LdsU64*)(size_t)(wave + kRecKey + 8u * owner);
+    if (mine != ~0ull) __hip_atomic_fetch_min(best, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    wave_lds_fence();
+    // the lane whose hit is its ray's best now (triangle indices differ, so
+    // there is one) says which triangle it was
+    if (mine != ~0ull && *best == mine) lds_put_u(wave + kRecSlot + 4u * owner, slot);
+    wave_lds_fence();
+}
+
+// Advance the wave's rays (tv.node != -1) until at least `enough` lanes have
+// none, all leaves found are tested, or kMaxDescent rounds have passed.
+// Each round takes every ray one node or leaf further.  The queue is worked
+// off when it holds a leaf for every lane, or when no more than exit_lanes
+// rays are left and at least as many leaves wait (tests that wait for more
+// leaves would let the rays go on past hits that end them).
+// The whole wave calls this; lanes without a ray have tv.node == -1.
+template <class Stack>
+__device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint32_t wave, uint32_t exit_lanes,
+                                  uint32_t enough) {
+    TravCount cnt;
+    int32_t node = tv.node;
+    uint32_t waiting = 0;   // wave-uniform: queued leaves
+    const uint32_t l = threadIdx.x & 63u;
+    const uint32_t most = sc.step_budget < (uint32_t)kMaxDescent ? sc.step_budget : (uint32_t)kMaxDescent;
+    uint32_t it = 0;
+    for (;;) {
+        const unsigned long long leaves = wave_ballot(node < -1);
+        if (leaves != 0ull) {
+            if (node < -1) {
+                const uint32_t at = waiting + lanes_below(leaves);
+                lds_put_u(wave + kQueueLink + 4u * at, (uint32_t)node);
+                *(LdsU8*)(size_t)(wave + kQueueOwner + at) = (uint8_t)l;
+                node = next_node<true>(tv, st);
+            }
+            waiting += popc_u32(leaves);
+        }
+        const uint32_t going = popc_u32(wave_ballot(node != -1));
+        const bool stop = 64u - going >= enough || it >= most;
+        if (waiting >= 64u || (waiting != 0u && (stop || (going <= exit_lanes && waiting >= going)))) {
+            do {
+                const uint32_t n = waiting < 64u ? waiting : 64u;
+                waiting -= n;
+                wave_lds_fence();
+                test_leaves(sc, wave, waiting, n);
+            } while (stop && waiting != 0u);
+            tv.lim = lds_get_f(wave + kRecKey + 8u * l + 4u) * kSlack;
+        }
+        if (stop) break;
+        ++it;
+        if (node >= 0) node = visit_inner4<false, true>(tv, node, sc, st, cnt);
+    }
+    // the bound that only a malformed tree reaches (every round enters a node
+    // or a leaf): end the ray and raise the scene's error flag
+    if (node != -1) {
+        if (tv.budget <= it) {
+            __hip_atomic_store(sc.err_flag, kErrStepBudget, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            node = -1;
+        }
+        tv.budget -= it;
+    }
     tv.node = node;
 }
 

@@ -1,0 +1,77 @@
+"""GPU tests of the chain engine's entry lists and leaf queue, against the
+per-pass engine (which has neither: every ray starts at the root) and, on the
+small scenes, the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+import oracle
+import scenegen
+from paper_2312_12392_amd import rcp
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+def patch_camera(eye, target=(0.0, 0.05, 0.0), fov=60.0):
+    return scenegen.camera_look_at(eye, target, [0, 1, 0], fov)
+
+
+def both_engines(s, cam, W, H, K, le, ld, mode=rcp.RCP_MODE_COLOR, z0=0.0, with_ids=True):
+    out = []
+    for e in (rcp.RCP_ENGINE_CHAIN, rcp.RCP_ENGINE_PASSES):
+        s.set_engine(e)
+        out.append(s.render(cam, W, H, K, le, ld, with_ids=with_ids, mode=mode, z0=z0))
+    torch.cuda.synchronize()
+    (a, ia), (b, ib) = out
+    assert torch.equal(a, b)
+    assert not with_ids or torch.equal(ia, ib)
+    return a, ia
+
+
+# sizes around a tile (8), a tile group (32 x 32 pixels) and the super-tiles
+@pytest.mark.parametrize("W,H", [(1, 1), (31, 33), (32, 32), (65, 31), (257, 130)])
+@pytest.mark.parametrize("mode,le,ld,z0", [(rcp.RCP_MODE_COLOR, 0.0, 0.05, 0.0), (rcp.RCP_MODE_COLOR, 0.3, 0.6, 0.0),
+                                           (rcp.RCP_MODE_DEPTH, 0.02, 0.1, 1.0), (rcp.RCP_MODE_DEPTH, 0.5, 0.5, -3.0),
+                                           (rcp.RCP_MODE_NORMAL, 0.1, 0.3, 0.0)])
+def test_entry_lists_against_the_root(W, H, mode, le, ld, z0):
+    """Wide displacements, a lambda beyond which no pyramid bounds the rays
+    (0.6: lists without culling), eyes above, inside and under the terrain."""
+    say("entry lists", W, H, mode, le, ld)
+    s = rcp.Scene(scenegen.terrain_patch(seed=17, cells=40, n_boxes=30))
+    for eye, target in [((0, 0.45, -1.25), (0, 0.05, 0)), ((0.1, 0.16, 0.2), (0.9, 0.1, 0.3)), ((0.3, -0.2, 0.1), (0.2, 0.6, 0.4))]:
+        both_engines(s, patch_camera(eye, target), W, H, 5, le, ld, mode, z0)
+    s.close()
+
+
+@pytest.mark.parametrize("fov,background", [(4.0, 0.5), (150.0, 0.5), (60.0, 3.0)])
+def test_entry_lists_lens_and_background(fov, background):
+    """Narrow and very wide lenses; a background above 1, which displaces by
+    more than lambda (misses are not clamped by the shading table)."""
+    say("entry lists lens", fov, background)
+    sc = scenegen.terrain_patch(seed=3, cells=30, n_boxes=10)
+    sc.background = np.full(3, background, np.float32)
+    s = rcp.Scene(sc)
+    cam = patch_camera((0.2, 0.5, -1.1), fov=fov)
+    img, ids = both_engines(s, cam, 90, 70, 5, 0.0, 0.1)
+    o_img, o_ids = oracle.OracleScene(sc, use_bvh=True).render(cam, 90, 70, 5, 0.0, 0.1)
+    assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
+
+
+@pytest.mark.parametrize("max_leaf", [1, 8])
+@pytest.mark.parametrize("n", [1, 2, 5, 16, 17, 300])
+def test_entry_lists_of_small_trees(n, max_leaf):
+    """Trees from a single leaf to more nodes than a list holds items, with
+    the leaf queue's shortest and longest leaves."""
+    say("entry lists, small tree", n, max_leaf)
+    sc = scenegen.soup_scene(seed=n, n=n)
+    s = rcp.Scene(sc, rcp.build_options(max_leaf=max_leaf))
+    cam = scenegen.camera_look_at([0, 0, -2], [0, 0, 0], [0, 1, 0], 60.0)
+    img, ids = both_engines(s, cam, 70, 50, 6, 0.0, 0.05)
+    o_img, o_ids = oracle.OracleScene(sc, use_bvh=False).render(cam, 70, 50, 6, 0.0, 0.05)
+    assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
