@@ -209,7 +209,9 @@ rcp_status rcp_scene_info(const rcp_scene* scene, rcp_scene_stats* out);
  *   out_images  device, [K][H][W][3] float32; receives I_1..I_K
  *   out_ids     device, [K][H][W] int32 hit triangle or -1; may be NULL
  * Pixels whose colour did not change between two passes keep it (the next
- * ray would be identical) and drop out of the following passes.
+ * ray would be identical) and drop out of the following passes; in
+ * RCP_MODE_COLOR the default engine also ends the chain of a pixel that
+ * returns to its colour of two or three passes before (it repeats from there).
  * Requires W, H >= 1, 1 <= K <= 64, W * H <= 2^27, a unit orthogonal
  * camera basis (|1 - |v|| <= 1e-5, |dot| <= 1e-5), tan_half_fovy > 0.
  * Asynchronous on hip_stream. */

@@ -259,7 +259,40 @@ __device__ inline void chain_body(const ChainArgs& a) {
                         q[0] = rgb[0]; q[1] = rgb[1]; q[2] = rgb[2];
                         if (vw.ids) vw.ids[(size_t)kk * P + pix] = hid;
                     }
-                    const bool next = changed && k + 1 < vw.K;
+                    bool next = changed && k + 1 < vw.K;
+                    if (ENTRY && !AUX && next && k >= 2) {
+                        // The colour of two or three passes ago again: that pass's
+                        // successor follows, and so on, so the remaining images
+                        // repeat with that period.  The colours of those passes
+                        // are read back from the pixel's own images.  (Terrain
+                        // frames: 9% of the rays at 1M triangles and K = 6; 4K
+                        // frame of 16M triangles, K = 8: 7.73 -> 5.96 ms.  The
+                        // depth and normal modes would need their hit data of
+                        // those passes as well: kept in registers, no faster at
+                        // 1080p and 4% slower on a small frame.)
+                        const float* q2 = vw.out + ((size_t)(k - 2) * P + pix) * 3;
+                        const float* q3 = k >= 3 ? vw.out + ((size_t)(k - 3) * P + pix) * 3 : q2;
+                        const float c2[3] = {q2[0], q2[1], q2[2]}, c3[3] = {q3[0], q3[1], q3[2]};
+                        int period = 0;
+                        if (__float_as_uint(c2[0]) == __float_as_uint(rgb[0]) && __float_as_uint(c2[1]) == __float_as_uint(rgb[1]) &&
+                            __float_as_uint(c2[2]) == __float_as_uint(rgb[2]))
+                            period = 2;
+                        else if (k >= 3 && __float_as_uint(c3[0]) == __float_as_uint(rgb[0]) &&
+                                 __float_as_uint(c3[1]) == __float_as_uint(rgb[1]) &&
+                                 __float_as_uint(c3[2]) == __float_as_uint(rgb[2]))
+                            period = 3;
+                        if (period != 0) {
+                            next = false;
+                            for (int kk = k + 1; kk < vw.K; ++kk) {
+                                const size_t to = (size_t)kk * P + pix, from = to - (size_t)period * P;
+                                const float r0 = vw.out[3 * from], r1 = vw.out[3 * from + 1], r2 = vw.out[3 * from + 2];
+                                vw.out[3 * to] = r0;
+                                vw.out[3 * to + 1] = r1;
+                                vw.out[3 * to + 2] = r2;
+                                if (vw.ids) vw.ids[to] = vw.ids[from];
+                            }
+                        }
+                    }
                     if (STATS) {
                         unsigned long long* sk = lstats + kStatCols * k;
                         atomicAdd(&sk[0], 1ull);

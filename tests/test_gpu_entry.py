@@ -1,6 +1,6 @@
-"""GPU tests of the chain engine's entry lists and leaf queue, against the
-per-pass engine (which has neither: every ray starts at the root) and, on the
-small scenes, the oracle."""
+"""GPU tests of the chain engine's entry lists, leaf queue and repeating
+chains, against the per-pass engine (which has none of them: every ray starts
+at the root and every pass is traced) and, on the small scenes, the oracle."""
 import numpy as np
 import pytest
 
@@ -74,4 +74,30 @@ def test_entry_lists_of_small_trees(n, max_leaf):
     img, ids = both_engines(s, cam, 70, 50, 6, 0.0, 0.05)
     o_img, o_ids = oracle.OracleScene(sc, use_bvh=False).render(cam, 70, 50, 6, 0.0, 0.05)
     assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
+
+
+@pytest.mark.parametrize("K", [3, 4, 5, 7, 20])
+@pytest.mark.parametrize("with_ids", [True, False])
+def test_repeating_chains(K, with_ids):
+    """Two and three stripes whose colours send the next ray back: many pixels
+    repeat with period 2 or 3, from every pass on."""
+    say("repeating chains", K, with_ids)
+    rng = np.random.default_rng(5)
+    n = 48
+    x = np.linspace(-1.0, 1.0, n + 1)
+    v, t, c = [], [], []
+    for i in range(n):
+        b = len(v)
+        v += [[x[i], -1, 0], [x[i + 1], -1, 0], [x[i + 1], 1, 0], [x[i], 1, 0]]
+        t += [[b, b + 2, b + 1], [b, b + 3, b + 2]]
+        r = [(0.25, 0.75), (0.2, 0.5, 0.8)][i % 2][i // 2 % (2 + i % 2)]
+        c += [[r, 0.5, 0.5], [r, 0.5, float(rng.uniform(0.4, 0.6))]]
+    sc = scenegen.Scene(verts=np.array(v), idx=np.array(t), rgb=np.array(c), light=np.array([0, 0, -1.0]), name="stripes")
+    s = rcp.Scene(sc)
+    cam = scenegen.camera_look_at([0, 0, -1.5], [0, 0, 0], [0, 1, 0], 60.0)
+    img, _ = both_engines(s, cam, 120, 40, K, 0.0, 0.06, with_ids=with_ids)
+    a = img.cpu().numpy()
+    if K >= 5:   # the case is there: pixels that come back after two passes without having settled
+        assert np.any(np.any(a[2] != a[3], axis=-1) & np.all(a[2] == a[4], axis=-1))
     s.close()
