@@ -68,6 +68,8 @@ bool alloc_hook_fails() {
     return false;
 }
 
+bool alloc_hook_armed() { return g_alloc_left.load() >= 0; }
+
 uint32_t debug_step_budget() { return g_step_budget.load(); }
 
 int debug_list_canary() { return g_list_canary.load(); }

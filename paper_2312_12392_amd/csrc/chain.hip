@@ -74,6 +74,7 @@ struct ChainArgs {
     uint32_t n_items;         // work items of the launch
     uint32_t* fetch;          // kFetchParts work counters kFetchStride words apart, zero at launch
     int refill_min;
+    uint32_t take;               // most pixels a wave holds at once (64, or fewer so that a small launch fills the chip)
     uint32_t exit_lanes;
     int32_t* spill;
     uint32_t spill_stride;
@@ -313,15 +314,17 @@ __device__ inline void chain_body(const ChainArgs& a) {
                 ended = false;
             }
             const unsigned long long idle = wave_ballot(!alive && !pending);
-            const uint32_t n_idle = (uint32_t)__popcll(idle);
+            // (a wave that holds fewer pixels than lanes fills up to `take`)
+            const uint32_t held = 64u - popc_u32(idle);
+            const uint32_t n_idle = held < a.take ? a.take - held : 0u;
             uint32_t base = 0, lim = 0;
             const bool fetch = !drained && n_idle > 0u;
             if (fetch) wave_fetch(a.fetch, n_items, n_idle, part, parts_done, drained, base, lim);
             bool init = pending;
             uint32_t group = 0xFFFFFFFFu;   // ENTRY: tile group of a new pixel
             if (fetch && !alive && !pending) {
-                const uint32_t item = base + lanes_below(idle);
-                if (item < lim) {
+                const uint32_t nth = lanes_below(idle), item = base + nth;
+                if (nth < n_idle && item < lim) {
                     // the view holding this item: last begin <= item
                     if (!ONE) {
                         int lo = 0, hi = a.n_views;
@@ -470,6 +473,104 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
 template <bool STATS, int MODE, bool ONE, bool ENTRY>
 __global__ __launch_bounds__(kBlock) void k_chain_aux(ChainArgs a) {
     chain_body<STATS, MODE, ONE, ENTRY, ENTRY ? kEntryStack : kStack, kBlock>(a);
+}
+
+// ---- Small scenes: every triangle tested ----------------------------------------
+// A frame of few pixels leaves the chip idle while its chains wait on one
+// dependent node or triangle load after another, and a small scene of large,
+// overlapping triangles has a tree that prunes little.  Then the pixel's rays
+// are tested against all triangles by G lanes side by side, 64 / G pixels per
+// wave, each pixel's passes in a loop: no tree, no stack, no work queue, and
+// nothing before the launch.  The nearest hit is the least (t, triangle index)
+// word of the group, as in the leaf queue.
+template <int MODE, int G>
+__global__ __launch_bounds__(kBlock) void k_direct(DevScene sc, ViewDev v) {
+    constexpr bool AUX = MODE != RCP_MODE_COLOR;
+    const uint32_t P = (uint32_t)v.W * (uint32_t)v.H;
+    const uint32_t pixel = (blockIdx.x * kBlock + threadIdx.x) / G, sub = threadIdx.x % G;
+    const bool live = pixel < P;
+    const int y = (int)(pixel / (uint32_t)v.W), x = (int)(pixel - (uint32_t)y * (uint32_t)v.W);
+    float prev[3] = {0.5f, 0.5f, 0.5f};
+    float pa[4] = {INFINITY, 0.0f, 0.0f, 0.0f};
+    int k = live ? 0 : v.K;    // the pixel's pass; v.K: its chain has ended
+    while (wave_ballot(k < v.K) != 0ull) {
+        float o[3], d[3];
+        make_ray<MODE>(v.cam, v.hw, v.W, v.H, x, y, prev[0], prev[1], prev[2], pa, v.z0, v.le, v.ld, o, d);
+        const RayW r = ray_setup(o, d, dominant_axis(d), sc.n_tris);
+        unsigned long long best = ~0ull;
+        uint32_t slot = 0;
+        if (k < v.K) {
+            const float4* tp = sc.tris + 3 * (size_t)r.tri_base;
+            const uint32_t last = sc.n_tris - 1u;
+            uint32_t i = sub;
+            const float4* a = tp + 3 * (size_t)min(i, last);
+            float4 v0 = a[0], v1 = a[1], v2 = a[2];
+            for (; i < sc.n_tris; i += G) {
+                // the next triangle is loaded while this one is tested
+                const float4* b = tp + 3 * (size_t)min(i + G, last);
+                const float4 n0 = b[0], n1 = b[1], n2 = b[2];
+                float t;
+                bool front;
+                if (hit_triangle(r, v0, v1, v2, t, front)) {
+                    const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | __float_as_uint(v0.w);
+                    if (key < best) {
+                        best = key;
+                        slot = i | (front ? 0x80000000u : 0u);
+                    }
+                }
+                v0 = n0; v1 = n1; v2 = n2;
+            }
+        }
+#pragma unroll
+        for (int m = G / 2; m >= 1; m >>= 1) {
+            const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(best >> 32), m, 64);
+            const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)best, m, 64);
+            const uint32_t os = (uint32_t)__shfl_xor((int)slot, m, 64);
+            const unsigned long long other = ((unsigned long long)hi << 32) | lo;
+            if (other < best) {
+                best = other;
+                slot = os;
+            }
+        }
+        if (k >= v.K) continue;
+        // shade, write, and keep the inputs of the next pass or end the chain
+        float rgb[3] = {sc.bg[0], sc.bg[1], sc.bg[2]};
+        float na[4] = {INFINITY, 0.0f, 0.0f, 0.0f};
+        int32_t hid = -1;
+        if (best != ~0ull) {
+            const uint32_t tri = slot & 0x7FFFFFFFu;
+            const float4 c = sc.shade[2 * (size_t)tri + ((slot >> 31) ? 0 : 1)];
+            rgb[0] = c.x; rgb[1] = c.y; rgb[2] = c.z;
+            hid = (int32_t)(uint32_t)best;
+            if (AUX) {
+                const float t = __uint_as_float((uint32_t)(best >> 32));
+                float p3[3];
+#pragma unroll
+                for (int c3 = 0; c3 < 3; ++c3) p3[c3] = o[c3] + t * d[c3];
+                na[0] = ((p3[0] - v.cam.eye[0]) * v.cam.forward[0] + (p3[1] - v.cam.eye[1]) * v.cam.forward[1]) +
+                        (p3[2] - v.cam.eye[2]) * v.cam.forward[2];
+                const float4 nv = sc.normals[tri];
+                na[1] = nv.x; na[2] = nv.y; na[3] = nv.z;
+            }
+        }
+        bool changed = false;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) changed = changed || __float_as_uint(rgb[c]) != __float_as_uint(prev[c]);
+        if (AUX)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) changed = changed || __float_as_uint(na[c]) != __float_as_uint(pa[c]);
+        const int k_end = changed ? k + 1 : v.K;
+        for (int kk = k + (int)sub; kk < k_end; kk += G) {
+            float* q = v.out + ((size_t)kk * P + pixel) * 3;
+            q[0] = rgb[0]; q[1] = rgb[1]; q[2] = rgb[2];
+            if (v.ids) v.ids[(size_t)kk * P + pixel] = hid;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) prev[c] = rgb[c];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) pa[c] = na[c];
+        k = k_end;
+    }
 }
 
 // Zero the work counters (kFetchParts per launch) and the stats.
@@ -985,6 +1086,20 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
     return RCP_OK;
 }
 
+// Pixels a wave holds at once.  A launch of few pixels would leave most of
+// the chip's waves without any while the others' rays wait for the slowest of
+// 64: the smallest power of two is taken that gives each resident wave at most
+// two handfuls.  (20,000-triangle terrain, K = 6, microseconds with 64 / the
+// choice: 64 x 64 353 / 223 with 1, 320 x 200 396 / 327 with 8, 512 x 512
+// 401 / 362 with 32; halving or doubling the choice is slower or the same.)
+void set_take(ChainArgs& a, const ChainGrid& g) {
+    const uint64_t waves = (uint64_t)g.threads() / 64u;
+    a.take = 1u;
+    while (a.take < 64u && (uint64_t)a.n_items > 2u * waves * a.take) a.take *= 2u;
+    // the refill threshold in idle lanes, in proportion
+    a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
+}
+
 rcp_status launch_chain(const ChainGrid& g, hipStream_t stream, ChainArgs a) {
     void* args[] = {(void*)&a};
     RCP_HIP(hipLaunchKernel(g.k.fn, dim3((unsigned)g.blocks), dim3((unsigned)g.k.block), args, g.smem, stream));
@@ -1116,6 +1231,7 @@ rcp_status launch_one_view(rcp_scene* s, Workspace& w, const Launch& lp, const C
     a.n_items = (uint32_t)view_items(view);
     a.fetch = w.counters;
     a.refill_min = lp.refill_min;
+    set_take(a, g);
     a.exit_lanes = (uint32_t)lp.exit_lanes;
     a.spill = w.spill;
     a.spill_stride = g.threads();
@@ -1135,11 +1251,65 @@ bool entries_fit(const rcp_scene* s, const float4* buf, size_t cap, uint64_t n) 
     return s->dev.n_nodes > 0 && buf && cap >= kEntryStride * n;
 }
 
+template <int MODE>
+void launch_direct_mode(const rcp_scene* s, const ViewDev& v, int lanes, hipStream_t stream) {
+    const uint64_t threads = (uint64_t)v.W * (uint64_t)v.H * (uint64_t)lanes;
+    const dim3 grid((unsigned)((threads + kBlock - 1) / kBlock));
+    switch (lanes) {
+        case 64: hipLaunchKernelGGL((k_direct<MODE, 64>), grid, dim3(kBlock), 0, stream, s->dev, v); break;
+        case 16: hipLaunchKernelGGL((k_direct<MODE, 16>), grid, dim3(kBlock), 0, stream, s->dev, v); break;
+        default: hipLaunchKernelGGL((k_direct<MODE, 4>), grid, dim3(kBlock), 0, stream, s->dev, v); break;
+    }
+}
+
+// Lanes per pixel of the direct kernel, or 0 where the tree is faster.
+//
+// Its time is that of the pixels times triangles it tests; the tree's is a
+// chain of dependent loads per pass, the longer the higher the tree's SAH cost
+// (expected visits and tests per ray): 10-20 for a terrain of any size, about
+// three quarters of the triangle count for a soup of large triangles.  K = 6,
+// microseconds, direct / tree:
+//   terrain, 1024 triangles (SAH cost 12): 64 x 64 42 / 190, 128 x 128 99 / 200,
+//     320 x 200 246 / 200; 4096 triangles: 64 x 64 130 / 210, 128 x 128 375 / 230;
+//     256 triangles: 320 x 200 85 / 190, 640 x 400 224 / 190
+//   soup, 256 triangles (211): 64 x 64 21 / 733, 1280 x 720 412 / 779;
+//     2048 triangles (1547): 640 x 400 890 / 4200; 16384 (11959): 64 x 64 518 / 13700
+// so it is taken up to 20M tests per pass, or half a million per unit of SAH
+// cost, and for no more triangles than a group tests in the time the tree's
+// passes take at least (4096, or 16 per unit of SAH cost).
+// 64 lanes per pixel leave few pixels per wave, which small frames want; 16
+// are faster from about 32K pixels on, 4 for large frames of few triangles
+// (128 triangles: 640 x 400 104 / 77 with 4 / 16 lanes, 1280 x 720 227 / 251).
+int direct_lanes(const rcp_scene* s, int W, int H) {
+    const double tris = s->dev.n_tris, pixels = (double)W * H, sah = s->stats.sah_cost;
+    if (tris < 1.0 || tris > std::max(4096.0, 16.0 * sah)) return 0;
+    if (pixels * tris > std::max(20e6, 0.5e6 * sah)) return 0;
+    // (the test hooks reach the error paths of the traversal and its
+    // workspace, which this kernel does not have)
+    if (s->dev.step_budget < 5ull * s->dev.n_nodes + 16ull || alloc_hook_armed()) return 0;
+    if (tris <= 64.0) return pixels <= 4e5 ? 16 : 4;
+    return pixels <= 32768.0 ? 64 : (tris > 128.0 || pixels <= 4e5 ? 16 : 4);
+}
+
+rcp_status launch_direct(const rcp_scene* s, const Camera& cam, int W, int H, int K, const Disp& disp, float* out_images,
+                         int32_t* out_ids, int lanes, hipStream_t stream) {
+    const ViewDev v = view_of(s, cam, W, H, K, disp, out_images, out_ids, 3);
+    switch (disp.mode) {
+        case RCP_MODE_DEPTH: launch_direct_mode<RCP_MODE_DEPTH>(s, v, lanes, stream); break;
+        case RCP_MODE_NORMAL: launch_direct_mode<RCP_MODE_NORMAL>(s, v, lanes, stream); break;
+        default: launch_direct_mode<RCP_MODE_COLOR>(s, v, lanes, stream); break;
+    }
+    RCP_CHECK_LAUNCH();
+    return RCP_OK;
+}
+
 }  // namespace
 
 rcp_status render_chain(rcp_scene* s, Workspace& w, const Camera& cam, int W, int H, int K, const Disp& disp,
                         float* out_images, int32_t* out_ids, unsigned long long* host_counts, hipStream_t stream) {
     const bool stats = host_counts != nullptr;
+    const int lanes = stats ? 0 : direct_lanes(s, W, H);
+    if (lanes > 0) return launch_direct(s, cam, W, H, K, disp, out_images, out_ids, lanes, stream);
     const Launch lp = launch_params(s, chain_ordered(s));
     const uint64_t n_entries = view_entries(W, H, lp.tile_log2w);
     rcp_status st = ensure_tiles(w, order_entries(W, H, lp.tile_log2w), n_entries, stream);
@@ -1194,6 +1364,8 @@ rcp_status render_chain_fixed(rcp_scene* s, Workspace& w, const Camera& cam, int
                   per_block * sizeof(int32_t), w.spill_cap * sizeof(int32_t), cus);
         return RCP_ERR_INVALID_ARGUMENT;
     }
+    if (const int lanes = direct_lanes(s, W, H))
+        return launch_direct(s, cam, W, H, K, disp, out_images, out_ids, lanes, stream);
     if ((size_t)g.blocks > fit) g.blocks = (int)fit;
     return launch_one_view(s, w, lp, g, cam, W, H, K, disp, out_images, out_ids, false, stream);
 }
@@ -1306,6 +1478,13 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     hb[bofs++] = (uint32_t)items;
     groups.back().items = (uint32_t)items;
 
+    if (n_views == 1)
+        if (const int lanes = direct_lanes(s, views[0].W, views[0].H)) {
+            const Disp d{views[0].disp.lambda_eye, views[0].disp.lambda_dir, views[0].disp.z0, views[0].disp.mode};
+            return launch_direct(s, hv[0].cam, views[0].W, views[0].H, views[0].K, d, views[0].out_images,
+                                 views[0].out_ids, lanes, stream);
+        }
+
     // entry lists for all views, up to kMaxBatchEntries (a server slot: as many
     // as it was sized for); without room for them the rays start at the root
     if (!ws.staging && n_entries <= kMaxBatchEntries && ws.entry_cap < kEntryStride * n_entries) {
@@ -1395,6 +1574,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         a.n_items = groups[g].items;
         a.fetch = ws.fetch + kFetchWords * g;
         a.refill_min = lpr.refill_min;
+        set_take(a, grids[g]);
         a.exit_lanes = (uint32_t)lpr.exit_lanes;
         a.spill = ws.spill;
         a.spill_stride = grids[g].threads();

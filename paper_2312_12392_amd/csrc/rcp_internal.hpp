@@ -50,6 +50,8 @@ rcp_status hip_status(hipError_t e, const char* what, const char* file, int line
 rcp_status dev_alloc(void** p, size_t bytes);
 // True when the allocation hook says the next device allocation fails.
 bool alloc_hook_fails();
+// True while that hook is set.
+bool alloc_hook_armed();
 // Per-ray traversal step budget of scenes built from now on (0: the bound
 // that only a malformed tree can reach).
 uint32_t debug_step_budget();
