@@ -62,3 +62,18 @@ def test_gather_on_a_rendered_frame(edge):
     o = oracle.gather(base, 5, 6.0, edge=edge, centred=True)
     assert np.array_equal(g, o)
     s.close()
+
+
+# image sizes around the tile (64 x 4 pixels, 16 rows where a thread has four)
+# and the size above which a launch holds two passes instead of three;
+# displacements on both sides of the row windows at which the passes per launch
+# and the order of the workgroups change
+@pytest.mark.parametrize("W,H,smudge", [(63, 3, 2.0), (64, 4, 2.0), (65, 5, 2.0), (129, 17, 9.0), (700, 571, 6.0),
+                                        (700, 572, 6.0), (1601, 257, 6.0), (1601, 257, 60.0), (9001, 49, 80.0)])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5])
+def test_gather_launch_shapes(W, H, smudge, n):
+    say("gather launch shapes", W, H, smudge, n)
+    rng = np.random.default_rng(W + H + n)
+    img = rng.uniform(0.0, 1.0, size=(H, W, 3)).astype(np.float32)
+    for edge in (rcp.RCP_EDGE_CLAMP, rcp.RCP_EDGE_WRAP, rcp.RCP_EDGE_MIRROR):
+        assert np.array_equal(run_gather(img, n, smudge, edge, True), oracle.gather(img, n, smudge, edge=edge, centred=True))
