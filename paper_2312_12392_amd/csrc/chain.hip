@@ -75,6 +75,7 @@ struct ChainArgs {
     uint32_t* fetch;          // kFetchParts work counters kFetchStride words apart, zero at launch
     int refill_min;
     uint32_t take;               // most pixels a wave holds at once (64, or fewer so that a small launch fills the chip)
+    bool whole;                  // waves take whole tiles and keep what is left for their next idle lanes
     uint32_t exit_lanes;
     int32_t* spill;
     uint32_t spill_stride;
@@ -113,7 +114,7 @@ constexpr uint32_t kEntryLinks = 6 * kEntryItems / 4;  // first float4 of the li
 static_assert(kEntryF4 < kEntryStride && kEntryStride <= 64, "one load per lane copies a list");
 constexpr int kGroupLog2 = 2;             // groups of 4 x 4 tiles
 constexpr int kEntrySlots = 3;            // lists a wave holds in LDS
-constexpr int kEntryStack = 8;            // LDS stack entries next to them
+constexpr int kEntryStack = kQueueStack;  // LDS stack entries next to them
 
 // Lanes waiting for a setup round that start one once the bands are used up
 // (measured on the terrain frame: 1 -- a round for every waiting lane --
@@ -179,6 +180,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
     bool drained = false;      // wave-uniform
     uint32_t part = blockIdx.x % kFetchParts;   // wave-uniform: the band fetched from
     uint32_t parts_done = 0;                    // wave-uniform: bands found used up
+    uint32_t cur = 0, end = 0;                  // wave-uniform: items taken from a band and not handed out yet
     int k = 0, x = 0, y = 0;
     // ENTRY: slot i of the wave's LDS holds the list of group tag[i], with
     // quads[i] used quads (wave-uniform); `slot` is the lane's slot
@@ -209,7 +211,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
         const unsigned long long waiting = wave_ballot(ended || pending);
         const uint32_t n_need = popc_u32(need), n_wait = popc_u32(waiting);
         if (n_need >= (uint32_t)a.refill_min ||
-            (drained && n_wait != 0u && (n_wait >= kDrainedRound || n_need == 64u))) {
+            (drained && cur == end && n_wait != 0u && (n_wait >= kDrainedRound || n_need == 64u))) {
             // lanes whose pass is traced: shade, write, and keep the inputs
             // of the next pass or end the chain
             if (ended) {
@@ -317,14 +319,29 @@ __device__ inline void chain_body(const ChainArgs& a) {
             // (a wave that holds fewer pixels than lanes fills up to `take`)
             const uint32_t held = 64u - popc_u32(idle);
             const uint32_t n_idle = held < a.take ? a.take - held : 0u;
+            // items for the idle lanes: what is left of those taken last, then
+            // a whole tile or as many as there are idle lanes left
+            const uint32_t left = end - cur;
             uint32_t base = 0, lim = 0;
-            const bool fetch = !drained && n_idle > 0u;
-            if (fetch) wave_fetch(a.fetch, n_items, n_idle, part, parts_done, drained, base, lim);
+            if (left < n_idle && !drained) {
+                const uint32_t want = a.whole ? a.take : n_idle - left;
+                wave_fetch(a.fetch, n_items, want, part, parts_done, drained, base, lim);
+                lim = base + want < lim ? base + want : lim;
+            }
+            const uint32_t nth = lanes_below(idle);
+            const uint32_t item = nth < left ? cur + nth : base + (nth - left);
+            const bool get = !alive && !pending && nth < n_idle && (nth < left || item < lim);
+            if (n_idle <= left) {
+                cur += n_idle;
+            } else {
+                cur = base + (n_idle - left);
+                end = lim;
+                if (cur > end) cur = end;
+            }
             bool init = pending;
             uint32_t group = 0xFFFFFFFFu;   // ENTRY: tile group of a new pixel
-            if (fetch && !alive && !pending) {
-                const uint32_t nth = lanes_below(idle), item = base + nth;
-                if (nth < n_idle && item < lim) {
+            {
+                if (get) {
                     // the view holding this item: last begin <= item
                     if (!ONE) {
                         int lo = 0, hi = a.n_views;
@@ -431,7 +448,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
             }
         }
         if (wave_ballot(alive) == 0ull) {
-            if (drained && wave_ballot(pending || ended) == 0ull) break;
+            if (drained && cur == end && wave_ballot(pending || ended) == 0ull) break;
             continue;
         }
 
@@ -439,8 +456,8 @@ __device__ inline void chain_body(const ChainArgs& a) {
         if (ENTRY) {
             // until the next setup round can start
             const uint32_t dead = popc_u32(wave_ballot(!alive));
-            const uint32_t enough = drained ? (dead + kDrainedRound < 64u ? dead + kDrainedRound : 64u) : (uint32_t)a.refill_min;
-            trav_queue(tv, a.sc, st, wave_lds, a.exit_lanes, enough);
+            const uint32_t enough = drained && cur == end ? (dead + kDrainedRound < 64u ? dead + kDrainedRound : 64u) : (uint32_t)a.refill_min;
+            trav_queue<true>(tv, a.sc, st, wave_lds, a.exit_lanes, enough);
         } else if (alive && tv.node != -1) {
             trav_step<STATS, false>(tv, a.sc, st, a.exit_lanes, cnt);
         }
@@ -1036,15 +1053,17 @@ size_t chain_smem(const Launch& lp, const ChainKernel& k, bool stats, int n_view
     return b;
 }
 
+}  // namespace
+
 // Resident workgroups per CU and CU count of a kernel at an LDS size, on the
 // current device.  The runtime's answers are cached: they cannot change in a
 // process, and asking costs more than a launch.
-rcp_status occupancy(const ChainKernel& k, size_t smem, int& per_cu, int& cus) {
+rcp_status resident_blocks(const void* kernel, int block, size_t smem, int& per_cu, int& cus) {
     static std::mutex mu;
     static std::map<std::tuple<const void*, size_t, int>, std::pair<int, int>> cache;
     int dev = 0;
     RCP_HIP(hipGetDevice(&dev));
-    const auto key = std::make_tuple(k.fn, smem, dev);
+    const auto key = std::make_tuple(kernel, smem, dev);
     {
         std::lock_guard<std::mutex> lk(mu);
         const auto it = cache.find(key);
@@ -1054,12 +1073,14 @@ rcp_status occupancy(const ChainKernel& k, size_t smem, int& per_cu, int& cus) {
             return RCP_OK;
         }
     }
-    RCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k.fn, k.block, smem));
+    RCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, smem));
     RCP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = std::make_pair(per_cu, cus);
     return RCP_OK;
 }
+
+namespace {
 
 // Kernel, grid and LDS size of a launch over n_views views in `mode`.
 struct ChainGrid {
@@ -1073,7 +1094,7 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
     g.k = chain_kernel(stats, n_views, mode, lp, entry);
     g.smem = chain_smem(lp, g.k, stats, n_views);
     int per_cu = 0, cus = 0;
-    const rcp_status st = occupancy(g.k, g.smem, per_cu, cus);
+    const rcp_status st = resident_blocks(g.k.fn, g.k.block, g.smem, per_cu, cus);
     if (st != RCP_OK) return st;
     if (per_cu < 1) per_cu = 1;
     // blocks_per_cu counts workgroups of kBlock threads; a larger workgroup
@@ -1096,6 +1117,14 @@ void set_take(ChainArgs& a, const ChainGrid& g) {
     const uint64_t waves = (uint64_t)g.threads() / 64u;
     a.take = 1u;
     while (a.take < 64u && (uint64_t)a.n_items > 2u * waves * a.take) a.take *= 2u;
+    // Whole tiles keep a tile's pixels in one wave and make a third of the
+    // atomics, but a wave then keeps up to a tile that others could start when
+    // the work runs out: taken from seven pixels per lane on.  (Frame ms,
+    // exact / whole: 1920 x 1080, K = 6, 5 per lane 1.06 / 1.09; 2560 x 1440, 9
+    // per lane 1.69 / 1.53; 3840 x 2160, K = 8, 21 per lane 4.33 / 3.38; 4 mixed
+    // views, 6 per lane 1.39 / 1.35.  Pieces of 8, 16 or 32 pixels gain nothing:
+    // the tiles then lie across waves as much as with exact counts.)
+    a.whole = a.n_items >= 7u * (uint64_t)g.threads();
     // the refill threshold in idle lanes, in proportion
     a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
 }

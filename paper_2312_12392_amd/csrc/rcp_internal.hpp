@@ -337,6 +337,9 @@ Launch launch_params(const rcp_scene* s, bool ordered = false);
 // Whether single renders of the chain engine on this scene use the cost order.
 inline bool chain_ordered(const rcp_scene* s) { return s->tuning.tile_order != 0 && s->occ.bits != nullptr; }
 
+// Resident workgroups of `block` threads per CU, and the CU count (chain.hip).
+rcp_status resident_blocks(const void* kernel, int block, size_t smem, int& per_cu, int& cus);
+
 // Make sure a render workspace fits a K-pass W x H render in `mode` (no
 // allocation happens in render afterwards for that size).
 rcp_status prepare_render(rcp_scene* s, Workspace& ws, int W, int H, int K, int mode, hipStream_t stream);

@@ -23,6 +23,9 @@
 // shade table) is FP32 evaluated left to right without contraction, with
 // correctly rounded division and square root.  The box tests only prune and
 // are widened so that they never reject a box the exact test would accept.
+#include <algorithm>
+#include <type_traits>
+
 #include "traverse.hpp"
 
 namespace rcp {
@@ -35,6 +38,7 @@ struct PassArgs {
     float le, ld, z0;
     uint32_t n_items0;              // pass-0 items (whole super-tiles of 64-pixel tiles)
     int refill_min;                 // idle lanes that trigger a refill (1..64)
+    uint32_t take;                  // most work items a wave holds at once (64, fewer in a small pass 0)
     uint32_t exit_lanes;            // searching lanes that end a traversal step early
     int tiles_x;
     int tile_log2w;                 // pass-0 tiles of 64 pixels, 2^tile_log2w wide
@@ -63,18 +67,47 @@ constexpr size_t kCounterWords = kPassFetch + (size_t)kMaxPasses * kFetchWords;
 constexpr int kWaves = kBlock / 64;
 constexpr int kStage = 128;     // per-wave staging of appended entries (flushed 64 at a time)
 
+// The traversal reads staged node i at LDS byte address 128 i: the dynamic LDS
+// must begin at address 0, as it does while a kernel declares no LDS of its
+// own (otherwise the launch does nothing and raises the scene's error flag).
+__device__ inline bool lds_at_zero(const float4* smem, const DevScene& sc) {
+    if ((uint32_t)(size_t)(const LdsV4*)smem == 0u) return true;
+    if (threadIdx.x == 0) __hip_atomic_store(sc.err_flag, kErrLdsLayout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return false;
+}
+
+// Copy the top levels (the workgroup; a barrier is due before they are read).
+__device__ inline void stage_top(float4* top, const DevScene& sc) {
+    for (uint32_t i = threadIdx.x; i < 8u * sc.top_count; i += kBlock)
+        if ((i & 7u) != 7u) top[i] = sc.nodes[i];   // the zero padding is never read
+}
+
+// LDS address of the wave's records and queue, the waves' parts from `at` on.
+__device__ inline uint32_t wave_address(char* at) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(const LdsI32*)(int32_t*)at + (threadIdx.x >> 6) * kQueueBytes);
+}
+
 template <bool STATS, int MODE>
 __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
     constexpr bool AUX = MODE != RCP_MODE_COLOR;
+    // LDS: the staged top levels, the stack area, the waves' ray records and
+    // leaf queues (not in the instrumented kernel), the stage
     extern __shared__ float4 smem[];
-    float4* stage_all = smem;                                           // kWaves * kStage (x2 with aux)
-    int32_t* stack_area = (int32_t*)(stage_all + (AUX ? 2 : 1) * kWaves * kStage);   // kStack * kBlock
+    using St = typename std::conditional<STATS, Stack, QStack>::type;
+    constexpr int kDepth = STATS ? kStack : kQueueStack;
+    if (!lds_at_zero(smem, a.sc)) return;
+    stage_top(smem, a.sc);
+    int32_t* stack_area = (int32_t*)(smem + 8 * (size_t)a.sc.top_count);           // kDepth * kBlock
+    char* queues = (char*)(stack_area + kDepth * kBlock);
+    const uint32_t wave_lds = wave_address(queues);
+    float4* stage_all = (float4*)(queues + (STATS ? 0 : kWaves * kQueueBytes));    // kWaves * kStage (x2 with aux)
+    __syncthreads();
 
     const int lane = threadIdx.x & 63;
     float4* stage = stage_all + (threadIdx.x >> 6) * kStage;
     float4* stage_aux = stage_all + kWaves * kStage + (threadIdx.x >> 6) * kStage;
     const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
-    Stack st;
+    St st;
     st.lds = stack_area + threadIdx.x;
     st.spill = a.spill + gtid;
     st.stride = a.spill_stride;
@@ -100,13 +133,14 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
     for (;;) {
         // ---- refill idle lanes with new work items ----------------------
         const unsigned long long idle = __ballot(!alive);
-        const uint32_t n_idle = (uint32_t)__popcll(idle);
-        if (!drained && n_idle >= (uint32_t)a.refill_min) {
+        const uint32_t n_free = (uint32_t)__popcll(idle);
+        if (!drained && n_free >= (uint32_t)a.refill_min) {
+            const uint32_t held = 64u - n_free, n_idle = held < a.take ? a.take - held : 0u;
             uint32_t base = 0, lim = 0;
             wave_fetch(fetch, n_items, n_idle, part, parts_done, drained, base, lim);
             if (!alive) {
-                const uint32_t item = base + lanes_below(idle);
-                bool valid = item < lim;
+                const uint32_t nth = lanes_below(idle), item = base + nth;
+                bool valid = nth < n_idle && item < lim;
                 int x = 0, y = 0;
                 if (a.k == 0) {
                     tile_pixel(item, (uint32_t)a.tiles_x, (uint32_t)a.tile_log2w, (uint32_t)a.super_log2, x, y);
@@ -140,6 +174,7 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
                     float ro[3], rd[3];
                     make_ray<MODE>(a.cam, half_width(a.cam.th, a.W, a.H), a.W, a.H, x, y, pr, pg, pb, pa, a.z0, a.le, a.ld, ro, rd);
                     trav_init(tv, a.sc, ro, rd, st);
+                    if (!STATS) record_ray(tv.rw, wave_lds);
                     alive = true;
                     if (STATS) ++s_rays;
                 }
@@ -150,8 +185,13 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
             continue;
         }
 
-        // ---- one traversal step -------------------------------------------
-        if (alive && tv.node != -1) trav_step<STATS, false>(tv, a.sc, st, a.exit_lanes, cnt);
+        // ---- traversal: one step, or until a refill (once the list is used up:
+        // until the wave's last ray has ended) --------------------------------
+        if (STATS) {
+            if (alive && tv.node != -1) trav_step<true, false>(tv, a.sc, st, a.exit_lanes, cnt);
+        } else {
+            trav_queue<false>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : (uint32_t)a.refill_min);
+        }
 
         // ---- finished rays: shade, write, compact ----------------------------
         const bool done = alive && tv.node == -1;
@@ -159,6 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
         float na[4] = {INFINITY, 0.0f, 0.0f, 0.0f};   // this pass's hit data
         int32_t hid = -1;
         if (done) {
+            if (!STATS) recorded_hit(tv.h, wave_lds);
             if (tv.h.id != INT_MAX) {
                 const float4 c = a.sc.shade[2 * (size_t)tv.h.slot + (tv.h.front ? 0 : 1)];
                 rgb[0] = c.x; rgb[1] = c.y; rgb[2] = c.z;
@@ -283,27 +324,86 @@ __global__ __launch_bounds__(kBlock) void k_gen_rays(Camera cam, int W, int H, f
     for (int c = 0; c < 3; ++c) { org[3 * (size_t)p + c] = o[c]; dir[3 * (size_t)p + c] = d[c]; }
 }
 
-__global__ __launch_bounds__(kBlock) void k_trace_rays(DevScene sc, const float* __restrict__ org,
-                                                        const float* __restrict__ dir, int n, float* __restrict__ out_t,
-                                                        int32_t* __restrict__ out_id, int32_t* __restrict__ out_front,
-                                                        int32_t* __restrict__ spill, uint32_t stride) {
-    extern __shared__ int32_t stack_area[];                             // kStack * kBlock
+// Closest hits of given rays.  A wave takes chunks of `chunk` consecutive rays,
+// wave w the chunks w, w + waves, ..., and refills its idle lanes from the
+// current one: no counters, and the waves advance through the rays together, so
+// that neighbouring rays are traced at the same time.  (1M scattered rays, 1M
+// triangles: 190 us; from atomic band counters 294; without refills 284.  1M
+// rays of an image: 160, 261, 174.)
+struct RayArgs {
+    DevScene sc;
+    const float* org;
+    const float* dir;
+    uint32_t n;
+    float* out_t;
+    int32_t* out_id;
+    int32_t* out_front;
+    int32_t* spill;
+    uint32_t spill_stride;
+    uint32_t chunk;                    // <= 64
+    uint32_t refill_min, exit_lanes;   // refill_min: idle lanes, more than 64 - chunk
+};
+
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_trace_rays(RayArgs a) {
+    // LDS: the staged top levels, the stack area, the waves' ray records and
+    // leaf queues
+    extern __shared__ float4 smem[];
+    if (!lds_at_zero(smem, a.sc)) return;
+    stage_top(smem, a.sc);
+    int32_t* stack_area = (int32_t*)(smem + 8 * (size_t)a.sc.top_count);
+    const uint32_t wave_lds = wave_address((char*)(stack_area + kQueueStack * kBlock));
+    __syncthreads();
     const uint32_t gtid = blockIdx.x * kBlock + threadIdx.x;
-    Stack st;
+    QStack st;
     st.lds = stack_area + threadIdx.x;
-    st.spill = spill + gtid;
-    st.stride = stride;
-    for (uint32_t r = gtid; r < (uint32_t)n; r += gridDim.x * kBlock) {
-        float o[3], d[3];
-        for (int c = 0; c < 3; ++c) { o[c] = org[3 * (size_t)r + c]; d[c] = dir[3 * (size_t)r + c]; }
-        Trav tv;
-        trav_init(tv, sc, o, d, st);
-        TravCount cnt;
-        while (tv.node != -1) trav_step<false, false>(tv, sc, st, 0u, cnt);
-        const bool hit = tv.h.id != INT_MAX;
-        out_t[r] = hit ? tv.h.t : INFINITY;
-        out_id[r] = hit ? tv.h.id : -1;
-        if (out_front) out_front[r] = hit && tv.h.front ? 1 : 0;
+    st.spill = a.spill + gtid;
+    st.stride = a.spill_stride;
+    bool alive = false, ended = false;
+    // wave-uniform: the rays left in the chunk, and the first one of the next
+    const uint32_t stride = gridDim.x * kWaves * a.chunk;
+    uint32_t cur = __builtin_amdgcn_readfirstlane(gtid >> 6) * a.chunk, next = cur + stride;
+    uint32_t end = cur + a.chunk < a.n ? cur + a.chunk : a.n;
+    bool drained = cur >= a.n;
+    uint32_t r = 0;
+    Trav tv;
+    tv.node = -1;
+    for (;;) {
+        if (ended) {
+            recorded_hit(tv.h, wave_lds);
+            const bool hit = tv.h.id != INT_MAX;
+            a.out_t[r] = hit ? tv.h.t : INFINITY;
+            a.out_id[r] = hit ? tv.h.id : -1;
+            if (a.out_front) a.out_front[r] = hit && tv.h.front ? 1 : 0;
+            ended = false;
+        }
+        if (!drained) {
+            const unsigned long long idle = wave_ballot(!alive);
+            const uint32_t nth = lanes_below(idle);
+            if (!alive && cur + nth < end) {
+                r = cur + nth;
+                float o[3], d[3];
+                for (int c = 0; c < 3; ++c) { o[c] = a.org[3 * (size_t)r + c]; d[c] = a.dir[3 * (size_t)r + c]; }
+                trav_init(tv, a.sc, o, d, st);
+                record_ray(tv.rw, wave_lds);
+                alive = true;
+            }
+            cur += popc_u32(idle);
+            if (cur >= end) {
+                drained = next >= a.n;
+                cur = next;
+                end = a.n - cur > a.chunk ? cur + a.chunk : a.n;
+                next += stride;
+            }
+        }
+        if (wave_ballot(alive) == 0ull) {
+            if (drained) break;
+            continue;
+        }
+        trav_queue<false>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : a.refill_min);
+        if (alive && tv.node == -1) {
+            alive = false;
+            ended = true;
+        }
     }
 }
 
@@ -413,18 +513,22 @@ struct GridInfo {
     size_t smem = 0;
 };
 
-template <typename KernelT>
-rcp_status persistent_grid(KernelT kernel, const DevScene& sc, GridInfo& g, bool aux, int blocks_per_cu) {
-    g.smem = sizeof(float4) * (aux ? 2 : 1) * kWaves * kStage + sizeof(int32_t) * kStack * kBlock;
-    int per_cu = 0;
-    RCP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, g.smem));
-    int dev = 0, cus = 0;
-    RCP_HIP(hipGetDevice(&dev));
-    RCP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+// Resident grid of a kernel at an LDS size.  The occupancy is asked for once
+// per kernel, LDS size and device: asking costs more than a launch.
+rcp_status persistent_grid(const void* kernel, size_t smem, int blocks_per_cu, GridInfo& g) {
+    g.smem = smem;
+    int per_cu = 0, cus = 0;
+    RCP_TRY_STATUS(resident_blocks(kernel, kBlock, smem, per_cu, cus));
     if (per_cu < 1) per_cu = 1;
     if (blocks_per_cu > 0 && blocks_per_cu < per_cu) per_cu = blocks_per_cu;
     g.blocks = per_cu * cus;
     return RCP_OK;
+}
+
+// LDS of the pass kernel: the stage only where a pass follows.
+size_t pass_smem(uint32_t top_count, bool stats, bool aux, bool stage) {
+    return kNodeBytes * (size_t)top_count + sizeof(int32_t) * (stats ? kStack : kQueueStack) * kBlock +
+           (stats ? 0 : kWaves * (size_t)kQueueBytes) + (stage ? sizeof(float4) * (aux ? 2 : 1) * kWaves * kStage : 0);
 }
 
 }  // namespace
@@ -483,9 +587,23 @@ __global__ void k_canary_check(const float4* __restrict__ st, const float4* __re
     if (bad) __hip_atomic_store(err_flag, kErrListCanary, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Top nodes the kernels of this file stage in LDS; the instrumented kernel
+// none.
+template <bool STATS>
+uint32_t staged_nodes(const Launch& lp) {
+    return STATS ? 0u : lp.top_count;
+}
+
 template <bool STATS, int MODE>
-rcp_status pass_grid(rcp_scene* s, const Launch& lp, GridInfo& g) {
-    return persistent_grid(k_pass<STATS, MODE>, s->dev, g, MODE != RCP_MODE_COLOR, lp.blocks_per_cu);
+rcp_status pass_grid(uint32_t top_count, int K, const Launch& lp, GridInfo& g) {
+    return persistent_grid((const void*)k_pass<STATS, MODE>, pass_smem(top_count, STATS, MODE != RCP_MODE_COLOR, K > 1),
+                           lp.blocks_per_cu, g);
+}
+
+// Stack overflow entries per thread of the pass kernel.
+template <bool STATS>
+size_t pass_spill(const rcp_scene* s) {
+    return spill_per_thread(s->dev, STATS ? kStack : kQueueStack);
 }
 
 template <bool STATS, int MODE>
@@ -493,11 +611,12 @@ rcp_status launch_passes(rcp_scene* s, Workspace& w, PassArgs& a, int K, hipStre
     constexpr bool AUX = MODE != RCP_MODE_COLOR;
     const Launch lp = launch_params(s);
     GridInfo g;
-    rcp_status st = pass_grid<STATS, MODE>(s, lp, g);
+    a.sc.top_count = staged_nodes<STATS>(lp);
+    rcp_status st = pass_grid<STATS, MODE>(a.sc.top_count, K, lp, g);
     if (st != RCP_OK) return st;
     const uint32_t threads = (uint32_t)g.blocks * kBlock;
     const size_t P = (size_t)a.W * (size_t)a.H;
-    const size_t spill_depth = spill_per_thread(s->dev);
+    const size_t spill_depth = pass_spill<STATS>(s);
     st = ensure_workspace(s, w, K > 1 ? P : 1, (K > 1 && AUX) ? P : 0, spill_depth * threads, stream);
     if (st != RCP_OK) return st;
     a.spill = w.spill;
@@ -510,8 +629,15 @@ rcp_status launch_passes(rcp_scene* s, Workspace& w, PassArgs& a, int K, hipStre
     const int canary = debug_list_canary();
     // the lists hold P entries (the workspace may hold more)
     const size_t cap = P;
+    // a small pass 0 is spread over the chip's waves, as in the chain engine (the
+    // later passes' lists are of unknown length)
+    const int refill = a.refill_min;
+    uint32_t take0 = 1u;
+    while (take0 < 64u && (uint64_t)a.n_items0 > 2u * (threads / 64u) * (uint64_t)take0) take0 *= 2u;
     for (int k = 0; k < K; ++k) {
         a.k = k;
+        a.take = k == 0 && !STATS ? take0 : 64u;
+        a.refill_min = 64 - (int)a.take + (refill * (int)a.take + 63) / 64;
         a.state_in = k == 0 ? nullptr : w.state[(k - 1) & 1];
         a.aux_in = (k == 0 || !AUX) ? nullptr : w.aux[(k - 1) & 1];
         a.state_out = k + 1 < K ? w.state[k & 1] : nullptr;
@@ -547,14 +673,12 @@ template <int MODE>
 rcp_status prepare_mode(rcp_scene* s, Workspace& w, int W, int H, int K, hipStream_t stream) {
     const Launch lp = launch_params(s);
     GridInfo g1, g2;
-    rcp_status st = pass_grid<false, MODE>(s, lp, g1);
-    if (st == RCP_OK) st = pass_grid<true, MODE>(s, lp, g2);
+    rcp_status st = pass_grid<false, MODE>(staged_nodes<false>(lp), K, lp, g1);
+    if (st == RCP_OK) st = pass_grid<true, MODE>(staged_nodes<true>(lp), K, lp, g2);
     if (st != RCP_OK) return st;
-    const uint32_t threads = (uint32_t)(g1.blocks > g2.blocks ? g1.blocks : g2.blocks) * kBlock;
+    const size_t spill = std::max(pass_spill<false>(s) * (size_t)g1.blocks, pass_spill<true>(s) * (size_t)g2.blocks) * kBlock;
     const size_t P = (size_t)W * (size_t)H;
-    const size_t spill_depth = spill_per_thread(s->dev);
-    return ensure_workspace(s, w, K > 1 ? P : 1, (K > 1 && MODE != RCP_MODE_COLOR) ? P : 0, spill_depth * threads,
-                            stream);
+    return ensure_workspace(s, w, K > 1 ? P : 1, (K > 1 && MODE != RCP_MODE_COLOR) ? P : 0, spill, stream);
 }
 }  // namespace
 
@@ -581,12 +705,12 @@ rcp_status render(rcp_scene* s, Workspace& w, const Camera& cam, int W, int H, i
     const int super_log2 = super_log2_for(W, H, lp.tile_log2w);
     PassArgs a{};
     a.sc = s->dev;
-    a.sc.top_count = 0;          // this kernel stages nothing in LDS
     a.cam = cam;
     a.W = W; a.H = H; a.K = K;
     a.le = disp.le; a.ld = disp.ld; a.z0 = disp.z0;
     a.n_items0 = (uint32_t)view_tile_items(W, H, lp.tile_log2w, super_log2);
-    a.refill_min = lp.refill_min;
+    // a single pass refills whole waves (1920 x 1080: 343 against 355 us at 56)
+    a.refill_min = K == 1 && s->tuning.refill_min <= 0 ? kDefaultRefillOrdered : lp.refill_min;
     a.exit_lanes = (uint32_t)lp.exit_lanes;
     a.tiles_x = tiles_x;
     a.tile_log2w = lp.tile_log2w;
@@ -632,17 +756,33 @@ rcp_status generate_rays(const Camera& cam, int W, int H, const Disp& disp, cons
 rcp_status trace_rays(rcp_scene* s, const float* org, const float* dir, int n, float* out_t, int32_t* out_id,
                       int32_t* out_front, hipStream_t stream) {
     if (n == 0) return RCP_OK;
+    const Launch lp = launch_params(s);
+    RayArgs a{};
+    a.sc = s->dev;
+    a.sc.top_count = staged_nodes<false>(lp);
     GridInfo g;
-    rcp_status st = persistent_grid(k_trace_rays, s->dev, g, false, 0);
+    rcp_status st = persistent_grid((const void*)k_trace_rays, pass_smem(a.sc.top_count, false, false, false), 0, g);
     if (st != RCP_OK) return st;
-    const uint32_t threads = (uint32_t)g.blocks * kBlock;
-    const size_t spill_depth = spill_per_thread(s->dev);
-    st = ensure_workspace(s, s->ws, 1, 0, spill_depth * threads, stream);
+    const uint32_t threads = (uint32_t)g.blocks * kBlock, waves = threads / 64u;
+    st = ensure_workspace(s, s->ws, 1, 0, pass_spill<false>(s) * threads, stream);
     if (st != RCP_OK) return st;
-    DevScene sc = s->dev;
-    sc.top_count = 0;            // this kernel stages nothing in LDS
-    hipLaunchKernelGGL(k_trace_rays, dim3(g.blocks), dim3(kBlock), g.smem, stream, sc, org, dir, n, out_t,
-                       out_id, out_front, s->ws.spill, threads);
+    a.org = org;
+    a.dir = dir;
+    a.n = (uint32_t)n;
+    a.out_t = out_t;
+    a.out_id = out_id;
+    a.out_front = out_front;
+    a.spill = s->ws.spill;
+    a.spill_stride = threads;
+    // chunks of 32 rays, refilled at 32 idle lanes (64 and 16 rays at their best
+    // thresholds: 204 and 201 us, 174 and 181 for the image); a launch of no
+    // more rays than lanes spreads them over all waves, in one chunk each
+    a.chunk = 1u;
+    while (a.chunk < 32u && (uint64_t)n > (uint64_t)waves * a.chunk) a.chunk *= 2u;
+    a.refill_min = 32u;
+    a.exit_lanes = 16u;
+    if ((uint64_t)n <= (uint64_t)waves * a.chunk) g.blocks = (int)(((uint32_t)n + a.chunk * kWaves - 1u) / (a.chunk * kWaves));
+    hipLaunchKernelGGL(k_trace_rays, dim3(g.blocks), dim3(kBlock), g.smem, stream, a);
     RCP_CHECK_LAUNCH();
     return RCP_OK;
 }

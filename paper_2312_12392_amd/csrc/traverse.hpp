@@ -356,7 +356,9 @@ struct StackT {
 // The traversal state of one ray lives in registers (plus its stack), so a
 // lane can advance its ray one step at a time and take a new ray as soon as
 // the current one is finished.
-using Stack = StackT<kStack, kBlock>;   // the stack of the per-pass and single-step kernels
+using Stack = StackT<kStack, kBlock>;   // the stack of the instrumented per-pass kernel
+constexpr int kQueueStack = 8;           // LDS stack entries of kernels with a leaf queue
+using QStack = StackT<kQueueStack, kBlock>;
 
 struct Trav {
     RayW rw;
@@ -743,7 +745,9 @@ __device__ inline void test_leaves(const DevScene& sc, uint32_t wave, uint32_t f
 // rays are left and at least as many leaves wait (tests that wait for more
 // leaves would let the rays go on past hits that end them).
 // The whole wave calls this; lanes without a ray have tv.node == -1.
-template <class Stack>
+// ENTRY: rays may have entry lists; otherwise the tree's first sc.top_count
+// nodes are read from LDS.
+template <bool ENTRY, class Stack>
 __device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint32_t wave, uint32_t exit_lanes,
                                   uint32_t enough) {
     TravCount cnt;
@@ -759,7 +763,7 @@ __device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint3
                 const uint32_t at = waiting + lanes_below(leaves);
                 lds_put_u(wave + kQueueLink + 4u * at, (uint32_t)node);
                 *(LdsU8*)(size_t)(wave + kQueueOwner + at) = (uint8_t)l;
-                node = next_node<true>(tv, st);
+                node = next_node<ENTRY>(tv, st);
             }
             waiting += popc_u32(leaves);
         }
@@ -776,7 +780,7 @@ __device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint3
         }
         if (stop) break;
         ++it;
-        if (node >= 0) node = visit_inner4<false, true>(tv, node, sc, st, cnt);
+        if (node >= 0) node = visit_inner4<false, ENTRY>(tv, node, sc, st, cnt);
     }
     // the bound that only a malformed tree reaches (every round enters a node
     // or a leaf): end the ray and raise the scene's error flag
