@@ -11,8 +11,8 @@
 //      (or, by default, PLOC: agglomerative clustering of Morton neighbours)
 //   5. the 4-wide tree the traversal uses, 128-byte nodes, by default from
 //      an SAH-optimal collapse of the binary tree: a bottom-up dynamic
-//      programme over the subtrees (one launch per tree level), then
-//      emission level by level.  The greedy alternative: a bottom-up refit that collapses
+//      programme over the subtrees (within PLOC's merges; for the radix
+//      tree one launch per tree level), then emission level by level.  The greedy alternative: a bottom-up refit that collapses
 //      subtrees into leaves (<= max_leaf triangles) where the binary SAH says
 //      so, packing of the binary tree in depth-first order, and wide nodes
 //      that open their children of largest area
@@ -69,23 +69,76 @@ __device__ inline float wave_max(float v) {
     return v;
 }
 
-// bounds[0..2] = ordered min of centres, bounds[3..5] = ordered max.
-__global__ void k_init_bounds(uint32_t* bounds) {
-    if (threadIdx.x < 3) bounds[threadIdx.x] = 0xFFFFFFFFu;
-    else if (threadIdx.x < 6) bounds[threadIdx.x] = 0u;
+// What the host needs to know of the input arrays: whether any index is out of
+// range or any float not finite, and the box of the vertices.  (One host thread
+// took 7 ms for it at 1M triangles.)
+struct InputCheck {
+    uint32_t bad;
+    uint32_t lo[3], hi[3];   // ordered (f2o)
+};
+
+__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u; }
+
+__global__ __launch_bounds__(kB) void k_check_inputs(const float* __restrict__ verts, uint32_t n_verts,
+                                                      const uint32_t* __restrict__ idx, const float* __restrict__ rgb,
+                                                      uint32_t n, InputCheck* out) {
+    const size_t t0 = (size_t)blockIdx.x * kB + threadIdx.x, step = (size_t)gridDim.x * kB;
+    bool bad = false;
+    for (size_t i = t0; i < 3 * (size_t)n; i += step) bad = bad || idx[i] >= n_verts || not_finite(rgb[i]);
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (size_t i = t0; i < n_verts; i += step)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float v = verts[3 * i + a];
+            bad = bad || not_finite(v);
+            lo[a] = fminf(lo[a], v);
+            hi[a] = fmaxf(hi[a], v);
+        }
+    __shared__ float red[kB / 64][6];
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float l = wave_min(lo[a]), h = wave_max(hi[a]);
+        if ((threadIdx.x & 63) == 0) {
+            red[wave][a] = l;
+            red[wave][3 + a] = h;
+        }
+    }
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x < 3) {
+        float l = red[0][threadIdx.x], h = red[0][3 + threadIdx.x];
+        for (int w = 1; w < kB / 64; ++w) {
+            l = fminf(l, red[w][threadIdx.x]);
+            h = fmaxf(h, red[w][3 + threadIdx.x]);
+        }
+        if (l <= h) {
+            atomicMin(&out->lo[threadIdx.x], f2o(l));
+            atomicMax(&out->hi[threadIdx.x], f2o(h));
+        }
+        if (threadIdx.x == 0 && any) atomicOr(&out->bad, 1u);
+    }
 }
 
-__global__ __launch_bounds__(kB) void k_tri_prep(const float* __restrict__ verts, const uint32_t* __restrict__ idx,
-                                                  uint32_t n, float4* __restrict__ tlo, float4* __restrict__ thi,
+// bounds[0..2] = ordered min of centres, bounds[3..5] = ordered max.
+__global__ void k_init_bounds(uint32_t* bounds, InputCheck* c) {
+    if (threadIdx.x < 3) bounds[threadIdx.x] = c->lo[threadIdx.x] = 0xFFFFFFFFu;
+    else if (threadIdx.x < 6) bounds[threadIdx.x] = c->hi[threadIdx.x - 3] = 0u;
+    else if (threadIdx.x == 6) c->bad = 0u;
+}
+
+// (An index out of range, which the check above reports while this runs, reads
+// the last vertex.)
+__global__ __launch_bounds__(kB) void k_tri_prep(const float* __restrict__ verts, uint32_t n_verts,
+                                                  const uint32_t* __restrict__ idx, uint32_t n, float4* __restrict__ tlo, float4* __restrict__ thi,
                                                   uint32_t* __restrict__ bounds) {
     // grid-stride over the triangles; the centroid bounds are reduced per
     // thread, per wave and per workgroup before six atomics per workgroup
     float3 cmin = make_float3(INFINITY, INFINITY, INFINITY);
     float3 cmax = make_float3(-INFINITY, -INFINITY, -INFINITY);
     for (uint32_t i = blockIdx.x * kB + threadIdx.x; i < n; i += gridDim.x * kB) {
-        float3 a = ld3(verts, idx[3 * (size_t)i]);
-        float3 b = ld3(verts, idx[3 * (size_t)i + 1]);
-        float3 d = ld3(verts, idx[3 * (size_t)i + 2]);
+        float3 a = ld3(verts, min(idx[3 * (size_t)i], n_verts - 1u));
+        float3 b = ld3(verts, min(idx[3 * (size_t)i + 1], n_verts - 1u));
+        float3 d = ld3(verts, min(idx[3 * (size_t)i + 2], n_verts - 1u));
         float3 lo = make_float3(fminf(fminf(a.x, b.x), d.x), fminf(fminf(a.y, b.y), d.y), fminf(fminf(a.z, b.z), d.z));
         float3 hi = make_float3(fmaxf(fmaxf(a.x, b.x), d.x), fmaxf(fmaxf(a.y, b.y), d.y), fmaxf(fmaxf(a.z, b.z), d.z));
         tlo[i] = make_float4(lo.x, lo.y, lo.z, 0.0f);
@@ -216,18 +269,35 @@ __global__ __launch_bounds__(kB) void k_radix_tree(const uint64_t* __restrict__ 
 // ---------------------------------------------------------------------------
 constexpr int kPlocRadius = 16;
 
+// At 1M triangles (32 rounds above kPlocSmall) a round was six launches, an
+// atomic per merge for the node numbers and a host read: 130 us, and a further
+// 100 launches took counts and collapse costs up the tree.  Now 29 us of
+// kernels and a read every fourth round, and the whole build went from 22.7 to
+// 5.8 ms with its host checks, allocations and level reads gone too.
+// One round is three launches, with the cluster count and the next node
+// number in device memory (RoundState r to r + 1), so that several rounds can
+// be enqueued before the host reads the count again; their grids are sized for
+// the last count it read, which only falls.
+struct RoundState {
+    int32_t m;          // clusters
+    int32_t next_id;    // the highest free node number
+};
+
 __global__ __launch_bounds__(kB) void k_ploc_init(int n, const float4* __restrict__ tlo, const float4* __restrict__ thi,
                                                    const uint32_t* __restrict__ sorted, int32_t* __restrict__ id,
-                                                   float4* __restrict__ lo, float4* __restrict__ hi) {
+                                                   float4* __restrict__ lo, float4* __restrict__ hi, RoundState* rs) {
     const int i = blockIdx.x * kB + threadIdx.x;
     if (i >= n) return;
+    if (i == 0) *rs = RoundState{n, n - 2};
     id[i] = (int32_t)(kLeafBit | (uint32_t)i);
     lo[i] = tlo[sorted[i]];
     hi[i] = thi[sorted[i]];
 }
 
-__global__ __launch_bounds__(kB) void k_ploc_nn(int m, const float4* __restrict__ lo, const float4* __restrict__ hi,
-                                                 int32_t* __restrict__ nn) {
+__global__ __launch_bounds__(kB) void k_ploc_nn(const RoundState* __restrict__ rs, const float4* __restrict__ lo,
+                                                 const float4* __restrict__ hi, int32_t* __restrict__ nn) {
+    const int m = rs->m;
+    if ((int)(blockIdx.x * kB) >= m) return;
     constexpr int kW = kB + 2 * kPlocRadius;
     __shared__ float s[6][kW];
     const int base = (int)(blockIdx.x * kB) - kPlocRadius;
@@ -269,56 +339,212 @@ __device__ inline int node_slot(int32_t c, int n) {
     return c < 0 ? n - 1 + (int)((uint32_t)c & ~kLeafBit) : c;
 }
 
-__global__ __launch_bounds__(kB) void k_ploc_merge(int m, int n, const int32_t* __restrict__ nn,
-                                                    const int32_t* __restrict__ id, const float4* __restrict__ lo,
-                                                    const float4* __restrict__ hi, int32_t* __restrict__ id2,
-                                                    float4* __restrict__ lo2, float4* __restrict__ hi2,
-                                                    uint32_t* __restrict__ pos, uint32_t* __restrict__ keep,
-                                                    int32_t* __restrict__ next_id, int32_t* __restrict__ left,
-                                                    int32_t* __restrict__ right, int32_t* __restrict__ parent) {
-    const int i = blockIdx.x * kB + threadIdx.x;
-    if (i >= m) return;
-    const int j = nn[i];
-    uint32_t k = 1u;
-    if (j >= 0 && nn[j] == i) {
-        if (i < j) {
-            const int32_t node = atomicSub(next_id, 1);
-            const int32_t a = id[i], b = id[j];
-            left[node] = a;
-            right[node] = b;
-            parent[node_slot(a, n)] = node;
-            parent[node_slot(b, n)] = node;
-            const float4 la = lo[i], lb = lo[j], ha = hi[i], hb = hi[j];
-            id2[i] = node;
-            lo2[i] = make_float4(fminf(la.x, lb.x), fminf(la.y, lb.y), fminf(la.z, lb.z), 0.0f);
-            hi2[i] = make_float4(fmaxf(ha.x, hb.x), fmaxf(ha.y, hb.y), fmaxf(ha.z, hb.z), 0.0f);
-        } else {
-            k = 0u;   // merged into cluster j
-        }
+struct NodeData {
+    float4* lo;        // box lo, w unused
+    float4* hi;
+    float* cost;
+    int32_t* n_inner;  // emitted inner nodes in the subtree (0 when collapsed)
+    int32_t* collapse;
+};
+
+// The optimal collapse's programme, per binary node.
+struct WideDP {
+    float4* cost;      // C(i, 1..4)
+    int4* count;       // wide nodes of each choice
+    uint32_t* dec;
+};
+
+__device__ inline void dp_child(int32_t c, const float3& lo, const float3& hi, const WideDP& wd, float c_isect,
+                                float c_entry, float C[5], int W[5]) {
+    if (c < 0) {
+        const float ct = (c_isect + c_entry) * half_area(lo, hi);
+        for (int j = 1; j <= 4; ++j) { C[j] = ct; W[j] = 0; }
     } else {
-        id2[i] = id[i];
-        lo2[i] = lo[i];
-        hi2[i] = hi[i];
+        // computed earlier (a deeper level, or an earlier round)
+        const float4 cc = wd.cost[c];
+        const int4 ww = wd.count[c];
+        C[1] = cc.x; C[2] = cc.y; C[3] = cc.z; C[4] = cc.w;
+        W[1] = ww.x; W[2] = ww.y; W[3] = ww.z; W[4] = ww.w;
     }
-    pos[i] = k;
-    keep[i] = k;
 }
 
-__global__ __launch_bounds__(kB) void k_ploc_compact(int m, const uint32_t* __restrict__ pos,
-                                                      const uint32_t* __restrict__ keep,
-                                                      const int32_t* __restrict__ id2, const float4* __restrict__ lo2,
-                                                      const float4* __restrict__ hi2, int32_t* __restrict__ id,
-                                                      float4* __restrict__ lo, float4* __restrict__ hi,
-                                                      uint32_t* __restrict__ m_out) {
-    const int i = blockIdx.x * kB + threadIdx.x;
-    if (i >= m) return;
-    if (keep[i]) {
-        const uint32_t p = pos[i];
-        id[p] = id2[i];
-        lo[p] = lo2[i];
-        hi[p] = hi2[i];
+// The programme of the optimal collapse (see the emission below) at binary
+// node `node` of children l and r with their boxes, and cnt triangles.
+__device__ inline void wide_dp(int node, int32_t l, int32_t r, const float3& llo, const float3& lhi, const float3& rlo,
+                               const float3& rhi, int cnt, const NodeData& nd, const WideDP& wd, int max_leaf, float c_trav,
+                               float c_isect) {
+    const float c_entry = kLeafEntry * c_trav;
+    float Cl[5], Cr[5];
+    int Wl[5], Wr[5];
+    dp_child(l, llo, lhi, wd, c_isect, c_entry, Cl, Wl);
+    dp_child(r, rlo, rhi, wd, c_isect, c_entry, Cr, Wr);
+    const float3 lo = make_float3(fminf(llo.x, rlo.x), fminf(llo.y, rlo.y), fminf(llo.z, rlo.z));
+    const float3 hi = make_float3(fmaxf(lhi.x, rhi.x), fmaxf(lhi.y, rhi.y), fmaxf(lhi.z, rhi.z));
+    const float a = half_area(lo, hi);
+    // the wide node rooted here: its four slots split between the children
+    int kint = 1;
+    float best4 = Cl[1] + Cr[3];
+    for (int k = 2; k <= 3; ++k) {
+        const float c = Cl[k] + Cr[4 - k];
+        if (c < best4) { best4 = c; kint = k; }
     }
-    if (i == m - 1) *m_out = pos[i] + keep[i];
+    const float c_int = c_trav * a + best4;
+    const float c_leaf = cnt <= max_leaf ? (c_isect * (float)cnt + c_entry) * a : INFINITY;
+    const bool leaf = c_leaf <= c_int;
+    float C[5];
+    int W[5];
+    C[1] = leaf ? c_leaf : c_int;
+    W[1] = leaf ? 0 : 1 + Wl[kint] + Wr[4 - kint];
+    uint32_t dec = (leaf ? 1u : 0u) | ((uint32_t)kint << 1);
+    for (int j = 2; j <= 4; ++j) {
+        float best = C[j - 1];
+        int d = 0;
+        for (int k = 1; k < j; ++k) {
+            const float c = Cl[k] + Cr[j - k];
+            if (c < best) { best = c; d = k; }
+        }
+        C[j] = best;
+        W[j] = d ? Wl[d] + Wr[j - d] : W[j - 1];
+        dec |= (uint32_t)d << (2 * j - 1);
+    }
+    nd.lo[node] = make_float4(lo.x, lo.y, lo.z, 0.0f);
+    nd.hi[node] = make_float4(hi.x, hi.y, hi.z, 0.0f);
+    wd.cost[node] = make_float4(C[1], C[2], C[3], C[4]);
+    wd.count[node] = make_int4(W[1], W[2], W[3], W[4]);
+    wd.dec[node] = dec;
+}
+
+constexpr int kPlocItems = 4;                     // clusters per thread of the two kernels below
+constexpr int kPlocTile = kB * kPlocItems;
+
+// What becomes of cluster i: merged with its neighbour j as the lower or the
+// upper one of a mutual pair, or kept.
+struct PlocFlags {
+    bool lower, keep;
+};
+
+__device__ inline PlocFlags ploc_flags(int i, int m, const int32_t* __restrict__ nn, int& j) {
+    PlocFlags f{false, false};
+    j = -1;
+    if (i < m) {
+        j = nn[i];
+        const bool mutual = j >= 0 && nn[j] == i;
+        f.lower = mutual && i < j;
+        f.keep = !mutual || i < j;
+    }
+    return f;
+}
+
+// Kept clusters and merges of each tile of kPlocTile clusters (kept in the low
+// half of the word).
+__global__ __launch_bounds__(kB) void k_ploc_count(const RoundState* __restrict__ rs, const int32_t* __restrict__ nn,
+                                                    uint32_t* __restrict__ tiles) {
+    const int m = rs->m, base = (int)blockIdx.x * kPlocTile;
+    if (base >= m) return;
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < kPlocItems; ++k) {
+        int j;
+        const PlocFlags f = ploc_flags(base + k * kB + (int)threadIdx.x, m, nn, j);
+        c += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f.keep)) | (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(f.lower)) << 16;
+    }
+    __shared__ uint32_t w[kB / 64];
+    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) tiles[blockIdx.x] = w[0] + w[1] + w[2] + w[3];
+}
+
+// A binary node made by a merge: children, parents, box, triangle count and,
+// for the optimal collapse, its programme (wd.cost not NULL).
+struct PlocOut {
+    int n;
+    int32_t *left, *right, *parent, *cnt;
+    NodeData nd;
+    WideDP wd;
+    int max_leaf;
+    float c_trav, c_isect;
+
+    __device__ inline void make(int32_t node, int32_t a, int32_t b, const float3& alo, const float3& ahi, const float3& blo,
+                                const float3& bhi) const {
+        left[node] = a;
+        right[node] = b;
+        parent[node_slot(a, n)] = node;
+        parent[node_slot(b, n)] = node;
+        const int c = (a < 0 ? 1 : cnt[a]) + (b < 0 ? 1 : cnt[b]);
+        cnt[node] = c;
+        if (wd.cost) wide_dp(node, a, b, alo, ahi, blo, bhi, c, nd, wd, max_leaf, c_trav, c_isect);
+    }
+};
+
+// The next round's clusters, in order, and the nodes of this round's merges,
+// numbered downward in order too.
+__global__ __launch_bounds__(kB) void k_ploc_merge(const RoundState* __restrict__ rs, RoundState* __restrict__ rs_next,
+                                                    const int32_t* __restrict__ nn, const uint32_t* __restrict__ tiles,
+                                                    const int32_t* __restrict__ id, const float4* __restrict__ lo,
+                                                    const float4* __restrict__ hi, int32_t* __restrict__ id2,
+                                                    float4* __restrict__ lo2, float4* __restrict__ hi2, PlocOut out) {
+    const int m = rs->m, next_id = rs->next_id, base = (int)blockIdx.x * kPlocTile;
+    if (base >= m) return;
+    const int wave = threadIdx.x >> 6;
+    __shared__ uint32_t before[2][kB / 64];        // kept, merged in the tiles before
+    __shared__ uint32_t part[kPlocItems][kB / 64];
+    uint32_t kept = 0, merged = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kB) {
+        kept += tiles[t] & 0xFFFFu;
+        merged += tiles[t] >> 16;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        kept += (uint32_t)__shfl_xor((int)kept, o);
+        merged += (uint32_t)__shfl_xor((int)merged, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        before[0][wave] = kept;
+        before[1][wave] = merged;
+    }
+    PlocFlags f[kPlocItems];
+    int j[kPlocItems];
+    uint32_t mine[kPlocItems];   // kept, merged among the wave's lanes before this one
+#pragma unroll
+    for (int k = 0; k < kPlocItems; ++k) {
+        f[k] = ploc_flags(base + k * kB + (int)threadIdx.x, m, nn, j[k]);
+        const unsigned long long a = __builtin_amdgcn_ballot_w64(f[k].keep), b = __builtin_amdgcn_ballot_w64(f[k].lower);
+        mine[k] = __builtin_amdgcn_mbcnt_hi((uint32_t)(a >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)a, 0u)) |
+                  __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u)) << 16;
+        if ((threadIdx.x & 63) == 0) part[k][wave] = (uint32_t)__popcll(a) | (uint32_t)__popcll(b) << 16;
+    }
+    __syncthreads();
+    kept = before[0][0] + before[0][1] + before[0][2] + before[0][3];
+    merged = before[1][0] + before[1][1] + before[1][2] + before[1][3];
+#pragma unroll
+    for (int k = 0; k < kPlocItems; ++k) {
+        uint32_t run = 0;
+        for (int w = 0; w < kB / 64; ++w) {
+            const uint32_t c = part[k][w];
+            if (w < wave) run += c;
+        }
+        const int i = base + k * kB + (int)threadIdx.x;
+        if (f[k].keep) {
+            const uint32_t at = kept + ((run + mine[k]) & 0xFFFFu);
+            int32_t c = id[i];
+            float4 l = lo[i], h = hi[i];
+            if (f[k].lower) {
+                const int32_t node = next_id - (int32_t)(merged + ((run + mine[k]) >> 16));
+                const float4 lb = lo[j[k]], hb = hi[j[k]];
+                out.make(node, c, id[j[k]], make_float3(l.x, l.y, l.z), make_float3(h.x, h.y, h.z),
+                         make_float3(lb.x, lb.y, lb.z), make_float3(hb.x, hb.y, hb.z));
+                l = make_float4(fminf(l.x, lb.x), fminf(l.y, lb.y), fminf(l.z, lb.z), 0.0f);
+                h = make_float4(fmaxf(h.x, hb.x), fmaxf(h.y, hb.y), fmaxf(h.z, hb.z), 0.0f);
+                c = node;
+            }
+            id2[at] = c;
+            lo2[at] = l;
+            hi2[at] = h;
+        }
+        const uint32_t all = part[k][0] + part[k][1] + part[k][2] + part[k][3];
+        kept += all & 0xFFFFu;
+        merged += all >> 16;
+    }
+    if (base + kPlocTile >= m && threadIdx.x == 0) *rs_next = RoundState{(int32_t)kept, next_id - (int32_t)merged};
 }
 
 // The last rounds of PLOC, once at most kPlocSmall clusters remain, in one
@@ -330,13 +556,13 @@ __global__ __launch_bounds__(kB) void k_ploc_compact(int m, const uint32_t* __re
 // if max_rounds ran out).
 constexpr int kPlocSmall = 1024;
 
-__global__ __launch_bounds__(kPlocSmall) void k_ploc_finish(int m, int n, int max_rounds,
+__global__ __launch_bounds__(kPlocSmall) void k_ploc_finish(RoundState* rs, int max_rounds,
                                                              const int32_t* __restrict__ id_in,
                                                              const float4* __restrict__ lo_in,
-                                                             const float4* __restrict__ hi_in,
-                                                             int32_t* __restrict__ next_id, int32_t* __restrict__ left,
-                                                             int32_t* __restrict__ right, int32_t* __restrict__ parent,
-                                                             uint32_t* __restrict__ m_out) {
+                                                             const float4* __restrict__ hi_in, PlocOut out) {
+    int m = rs->m;
+    __shared__ int32_t s_next;
+    if (threadIdx.x == 0) s_next = rs->next_id;
     __shared__ float s[6][kPlocSmall];                 // lo.x, lo.y, lo.z, hi.x, hi.y, hi.z
     __shared__ int32_t s_id[kPlocSmall];
     __shared__ int32_t s_nn[kPlocSmall];
@@ -383,12 +609,9 @@ __global__ __launch_bounds__(kPlocSmall) void k_ploc_finish(int m, int n, int ma
             const int j = s_nn[i];
             if (j >= 0 && s_nn[j] == i) {
                 if (i < j) {
-                    const int32_t node = atomicSub(next_id, 1);
-                    const int32_t ca = s_id[i], cb = s_id[j];
-                    left[node] = ca;
-                    right[node] = cb;
-                    parent[node_slot(ca, n)] = node;
-                    parent[node_slot(cb, n)] = node;
+                    const int32_t node = atomicSub(&s_next, 1);
+                    out.make(node, s_id[i], s_id[j], make_float3(b0, b1, b2), make_float3(b3, b4, b5),
+                             make_float3(s[0][j], s[1][j], s[2][j]), make_float3(s[3][j], s[4][j], s[5][j]));
                     nid = node;
                     b0 = fminf(b0, s[0][j]); b1 = fminf(b1, s[1][j]); b2 = fminf(b2, s[2][j]);
                     b3 = fmaxf(b3, s[3][j]); b4 = fmaxf(b4, s[4][j]); b5 = fmaxf(b5, s[5][j]);
@@ -415,7 +638,7 @@ __global__ __launch_bounds__(kPlocSmall) void k_ploc_finish(int m, int n, int ma
         m = (int)total;
         __syncthreads();
     }
-    if (i == 0) *m_out = (uint32_t)m;
+    if (i == 0) *rs = RoundState{m, s_next};
 }
 
 // ---- bottom-up passes -----------------------------------------------------
@@ -452,17 +675,6 @@ __global__ __launch_bounds__(kB) void k_level_starts(int m, const uint64_t* __re
     const int i = blockIdx.x * kB + threadIdx.x;
     if (i < m && (i == 0 || keys[i] != keys[i - 1])) starts[keys[i]] = (uint32_t)i;
 }
-
-// Leaves under every inner node.
-struct LeafCountBody {
-    const int32_t* left;
-    const int32_t* right;
-    int32_t* cnt;
-    __device__ void operator()(int node) const {
-        const int32_t l = left[node], r = right[node];
-        cnt[node] = (l < 0 ? 1 : cnt[l]) + (r < 0 ? 1 : cnt[r]);
-    }
-};
 
 __global__ __launch_bounds__(kB) void k_dfs_first(int n, const int32_t* __restrict__ left,
                                                    const int32_t* __restrict__ right, const int32_t* __restrict__ parent,
@@ -507,18 +719,6 @@ __global__ __launch_bounds__(kB) void k_dfs_renumber(int n, const int32_t* __res
         rlast[x] = first[x] + cnt[x] - 1;
     }
 }
-
-__global__ void k_set_i32(int32_t* p, int32_t v) {
-    if (threadIdx.x == 0) *p = v;
-}
-
-struct NodeData {
-    float4* lo;        // box lo, w unused
-    float4* hi;
-    float* cost;
-    int32_t* n_inner;  // emitted inner nodes in the subtree (0 when collapsed)
-    int32_t* collapse;
-};
 
 __device__ inline void child_info(int32_t c, const float4* __restrict__ tlo, const float4* __restrict__ thi,
                                   const uint32_t* __restrict__ sorted, NodeData nd, float c_isect,
@@ -659,8 +859,11 @@ __global__ __launch_bounds__(kB) void k_pack_nodes(int n, const int32_t* __restr
 // Occupancy grid of the scene box: the cell of each triangle's centroid is
 // set.  Most triangles find their cell already set, so the word is read
 // first and only a clear bit takes an atomic.
-__global__ void k_occupancy(const float* __restrict__ verts, const uint32_t* __restrict__ idx, uint32_t n,
-                            OccGrid g, uint32_t* bits) {
+__global__ __launch_bounds__(1024) void k_occupancy(const float* __restrict__ verts, const uint32_t* __restrict__ idx, uint32_t n,
+                                                    OccGrid g, uint32_t* bits) {
+    extern __shared__ uint32_t own[];   // the workgroup's grid (g.words)
+    for (uint32_t w = threadIdx.x; w < g.words; w += blockDim.x) own[w] = 0u;
+    __syncthreads();
     for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
         int q[3];
 #pragma unroll
@@ -672,9 +875,11 @@ __global__ void k_occupancy(const float* __restrict__ verts, const uint32_t* __r
         }
         const uint32_t cell = (uint32_t)((q[2] * g.n[1] + q[1]) * g.n[0] + q[0]);
         const uint32_t m = 1u << (cell & 31u);
-        if (!(__hip_atomic_load(&bits[cell >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m))
-            atomicOr(&bits[cell >> 5], m);
+        if (!(own[cell >> 5] & m)) atomicOr(&own[cell >> 5], m);
     }
+    __syncthreads();
+    for (uint32_t w = threadIdx.x; w < g.words; w += blockDim.x)
+        if (own[w]) atomicOr(&bits[w], own[w]);
 }
 
 // Whole scene in one leaf (n <= max_leaf): a root whose two children are the
@@ -700,7 +905,7 @@ __global__ void k_pack_single(int n, const float4* __restrict__ tlo, const float
 // largest box surface area by its two children, until it has four children
 // or only leaves.  Boxes are copied from the binary nodes (already widened),
 // so the wide tree prunes exactly as conservatively.  Built level by level:
-// the nodes of one level are slots [begin, end), each records the binary
+// the nodes of one level are consecutive slots, each records the binary
 // node it expands in src[], and its inner children get slots of the next
 // level from one counter.
 // ---------------------------------------------------------------------------
@@ -713,19 +918,58 @@ struct WideStats {
     unsigned long long hist[8];
 };
 
-// leaf_sizes: the node's leaves by size in 4-bit fields (field c counts the
-// leaves of c + 1 triangles; a node has at most 4).  Every atomic has the
-// same address in all lanes, so the compiler sums each over the wave first:
-// one memory atomic per wave and counter.
-__device__ inline void wide_stat(WideStats* ws, float node_area, float leaf_cost, uint32_t n_leaves,
-                                 uint32_t leaf_sizes, float c_trav, float inv_root_area) {
-    const float rel = (c_trav * node_area + leaf_cost) * inv_root_area;
-    atomicAdd(&ws->sah_fx, (unsigned long long)((double)rel * 4294967296.0 + 0.5));
-    if (n_leaves) atomicAdd(&ws->leaves, (unsigned long long)n_leaves);
+// A thread's share of them; leaf_sizes: a node's leaves by size in 4-bit
+// fields (field c counts the leaves of c + 1 triangles; a node has at most 4).
+struct WideAcc {
+    unsigned long long sah_fx = 0;
+    uint32_t leaves = 0;
+    uint32_t hist[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    __device__ inline void add(float node_area, float leaf_cost, uint32_t n_leaves, uint32_t leaf_sizes, float c_trav,
+                               float inv_root_area) {
+        const float rel = (c_trav * node_area + leaf_cost) * inv_root_area;
+        sah_fx += (unsigned long long)((double)rel * 4294967296.0 + 0.5);
+        leaves += n_leaves;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const uint32_t v = (leaf_sizes >> (4 * c)) & 15u;
-        if (v) atomicAdd(&ws->hist[c], (unsigned long long)v);
+        for (int c = 0; c < 8; ++c) hist[c] += (leaf_sizes >> (4 * c)) & 15u;
+    }
+    // All threads of the workgroup: summed in LDS, ten memory atomics a
+    // workgroup (ten a wave were half of an emission launch).
+    __device__ inline void flush(WideStats* ws) const {
+        __shared__ unsigned long long sum[10];
+        if (threadIdx.x < 10) sum[threadIdx.x] = 0;
+        __syncthreads();
+        if (leaves | (uint32_t)(sah_fx != 0)) {
+            atomicAdd(&sum[0], (unsigned long long)leaves);
+            atomicAdd(&sum[1], sah_fx);
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (hist[c]) atomicAdd(&sum[2 + c], (unsigned long long)hist[c]);
+        }
+        __syncthreads();
+        if (threadIdx.x < 10 && sum[threadIdx.x])
+            atomicAdd(threadIdx.x == 0 ? &ws->leaves : threadIdx.x == 1 ? &ws->sah_fx : &ws->hist[threadIdx.x - 2],
+                      sum[threadIdx.x]);
+    }
+};
+
+// The levels of the wide tree as they are emitted: the nodes of level l are
+// slots [start[l], start[l] + count[l]).  Level l's launch finds both there,
+// counts level l + 1 and stores its start, so the levels need no host read
+// between them.  A launch after an error does nothing.
+constexpr uint32_t kMaxWideLevels = 1024;
+struct LevelTable {
+    uint32_t error;
+    uint32_t count[kMaxWideLevels + 1];
+    uint32_t start[kMaxWideLevels + 1];
+};
+
+__global__ __launch_bounds__(kB) void k_init_levels(LevelTable* lt, uint32_t* src, WideStats* ws) {
+    for (uint32_t i = threadIdx.x; i <= kMaxWideLevels; i += kB) lt->count[i] = i == 0 ? 1u : 0u;
+    for (uint32_t i = threadIdx.x; i < sizeof(WideStats) / 8; i += kB) ((unsigned long long*)ws)[i] = 0;
+    if (threadIdx.x == 0) {
+        lt->error = 0u;
+        lt->start[0] = 0u;
+        src[0] = 0u;
     }
 }
 
@@ -751,12 +995,9 @@ __device__ inline void wide_children(const float4* __restrict__ n2, uint32_t nod
     b.area = half_area(b);
 }
 
-__global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2, uint32_t begin, uint32_t end,
-                                                   uint32_t* __restrict__ src, uint32_t* __restrict__ counter,
-                                                   float4* __restrict__ n4, WideStats* stats, float c_trav,
-                                                   float c_isect, float inv_root_area) {
-    const uint32_t slot = begin + blockIdx.x * kB + threadIdx.x;
-    if (slot >= end) return;
+__device__ inline void collapse4_node(const float4* __restrict__ n2, uint32_t slot, uint32_t end, uint32_t cap,
+                                      uint32_t level, LevelTable* lt, uint32_t* __restrict__ src, float4* __restrict__ n4,
+                                      WideAcc& acc, float c_trav, float c_isect, float inv_root_area) {
     WideCand c[4];
     int m = 2;
     wide_children(n2, src[slot], c[0], c[1]);
@@ -773,7 +1014,8 @@ __global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2,
     }
     int n_inner = 0;
     for (int i = 0; i < m; ++i) n_inner += (c[i].link & kLeafBit) ? 0 : 1;
-    const uint32_t base = n_inner ? atomicAdd(counter, (uint32_t)n_inner) : 0u;
+    const uint32_t base = end + (n_inner ? atomicAdd(&lt->count[level + 1], (uint32_t)n_inner) : 0u);
+    if (base + (uint32_t)n_inner > cap) { atomicOr(&lt->error, 2u); return; }
     float lo[3][4], hi[3][4];
     uint32_t link[4];
     int k = 0;
@@ -811,7 +1053,19 @@ __global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2,
             leaf_sizes += 1u << (4u * (c[i].link & 7u));
         }
     }
-    wide_stat(stats, half_area(u), leaf_cost, n_leaves, leaf_sizes, c_trav, inv_root_area);
+    acc.add(half_area(u), leaf_cost, n_leaves, leaf_sizes, c_trav, inv_root_area);
+}
+
+__global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2, uint32_t cap, uint32_t level,
+                                                   LevelTable* lt, uint32_t* __restrict__ src, float4* __restrict__ n4,
+                                                   WideStats* stats, float c_trav, float c_isect, float inv_root_area) {
+    const uint32_t begin = lt->start[level], count = lt->count[level], end = begin + count;
+    if (lt->error || count == 0) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) lt->start[level + 1] = end;
+    WideAcc acc;
+    for (uint32_t i = blockIdx.x * kB + threadIdx.x; i < count; i += gridDim.x * kB)
+        collapse4_node(n2, begin + i, end, cap, level, lt, src, n4, acc, c_trav, c_isect, inv_root_area);
+    acc.flush(stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -831,34 +1085,6 @@ __global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2,
 // child's slots for j = 2, 3, 4 (0: j - 1 slots of i itself suffice).
 // ---------------------------------------------------------------------------
 
-struct WideDP {
-    float4* cost;      // C(i, 1..4)
-    int4* count;       // wide nodes of each choice
-    uint32_t* dec;
-};
-
-__device__ inline void dp_child(int32_t c, const float4* __restrict__ tlo, const float4* __restrict__ thi,
-                                const uint32_t* __restrict__ sorted, NodeData nd, WideDP wd, float c_isect,
-                                float c_entry, float3& lo, float3& hi, float C[5], int W[5]) {
-    if (c < 0) {
-        const uint32_t t = sorted[(uint32_t)c & ~kLeafBit];
-        const float4 a = tlo[t], b = thi[t];
-        lo = make_float3(a.x, a.y, a.z);
-        hi = make_float3(b.x, b.y, b.z);
-        const float ct = (c_isect + c_entry) * half_area(lo, hi);
-        for (int j = 1; j <= 4; ++j) { C[j] = ct; W[j] = 0; }
-    } else {
-        // computed earlier in the pass (a deeper level, or the sibling's walk)
-        const float4 a = nd.lo[c], b = nd.hi[c];
-        lo = make_float3(a.x, a.y, a.z);
-        hi = make_float3(b.x, b.y, b.z);
-        const float4 cc = wd.cost[c];
-        const int4 ww = wd.count[c];
-        C[1] = cc.x; C[2] = cc.y; C[3] = cc.z; C[4] = cc.w;
-        W[1] = ww.x; W[2] = ww.y; W[3] = ww.z; W[4] = ww.w;
-    }
-}
-
 struct WideDPBody {
     const int32_t* left;
     const int32_t* right;
@@ -871,48 +1097,18 @@ struct WideDPBody {
     WideDP wd;
     int max_leaf;
     float c_trav, c_isect;
+    __device__ void box(int32_t c, float3& lo, float3& hi) const {
+        const uint32_t t = c < 0 ? sorted[(uint32_t)c & ~kLeafBit] : 0u;
+        const float4 a = c < 0 ? tlo[t] : nd.lo[c], b = c < 0 ? thi[t] : nd.hi[c];
+        lo = make_float3(a.x, a.y, a.z);
+        hi = make_float3(b.x, b.y, b.z);
+    }
     __device__ void operator()(int node) const {
-        const float c_entry = kLeafEntry * c_trav;
         float3 llo, lhi, rlo, rhi;
-        float Cl[5], Cr[5];
-        int Wl[5], Wr[5];
-        dp_child(left[node], tlo, thi, sorted, nd, wd, c_isect, c_entry, llo, lhi, Cl, Wl);
-        dp_child(right[node], tlo, thi, sorted, nd, wd, c_isect, c_entry, rlo, rhi, Cr, Wr);
-        const float3 lo = make_float3(fminf(llo.x, rlo.x), fminf(llo.y, rlo.y), fminf(llo.z, rlo.z));
-        const float3 hi = make_float3(fmaxf(lhi.x, rhi.x), fmaxf(lhi.y, rhi.y), fmaxf(lhi.z, rhi.z));
-        const float a = half_area(lo, hi);
-        const int cnt = rlast[node] - rfirst[node] + 1;
-        // the wide node rooted here: its four slots split between the children
-        int kint = 1;
-        float best4 = Cl[1] + Cr[3];
-        for (int k = 2; k <= 3; ++k) {
-            const float c = Cl[k] + Cr[4 - k];
-            if (c < best4) { best4 = c; kint = k; }
-        }
-        const float c_int = c_trav * a + best4;
-        const float c_leaf = cnt <= max_leaf ? (c_isect * (float)cnt + c_entry) * a : INFINITY;
-        const bool leaf = c_leaf <= c_int;
-        float C[5];
-        int W[5];
-        C[1] = leaf ? c_leaf : c_int;
-        W[1] = leaf ? 0 : 1 + Wl[kint] + Wr[4 - kint];
-        uint32_t dec = (leaf ? 1u : 0u) | ((uint32_t)kint << 1);
-        for (int j = 2; j <= 4; ++j) {
-            float best = C[j - 1];
-            int d = 0;
-            for (int k = 1; k < j; ++k) {
-                const float c = Cl[k] + Cr[j - k];
-                if (c < best) { best = c; d = k; }
-            }
-            C[j] = best;
-            W[j] = d ? Wl[d] + Wr[j - d] : W[j - 1];
-            dec |= (uint32_t)d << (2 * j - 1);
-        }
-        nd.lo[node] = make_float4(lo.x, lo.y, lo.z, 0.0f);
-        nd.hi[node] = make_float4(hi.x, hi.y, hi.z, 0.0f);
-        wd.cost[node] = make_float4(C[1], C[2], C[3], C[4]);
-        wd.count[node] = make_int4(W[1], W[2], W[3], W[4]);
-        wd.dec[node] = dec;
+        box(left[node], llo, lhi);
+        box(right[node], rlo, rhi);
+        wide_dp(node, left[node], right[node], llo, lhi, rlo, rhi, rlast[node] - rfirst[node] + 1, nd, wd, max_leaf, c_trav,
+                c_isect);
     }
 };
 
@@ -934,17 +1130,23 @@ __global__ void k_wide_summary(const int32_t* __restrict__ left, const int32_t* 
     sm->bbox[3] = b.x; sm->bbox[4] = b.y; sm->bbox[5] = b.z;
 }
 
-// One level of the optimal collapse: slot s expands binary node src[s].
-__global__ __launch_bounds__(kB) void k_emit4(const int32_t* __restrict__ left, const int32_t* __restrict__ right,
-                                               const int32_t* __restrict__ rfirst, const int32_t* __restrict__ rlast,
-                                               const float4* __restrict__ tlo, const float4* __restrict__ thi,
-                                               const uint32_t* __restrict__ sorted, NodeData nd, WideDP wd,
-                                               uint32_t begin, uint32_t end, uint32_t* __restrict__ src,
-                                               uint32_t* __restrict__ counter, float4* __restrict__ n4,
-                                               WideStats* stats, float c_trav, float c_isect, float inv_root_area,
-                                               uint32_t cap, uint32_t* __restrict__ error) {
-    const uint32_t slot = begin + blockIdx.x * kB + threadIdx.x;
-    if (slot >= end) return;
+// What the optimal collapse reads of the binary tree.
+struct BinTree {
+    const int32_t *left, *right, *rfirst, *rlast;
+    const float4 *tlo, *thi;
+    const uint32_t* sorted;
+    NodeData nd;
+    WideDP wd;
+};
+
+__device__ inline void emit4_node(const BinTree& t, uint32_t slot, uint32_t end, uint32_t cap, uint32_t level,
+                                  LevelTable* lt, uint32_t* __restrict__ src, float4* __restrict__ n4, WideAcc& acc,
+                                  float c_trav, float c_isect, float inv_root_area) {
+    const int32_t* left = t.left;
+    const int32_t* right = t.right;
+    const NodeData& nd = t.nd;
+    const WideDP& wd = t.wd;
+    uint32_t* error = &lt->error;
     const int32_t x = (int32_t)src[slot];
     const int kint = (int)((wd.dec[x] >> 1) & 3u);
     // work list of (binary child, slots it may fill); the slots of its
@@ -978,14 +1180,14 @@ __global__ __launch_bounds__(kB) void k_emit4(const int32_t* __restrict__ left, 
         float4 a, b;
         if (c < 0) {   // one triangle
             const uint32_t pos = (uint32_t)c & ~kLeafBit;
-            const uint32_t t = sorted[pos];
-            a = tlo[t]; b = thi[t];
+            const uint32_t tri = t.sorted[pos];
+            a = t.tlo[tri]; b = t.thi[tri];
             link[m] = leaf_link(pos, 1u);
             inner[m] = -1;
         } else {
             a = nd.lo[c]; b = nd.hi[c];
             if (wd.dec[c] & 1u) {
-                link[m] = leaf_link((uint32_t)rfirst[c], (uint32_t)(rlast[c] - rfirst[c] + 1));
+                link[m] = leaf_link((uint32_t)t.rfirst[c], (uint32_t)(t.rlast[c] - t.rfirst[c] + 1));
                 inner[m] = -1;
             } else {
                 link[m] = 0u;
@@ -1007,7 +1209,7 @@ __global__ __launch_bounds__(kB) void k_emit4(const int32_t* __restrict__ left, 
     if (sp > 0 || m < 2) { atomicOr(error, 1u); return; }
     int n_inner = 0;
     for (int i = 0; i < m; ++i) n_inner += inner[i] >= 0 ? 1 : 0;
-    const uint32_t base = n_inner ? atomicAdd(counter, (uint32_t)n_inner) : 0u;
+    const uint32_t base = end + (n_inner ? atomicAdd(&lt->count[level + 1], (uint32_t)n_inner) : 0u);
     if (base + (uint32_t)n_inner > cap) { atomicOr(error, 2u); return; }   // more nodes than counted
     int k = 0;
     for (int i = 0; i < 4; ++i) {
@@ -1031,8 +1233,21 @@ __global__ __launch_bounds__(kB) void k_emit4(const int32_t* __restrict__ left, 
                        __uint_as_float(link[3]));
     o[7] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const float4 xa = nd.lo[x], xb = nd.hi[x];
-    wide_stat(stats, half_area(make_float3(xa.x, xa.y, xa.z), make_float3(xb.x, xb.y, xb.z)), leaf_cost, n_leaves,
-              leaf_sizes, c_trav, inv_root_area);
+    acc.add(half_area(make_float3(xa.x, xa.y, xa.z), make_float3(xb.x, xb.y, xb.z)), leaf_cost, n_leaves, leaf_sizes,
+            c_trav, inv_root_area);
+}
+
+// One level of the optimal collapse: slot s expands binary node src[s].
+__global__ __launch_bounds__(kB) void k_emit4(BinTree t, uint32_t cap, uint32_t level, LevelTable* lt,
+                                               uint32_t* __restrict__ src, float4* __restrict__ n4, WideStats* stats,
+                                               float c_trav, float c_isect, float inv_root_area) {
+    const uint32_t begin = lt->start[level], count = lt->count[level], end = begin + count;
+    if (lt->error || count == 0) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) lt->start[level + 1] = end;
+    WideAcc acc;
+    for (uint32_t i = blockIdx.x * kB + threadIdx.x; i < count; i += gridDim.x * kB)
+        emit4_node(t, begin + i, end, cap, level, lt, src, n4, acc, c_trav, c_isect, inv_root_area);
+    acc.flush(stats);
 }
 
 __global__ void k_set_u32(uint32_t* p, uint32_t v) {
@@ -1104,20 +1319,40 @@ rcp_status dalloc(T** p, size_t count) {
     return dev_alloc((void**)p, sizeof(T) * count);
 }
 
-// Scratch buffers of a build, released on its stream when the set goes out
-// of scope (stream-ordered, so no device-wide synchronisation).
+// Scratch buffers of a build, released on its stream when the set goes out of
+// scope (stream-ordered, so no device-wide synchronisation).  They are cut from
+// a few large blocks: what an allocation and its release cost does not depend
+// on its size (50 of 6 MB: 12 ms, one of 330 MB: 0.5 ms).
 struct TempSet {
     hipStream_t stream;
     std::vector<void*> ptrs;
+    char* at = nullptr;
+    size_t left = 0;
     explicit TempSet(hipStream_t s) : stream(s) {}
     ~TempSet() {
         for (void* p : ptrs) stream_free(p, stream);
     }
+    // A block of at least `bytes` for the buffers to come.
+    rcp_status reserve(size_t bytes) {
+        void* p = nullptr;
+        const rcp_status st = stream_alloc(&p, bytes, stream);
+        if (st != RCP_OK) return st;
+        ptrs.push_back(p);
+        at = (char*)p;
+        left = bytes;
+        return RCP_OK;
+    }
     template <typename T>
     rcp_status alloc(T** p, size_t count) {
-        rcp_status st = stream_alloc((void**)p, sizeof(T) * count, stream);
-        if (st == RCP_OK && *p) ptrs.push_back((void*)*p);
-        return st;
+        const size_t bytes = (sizeof(T) * (count > 0 ? count : 1) + 255) & ~(size_t)255;
+        if (bytes > left) {
+            const rcp_status st = reserve(bytes);
+            if (st != RCP_OK) return st;
+        }
+        *p = (T*)at;
+        at += bytes;
+        left -= bytes;
+        return RCP_OK;
     }
 };
 
@@ -1188,18 +1423,22 @@ rcp_status bottom_up(const LevelOrder& lo, const Body& body, hipStream_t stream)
 // order (sorted is permuted in place).  Returns RCP_ERR_NOT_READY when the
 // rounds do not converge within the cap; the caller then builds the radix
 // tree from the untouched sorted order instead.
-rcp_status ploc_build(int n, const float4* tlo, const float4* thi, uint32_t* sorted, int32_t* left, int32_t* right,
-                      int32_t* parent, int32_t* rfirst, int32_t* rlast, TempSet& outer, LevelOrder& levels,
-                      hipStream_t stream) {
-    TempSet tmp(stream);
-    int32_t *id, *id2, *nn, *next_id, *cnt, *first, *parent_tmp;
+// With the SAH collapse (wd.cost not NULL) the merges run its programme as they
+// make the nodes, and the tree needs no bottom-up pass.
+rcp_status ploc_build(int n, const float4* tlo, const float4* thi, uint32_t*& sorted, int32_t* left, int32_t* right,
+                      int32_t* parent, int32_t* rfirst, int32_t* rlast, NodeData nd, WideDP wd, int max_leaf,
+                      float c_trav, float c_isect, TempSet& tmp, hipStream_t stream) {
+    int32_t *id, *id2, *nn, *cnt, *first, *parent_tmp;
     float4 *lo, *hi, *lo2, *hi2;
-    uint32_t *pos, *keep, *m_out, *scratch, *sorted2;
+    uint32_t *tiles, *sorted2;
+    RoundState* rs;
+    int log2n = 0;
+    while ((1 << log2n) < n) ++log2n;
+    const int max_rounds = 64 + 16 * log2n;
     const size_t un = (size_t)n;
     RCP_TRY(tmp.alloc(&id, un));
     RCP_TRY(tmp.alloc(&id2, un));
     RCP_TRY(tmp.alloc(&nn, un));
-    RCP_TRY(tmp.alloc(&next_id, 1));
     RCP_TRY(tmp.alloc(&cnt, un));
     RCP_TRY(tmp.alloc(&first, 2 * un));
     RCP_TRY(tmp.alloc(&parent_tmp, 2 * un));
@@ -1207,81 +1446,103 @@ rcp_status ploc_build(int n, const float4* tlo, const float4* thi, uint32_t* sor
     RCP_TRY(tmp.alloc(&hi, un));
     RCP_TRY(tmp.alloc(&lo2, un));
     RCP_TRY(tmp.alloc(&hi2, un));
-    RCP_TRY(tmp.alloc(&pos, un));
-    RCP_TRY(tmp.alloc(&keep, un));
-    RCP_TRY(tmp.alloc(&m_out, 1));
-    RCP_TRY(tmp.alloc(&scratch, scan_scratch_words(n)));
+    RCP_TRY(tmp.alloc(&tiles, un / kPlocTile + 1));
+    RCP_TRY(tmp.alloc(&rs, (size_t)max_rounds + 1));
     RCP_TRY(tmp.alloc(&sorted2, un));
-    // every entry gets its parent from a merge; -1 until then, so that a walk
-    // to the root ends whatever happens
+    // every entry but the root's gets its parent from a merge; -1 until then,
+    // so that a walk to the root ends whatever happens
     RCP_HIP(hipMemsetAsync(parent_tmp, 0xFF, sizeof(int32_t) * 2 * un, stream));
     hipLaunchKernelGGL(k_ploc_init, dim3(blocks(n)), dim3(kB), 0, stream, n, tlo, thi, (const uint32_t*)sorted, id,
-                       lo, hi);
-    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, next_id, (int32_t)(n - 2));
+                       lo, hi, rs);
     RCP_CHECK_LAUNCH();
-    int log2n = 0;
-    while ((1 << log2n) < n) ++log2n;
-    const int max_rounds = 64 + 16 * log2n;
-    int m = n, rounds = 0;
-    while (m > 1) {
-        if (m <= kPlocSmall) {   // the remaining rounds in one workgroup
-            hipLaunchKernelGGL(k_ploc_finish, dim3(1), dim3(kPlocSmall), 0, stream, m, n, max_rounds - rounds,
-                               (const int32_t*)id, (const float4*)lo, (const float4*)hi, next_id, left, right,
-                               parent_tmp, m_out);
-            RCP_CHECK_LAUNCH();
-            uint32_t fin = 0;
-            RCP_HIP(hipMemcpyAsync(&fin, m_out, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-            RCP_HIP(hipStreamSynchronize(stream));
-            if (fin != 1u) {
-                set_error("PLOC's last rounds ended with %u of %d clusters", fin, m);
-                return RCP_ERR_INTERNAL;
-            }
-            m = 1;
-            break;
+    const PlocOut out{n, left, right, parent_tmp, cnt, nd, wd, max_leaf, c_trav, c_isect};
+    // kPlocBatch rounds between host reads (a read costs about what two rounds
+    // of a small grid do)
+    constexpr int kPlocBatch = 4;
+    int m = n, round = 0;
+    while (m > kPlocSmall) {
+        if (round + kPlocBatch > max_rounds) return RCP_ERR_NOT_READY;
+        for (int k = 0; k < kPlocBatch; ++k, ++round) {
+            const unsigned tiled = (unsigned)((m + kPlocTile - 1) / kPlocTile);
+            hipLaunchKernelGGL(k_ploc_nn, dim3(blocks(m)), dim3(kB), 0, stream, (const RoundState*)rs + round,
+                               (const float4*)lo, (const float4*)hi, nn);
+            hipLaunchKernelGGL(k_ploc_count, dim3(tiled), dim3(kB), 0, stream, (const RoundState*)rs + round,
+                               (const int32_t*)nn, tiles);
+            hipLaunchKernelGGL(k_ploc_merge, dim3(tiled), dim3(kB), 0, stream, (const RoundState*)rs + round,
+                               rs + round + 1, (const int32_t*)nn, (const uint32_t*)tiles, (const int32_t*)id,
+                               (const float4*)lo, (const float4*)hi, id2, lo2, hi2, out);
+            std::swap(id, id2);
+            std::swap(lo, lo2);
+            std::swap(hi, hi2);
         }
-        if (++rounds > max_rounds) return RCP_ERR_NOT_READY;
-        hipLaunchKernelGGL(k_ploc_nn, dim3(blocks(m)), dim3(kB), 0, stream, m, (const float4*)lo, (const float4*)hi,
-                           nn);
-        hipLaunchKernelGGL(k_ploc_merge, dim3(blocks(m)), dim3(kB), 0, stream, m, n, (const int32_t*)nn,
-                           (const int32_t*)id, (const float4*)lo, (const float4*)hi, id2, lo2, hi2, pos, keep, next_id,
-                           left, right, parent_tmp);
         RCP_CHECK_LAUNCH();
-        RCP_TRY(scan_exclusive_u32(pos, m, scratch, stream));
-        hipLaunchKernelGGL(k_ploc_compact, dim3(blocks(m)), dim3(kB), 0, stream, m, (const uint32_t*)pos,
-                           (const uint32_t*)keep, (const int32_t*)id2, (const float4*)lo2, (const float4*)hi2, id, lo,
-                           hi, m_out);
-        RCP_CHECK_LAUNCH();
-        uint32_t next = 0;
-        RCP_HIP(hipMemcpyAsync(&next, m_out, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+        RoundState now{};
+        RCP_HIP(hipMemcpyAsync(&now, rs + round, sizeof(now), hipMemcpyDeviceToHost, stream));
         RCP_HIP(hipStreamSynchronize(stream));
-        if (next < 1u || next >= (uint32_t)m) {
-            set_error("PLOC round %d went from %d to %u clusters", rounds, m, next);
+        if (now.m < 1 || now.m >= m) {
+            set_error("PLOC round %d went from %d to %d clusters", round, m, now.m);
             return RCP_ERR_INTERNAL;
         }
-        m = (int)next;
+        m = now.m;
     }
-    int32_t last = 0;
-    RCP_HIP(hipMemcpyAsync(&last, next_id, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    // the remaining rounds in one workgroup
+    hipLaunchKernelGGL(k_ploc_finish, dim3(1), dim3(kPlocSmall), 0, stream, rs + round, max_rounds - round,
+                       (const int32_t*)id, (const float4*)lo, (const float4*)hi, out);
+    RCP_CHECK_LAUNCH();
+    RoundState fin{};
+    RCP_HIP(hipMemcpyAsync(&fin, rs + round, sizeof(fin), hipMemcpyDeviceToHost, stream));
     RCP_HIP(hipStreamSynchronize(stream));
-    if (last != -1) {
-        set_error("PLOC made %d inner nodes, expected %d", n - 2 - last, n - 1);
+    if (fin.m != 1 || fin.next_id != -1) {
+        set_error("PLOC ended with %d clusters of %d and made %d inner nodes of %d", fin.m, m, n - 2 - fin.next_id, n - 1);
         return RCP_ERR_INTERNAL;
     }
-    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(64), 0, stream, parent_tmp, -1);   // the root
-    RCP_CHECK_LAUNCH();
-    // the depth order of the inner nodes holds for the renumbered tree too
-    // (inner nodes keep their numbers)
-    RCP_TRY(level_order(n, parent_tmp, outer, levels, stream));
-    RCP_TRY(bottom_up(levels, LeafCountBody{left, right, cnt}, stream));
     hipLaunchKernelGGL(k_dfs_first, dim3(blocks(2L * n - 1)), dim3(kB), 0, stream, n, (const int32_t*)left,
                        (const int32_t*)right, (const int32_t*)parent_tmp, (const int32_t*)cnt, first);
     hipLaunchKernelGGL(k_dfs_renumber, dim3(blocks(2L * n - 1)), dim3(kB), 0, stream, n, (const int32_t*)first,
                        (const int32_t*)cnt, (const uint32_t*)sorted, (const int32_t*)parent_tmp, sorted2, parent,
                        left, right, rfirst, rlast);
     RCP_CHECK_LAUNCH();
-    RCP_HIP(hipMemcpyAsync(sorted, sorted2, sizeof(uint32_t) * un, hipMemcpyDeviceToDevice, stream));
-    RCP_HIP(hipStreamSynchronize(stream));
+    sorted = sorted2;
     return RCP_OK;
+}
+
+// Launch the levels of the wide tree, launch(level, workgroups), a batch of
+// them between host reads.  On return *n_nodes and *n_levels are the tree's,
+// and top_nodes[l] its nodes of levels < l.
+template <class Launch>
+rcp_status emit_levels(uint32_t cap, LevelTable* lt, const Launch& launch, uint32_t* n_nodes, uint32_t* n_levels,
+                       uint32_t* top_nodes, hipStream_t stream) {
+    constexpr uint32_t kBatch = 8;
+    // error and counts: what precedes the starts
+    std::vector<uint32_t> seen(1 + kMaxWideLevels + 1);
+    uint32_t total = 0, levels = 0;
+    for (;;) {
+        if (levels + kBatch > kMaxWideLevels) {
+            set_error("wide BVH of more than %u levels", levels);
+            return RCP_ERR_INTERNAL;
+        }
+        for (uint32_t l = levels; l < levels + kBatch; ++l) {
+            const uint32_t most = l < 15u ? std::min(cap, 1u << (2u * l)) : cap;   // nodes of level l
+            launch(l, std::min(blocks(most), 512u));
+        }
+        RCP_CHECK_LAUNCH();
+        RCP_HIP(hipMemcpyAsync(seen.data(), lt, sizeof(uint32_t) * (levels + kBatch + 2), hipMemcpyDeviceToHost, stream));
+        RCP_HIP(hipStreamSynchronize(stream));
+        for (const uint32_t last = levels + kBatch; levels < last; ++levels) {
+            const uint32_t c = seen[1 + levels];
+            if (seen[0] || c > cap - total) {
+                set_error("wide BVH: level %u has %u nodes after %u of %u (error %u)", levels, c, total, cap, seen[0]);
+                return RCP_ERR_INTERNAL;
+            }
+            if (c == 0) {
+                *n_nodes = total;
+                *n_levels = levels;
+                return RCP_OK;
+            }
+            total += c;
+            if (levels < (uint32_t)kTopLevels) top_nodes[levels + 1] = total;
+        }
+    }
 }
 
 }  // namespace
@@ -1301,10 +1562,8 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
         bool ok = false;
         ~Guard() {
             if (!ok && s) {
-                if (s->nodes) (void)hipFree(s->nodes);
                 if (s->tris) (void)hipFree(s->tris);
-                if (s->shade) (void)hipFree(s->shade);
-                if (s->normals) (void)hipFree(s->normals);
+                if (s->nodes) (void)hipFree(s->nodes);
                 if (s->occ.bits) (void)hipFree(s->occ.bits);
                 if (s->err_host) (void)hipHostFree(s->err_host);
                 delete s;
@@ -1325,34 +1584,72 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
     RCP_HIP(hipEventCreate(&e1));
     struct EvGuard { hipEvent_t a, b; ~EvGuard() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); } } evg{e0, e1};
 
-    // the box of the vertices (for the occupancy grid) and the largest
-    // |coordinate| (for the traversal's box widening), in one pass
-    float blo[3] = {INFINITY, INFINITY, INFINITY}, bhi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    float radius = 0.0f;
-    for (size_t i = 0; i < (size_t)desc->n_verts && n > 0; ++i)
-        for (int a = 0; a < 3; ++a) {
-            const float v = desc->verts[3 * i + a];
-            blo[a] = fminf(blo[a], v);
-            bhi[a] = fmaxf(bhi[a], v);
-            radius = fmaxf(radius, fabsf(v));
-        }
-
     TempSet tmp(stream);
     float* d_verts = nullptr;
     uint32_t* d_idx = nullptr;
     float* d_rgb = nullptr;
     if (n > 0) {
+        const size_t un = n;
+        RCP_TRY(tmp.reserve(12 * ((size_t)desc->n_verts + 2 * un) + 4096));
         RCP_TRY(tmp.alloc(&d_verts, 3 * (size_t)desc->n_verts));
-        RCP_TRY(tmp.alloc(&d_idx, 3 * (size_t)n));
-        RCP_TRY(tmp.alloc(&d_rgb, 3 * (size_t)n));
+        RCP_TRY(tmp.alloc(&d_idx, 3 * un));
+        RCP_TRY(tmp.alloc(&d_rgb, 3 * un));
         RCP_HIP(hipMemcpyAsync(d_verts, desc->verts, sizeof(float) * 3 * (size_t)desc->n_verts,
                                hipMemcpyHostToDevice, stream));
         RCP_HIP(hipMemcpyAsync(d_idx, desc->idx, sizeof(uint32_t) * 3 * (size_t)n, hipMemcpyHostToDevice, stream));
         RCP_HIP(hipMemcpyAsync(d_rgb, desc->tri_rgb, sizeof(float) * 3 * (size_t)n, hipMemcpyHostToDevice, stream));
     }
     RCP_HIP(hipEventRecord(e0, stream));
+
+    uint32_t n_nodes = 0, n_leaves = 0, max_depth = 0, stack_bound = 0, top_count = 0;
+    float sah = 0.0f, radius = 0.0f;
+    uint32_t* sorted = nullptr;
+    float4 *tlo = nullptr, *thi = nullptr;
     if (n > 0) {
-        // the occupancy grid over the box of the vertices
+        uint32_t* bounds;
+        uint64_t *keys, *keys2;
+        uint32_t* vals2;
+        InputCheck* chk;
+        LevelTable* lt;
+        WideStats* wst;
+        // what the default build takes: the buffers below and in ploc_build,
+        // 252 bytes a triangle, and 256 a buffer for their rounding up
+        RCP_TRY(tmp.reserve(256 * (size_t)n + 64 * 1024));
+        RCP_TRY(tmp.alloc(&chk, 1));
+        RCP_TRY(tmp.alloc(&lt, 1));
+        RCP_TRY(tmp.alloc(&wst, 1));
+        RCP_TRY(tmp.alloc(&tlo, n));
+        RCP_TRY(tmp.alloc(&thi, n));
+        RCP_TRY(tmp.alloc(&bounds, 8));
+        RCP_TRY(tmp.alloc(&keys, n));
+        RCP_TRY(tmp.alloc(&keys2, n));
+        RCP_TRY(tmp.alloc(&sorted, n));
+        RCP_TRY(tmp.alloc(&vals2, n));
+        hipLaunchKernelGGL(k_init_bounds, dim3(1), dim3(64), 0, stream, bounds, chk);
+        hipLaunchKernelGGL(k_check_inputs, dim3(std::min(blocks(n), 512u)), dim3(kB), 0, stream, (const float*)d_verts,
+                           desc->n_verts, (const uint32_t*)d_idx, (const float*)d_rgb, n, chk);
+        hipLaunchKernelGGL(k_tri_prep, dim3(std::min(blocks(n), 512u)), dim3(kB), 0, stream, (const float*)d_verts,
+                           desc->n_verts, (const uint32_t*)d_idx, n, tlo, thi, bounds);
+        hipLaunchKernelGGL(k_morton, dim3(blocks(n)), dim3(kB), 0, stream, (const float4*)tlo,
+                           (const float4*)thi, n, (const uint32_t*)bounds, keys, sorted);
+        RCP_CHECK_LAUNCH();
+        RCP_TRY(radix_sort_pairs(keys, sorted, keys2, vals2, (int)n, 64, stream));
+
+        InputCheck hc{};
+        RCP_HIP(hipMemcpyAsync(&hc, chk, sizeof(hc), hipMemcpyDeviceToHost, stream));
+        RCP_HIP(hipStreamSynchronize(stream));
+        if (hc.bad) {
+            set_error("an index is out of range, or a coordinate or colour is not finite");
+            return RCP_ERR_INVALID_ARGUMENT;
+        }
+        // the occupancy grid over the box of the vertices, and the largest
+        // |coordinate| (for the traversal's box widening)
+        float blo[3], bhi[3];
+        for (int a = 0; a < 3; ++a) {
+            blo[a] = o2f(hc.lo[a]);
+            bhi[a] = o2f(hc.hi[a]);
+            radius = fmaxf(radius, fmaxf(fabsf(blo[a]), fabsf(bhi[a])));
+        }
         const float emax = fmaxf(fmaxf(bhi[0] - blo[0], bhi[1] - blo[1]), bhi[2] - blo[2]);
         OccGrid& g = s->occ;
         for (int a = 0; a < 3; ++a) {
@@ -1367,44 +1664,15 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
         g.words = (uint32_t)(((size_t)g.n[0] * g.n[1] * g.n[2] + 31) / 32);
         RCP_TRY(dalloc(&g.bits, g.words));
         RCP_HIP(hipMemsetAsync(g.bits, 0, sizeof(uint32_t) * g.words, stream));
-        hipLaunchKernelGGL(k_occupancy, dim3(std::min(blocks(n), 4096u)), dim3(kB), 0, stream, (const float*)d_verts,
-                           (const uint32_t*)d_idx, n, g, g.bits);
+        hipLaunchKernelGGL(k_occupancy, dim3(std::min(((unsigned)n + 1023u) / 1024u, 256u)), dim3(1024),
+                           sizeof(uint32_t) * g.words, stream, (const float*)d_verts, (const uint32_t*)d_idx, n, g,
+                           g.bits);
         RCP_CHECK_LAUNCH();
-    }
-
-    uint32_t n_nodes = 0, n_leaves = 0, max_depth = 0, stack_bound = 0, top_count = 0;
-    float sah = 0.0f;
-    uint32_t* sorted = nullptr;
-    float4 *tlo = nullptr, *thi = nullptr;
-    if (n > 0) {
-        uint32_t* bounds;
-        uint64_t *keys, *keys2;
-        uint32_t* vals2;
-        RCP_TRY(tmp.alloc(&tlo, n));
-        RCP_TRY(tmp.alloc(&thi, n));
-        RCP_TRY(tmp.alloc(&bounds, 8));
-        RCP_TRY(tmp.alloc(&keys, n));
-        RCP_TRY(tmp.alloc(&keys2, n));
-        RCP_TRY(tmp.alloc(&sorted, n));
-        RCP_TRY(tmp.alloc(&vals2, n));
-        hipLaunchKernelGGL(k_init_bounds, dim3(1), dim3(64), 0, stream, bounds);
-        hipLaunchKernelGGL(k_tri_prep, dim3(std::min(blocks(n), 2048u)), dim3(kB), 0, stream, (const float*)d_verts,
-                           (const uint32_t*)d_idx, n, tlo, thi, bounds);
-        hipLaunchKernelGGL(k_morton, dim3(blocks(n)), dim3(kB), 0, stream, (const float4*)tlo,
-                           (const float4*)thi, n, (const uint32_t*)bounds, keys, sorted);
-        RCP_CHECK_LAUNCH();
-        RCP_TRY(radix_sort_pairs(keys, sorted, keys2, vals2, (int)n, 64, stream));
 
         Summary* sm;
         WideSummary* wsm;
-        WideStats* wst;
-        uint32_t* err;
         RCP_TRY(tmp.alloc(&sm, 1));
         RCP_TRY(tmp.alloc(&wsm, 1));
-        RCP_TRY(tmp.alloc(&wst, 1));
-        RCP_TRY(tmp.alloc(&err, 1));
-        RCP_HIP(hipMemsetAsync(wst, 0, sizeof(WideStats), stream));
-        RCP_HIP(hipMemsetAsync(err, 0, sizeof(uint32_t), stream));
         Summary hs{};
         WideSummary hw{};
         bool single = n <= 1;
@@ -1421,25 +1689,32 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
             RCP_TRY(tmp.alloc(&rlast, ni));
             RCP_TRY(tmp.alloc(&nd.lo, ni));
             RCP_TRY(tmp.alloc(&nd.hi, ni));
-            rcp_status tree = RCP_ERR_NOT_READY;
-            LevelOrder levels;
-            if (builder == RCP_BUILDER_PLOC)
-                tree = ploc_build((int)n, tlo, thi, sorted, left, right, parent, rfirst, rlast, tmp, levels, stream);
-            if (tree == RCP_ERR_NOT_READY) {   // the radix tree, or PLOC did not converge
-                hipLaunchKernelGGL(k_radix_tree, dim3(blocks(ni)), dim3(kB), 0, stream, (const uint64_t*)keys,
-                                   (int)n, left, right, parent, rfirst, rlast);
-                RCP_CHECK_LAUNCH();
-                tree = level_order((int)n, parent, tmp, levels, stream);
-            }
-            if (tree != RCP_OK) return tree;
-            if (collapse == RCP_COLLAPSE_SAH) {
+            const bool optimal = collapse == RCP_COLLAPSE_SAH;
+            if (optimal) {
                 RCP_TRY(tmp.alloc(&wd.cost, ni));
                 RCP_TRY(tmp.alloc(&wd.count, ni));
                 RCP_TRY(tmp.alloc(&wd.dec, ni));
-                RCP_TRY(bottom_up(levels,
-                                  WideDPBody{left, right, rfirst, rlast, tlo, thi, sorted, nd, wd, max_leaf, c_trav,
-                                             c_isect},
-                                  stream));
+            }
+            rcp_status tree = RCP_ERR_NOT_READY;
+            if (builder == RCP_BUILDER_PLOC)
+                tree = ploc_build((int)n, tlo, thi, sorted, left, right, parent, rfirst, rlast, nd, wd, max_leaf, c_trav,
+                                  c_isect, tmp, stream);
+            const bool radix = tree == RCP_ERR_NOT_READY;   // asked for, or PLOC did not converge
+            if (radix) {
+                hipLaunchKernelGGL(k_radix_tree, dim3(blocks(ni)), dim3(kB), 0, stream, (const uint64_t*)keys,
+                                   (int)n, left, right, parent, rfirst, rlast);
+                RCP_CHECK_LAUNCH();
+                tree = RCP_OK;
+            }
+            if (tree != RCP_OK) return tree;
+            LevelOrder levels;
+            if (radix || !optimal) RCP_TRY(level_order((int)n, parent, tmp, levels, stream));
+            if (optimal) {
+                if (radix)
+                    RCP_TRY(bottom_up(levels,
+                                      WideDPBody{left, right, rfirst, rlast, tlo, thi, sorted, nd, wd, max_leaf, c_trav,
+                                                 c_isect},
+                                      stream));
                 hipLaunchKernelGGL(k_wide_summary, dim3(1), dim3(1), 0, stream, (const int32_t*)left,
                                    (const int32_t*)right, nd, wd, wsm);
                 RCP_CHECK_LAUNCH();
@@ -1471,46 +1746,28 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
         uint32_t levels = 0;
         if (!single && collapse == RCP_COLLAPSE_SAH) {
             // the optimal collapse, one launch per level of wide nodes
-            n_nodes = (uint32_t)hw.n_wide;
-            uint32_t *src, *counter;
-            RCP_TRY(tmp.alloc(&src, n_nodes));
-            RCP_TRY(tmp.alloc(&counter, 1));
-            RCP_TRY(dalloc(&s->nodes, 8 * (size_t)n_nodes));
-            hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(64), 0, stream, src, 0u);
-            hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(64), 0, stream, counter, 1u);
-            RCP_CHECK_LAUNCH();
-            uint32_t begin = 0, end = 1;
-            while (begin < end) {
-                hipLaunchKernelGGL(k_emit4, dim3(blocks(end - begin)), dim3(kB), 0, stream, (const int32_t*)left,
-                                   (const int32_t*)right, (const int32_t*)rfirst, (const int32_t*)rlast,
-                                   (const float4*)tlo, (const float4*)thi, (const uint32_t*)sorted, nd, wd, begin,
-                                   end, src, counter, s->nodes, wst, c_trav, c_isect, inv_root_area, n_nodes,
-                                   err);
-                RCP_CHECK_LAUNCH();
-                uint32_t next = 0, bad = 0;
-                RCP_HIP(hipMemcpyAsync(&next, counter, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-                RCP_HIP(hipMemcpyAsync(&bad, err, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-                RCP_HIP(hipStreamSynchronize(stream));
-                if (bad || next > n_nodes || next < end) {
-                    set_error("optimal collapse: level %u ended at %u of %u nodes (error %u)", levels, next, n_nodes,
-                              bad);
-                    return RCP_ERR_INTERNAL;
-                }
-                begin = end;
-                end = next;
-                ++levels;
-                if (levels <= (uint32_t)kTopLevels) s->top_nodes[levels] = begin;   // nodes of levels < `levels`
-            }
-            if (end != n_nodes) {
-                set_error("optimal collapse emitted %u of %u wide nodes", end, n_nodes);
+            const uint32_t cap = (uint32_t)hw.n_wide;
+            const BinTree bt{left, right, rfirst, rlast, tlo, thi, sorted, nd, wd};
+            uint32_t* src;
+            RCP_TRY(tmp.alloc(&src, cap));
+            RCP_TRY(dalloc(&s->nodes, 8 * (size_t)cap));
+            hipLaunchKernelGGL(k_init_levels, dim3(1), dim3(kB), 0, stream, lt, src, wst);
+            RCP_TRY(emit_levels(cap, lt, [&](uint32_t l, unsigned grid) {
+                hipLaunchKernelGGL(k_emit4, dim3(grid), dim3(kB), 0, stream, bt, cap, l, lt, src, s->nodes, wst, c_trav,
+                                   c_isect, inv_root_area);
+            }, &n_nodes, &levels, s->top_nodes, stream));
+            if (n_nodes != cap) {
+                set_error("optimal collapse emitted %u of %u wide nodes", n_nodes, cap);
                 return RCP_ERR_INTERNAL;
             }
         } else {
+            float4* n2;   // the packed binary tree
+            uint32_t cap;
             if (single) {
-                n_nodes = 1;
-                RCP_TRY(dalloc(&s->nodes, 4));
+                cap = 1;
+                RCP_TRY(tmp.alloc(&n2, 4));
                 hipLaunchKernelGGL(k_pack_single, dim3(1), dim3(1), 0, stream, (int)n, (const float4*)tlo,
-                                   (const float4*)thi, s->nodes);
+                                   (const float4*)thi, n2);
                 RCP_CHECK_LAUNCH();
             } else {
                 const long ni = (long)n - 1;
@@ -1519,45 +1776,24 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
                 hipLaunchKernelGGL(k_layout_walk, dim3(blocks(ni)), dim3(kB), 0, stream, (int)n,
                                    (const int32_t*)left, (const int32_t*)parent, nd, newidx);
                 RCP_CHECK_LAUNCH();
-                n_nodes = (uint32_t)hs.n_inner;
-                RCP_TRY(dalloc(&s->nodes, 4 * (size_t)n_nodes));
+                cap = (uint32_t)hs.n_inner;
+                RCP_TRY(tmp.alloc(&n2, 4 * (size_t)cap));
                 hipLaunchKernelGGL(k_pack_nodes, dim3(blocks(ni)), dim3(kB), 0, stream, (int)n,
                                    (const int32_t*)left, (const int32_t*)right, (const int32_t*)rfirst,
                                    (const int32_t*)rlast, (const float4*)tlo, (const float4*)thi,
-                                   (const uint32_t*)sorted, nd, (const int32_t*)newidx, s->nodes);
+                                   (const uint32_t*)sorted, nd, (const int32_t*)newidx, n2);
                 RCP_CHECK_LAUNCH();
             }
             // greedy collapse of the packed binary tree into 4-wide nodes, one
-            // launch per level; the binary nodes are freed with the other
-            // temporaries
-            float4* n2 = s->nodes;
-            tmp.ptrs.push_back((void*)n2);
-            s->nodes = nullptr;
-            uint32_t *src, *counter;
-            RCP_TRY(tmp.alloc(&src, n_nodes));
-            RCP_TRY(tmp.alloc(&counter, 1));
-            RCP_TRY(dalloc(&s->nodes, 8 * (size_t)n_nodes));
-            hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(64), 0, stream, src, 0u);
-            hipLaunchKernelGGL(k_set_u32, dim3(1), dim3(64), 0, stream, counter, 1u);
-            RCP_CHECK_LAUNCH();
-            uint32_t begin = 0, end = 1;
-            while (begin < end) {
-                hipLaunchKernelGGL(k_collapse4, dim3(blocks(end - begin)), dim3(kB), 0, stream, (const float4*)n2,
-                                   begin, end, src, counter, s->nodes, wst, c_trav, c_isect, inv_root_area);
-                RCP_CHECK_LAUNCH();
-                uint32_t next = 0;
-                RCP_HIP(hipMemcpyAsync(&next, counter, sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-                RCP_HIP(hipStreamSynchronize(stream));
-                if (next > n_nodes || next < end) {
-                    set_error("wide BVH collapse produced %u nodes from %u binary nodes", next, n_nodes);
-                    return RCP_ERR_INTERNAL;
-                }
-                begin = end;
-                end = next;
-                ++levels;
-                if (levels <= (uint32_t)kTopLevels) s->top_nodes[levels] = begin;   // nodes of levels < `levels`
-            }
-            n_nodes = end;
+            // launch per level
+            uint32_t* src;
+            RCP_TRY(tmp.alloc(&src, cap));
+            RCP_TRY(dalloc(&s->nodes, 8 * (size_t)cap));
+            hipLaunchKernelGGL(k_init_levels, dim3(1), dim3(kB), 0, stream, lt, src, wst);
+            RCP_TRY(emit_levels(cap, lt, [&](uint32_t l, unsigned grid) {
+                hipLaunchKernelGGL(k_collapse4, dim3(grid), dim3(kB), 0, stream, (const float4*)n2, cap, l, lt, src,
+                                   s->nodes, wst, c_trav, c_isect, inv_root_area);
+            }, &n_nodes, &levels, s->top_nodes, stream));
         }
         // a tree of fewer levels is staged whole
         for (uint32_t l = levels + 1u; l <= (uint32_t)kTopLevels; ++l) s->top_nodes[l] = n_nodes;
@@ -1577,9 +1813,10 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
             for (int c = 0; c < 8; ++c) s->stats.leaf_hist[c] = (uint32_t)hst.hist[c];
             if (single) sah = c_isect * (float)n;   // one leaf of every triangle, relative to its own box
         }
-        RCP_TRY(dalloc(&s->tris, 9 * (size_t)n));   // three rotated copies
-        RCP_TRY(dalloc(&s->shade, 2 * (size_t)n));
-        RCP_TRY(dalloc(&s->normals, (size_t)n));
+        // three rotated copies of the triangles, two colours and the normal, in one allocation
+        RCP_TRY(dalloc(&s->tris, 12 * (size_t)n));
+        s->shade = s->tris + 9 * (size_t)n;
+        s->normals = s->tris + 11 * (size_t)n;
         ShadeParams sp{{desc->light_dir[0], desc->light_dir[1], desc->light_dir[2]}, desc->k_a, desc->k_d};
         hipLaunchKernelGGL(k_pack_tris, dim3(blocks(n)), dim3(kB), 0, stream, n, (const float*)d_verts,
                            (const uint32_t*)d_idx, (const float*)d_rgb, (const uint32_t*)sorted, sp, s->tris,

@@ -250,8 +250,8 @@ struct rcp_scene {
     rcp::DevScene dev{};
     float4* nodes = nullptr;
     float4* tris = nullptr;
-    float4* shade = nullptr;
-    float4* normals = nullptr;
+    float4* shade = nullptr;     // within the allocation of tris
+    float4* normals = nullptr;   // too
     rcp_scene_stats stats{};
     uint32_t top_nodes[rcp::kTopLevels + 1] = {};   // nodes in the tree's first L levels, L = 0..kTopLevels
     uint32_t* err_host = nullptr;   // pinned, device-mapped error flag (DevScene::err_flag)
