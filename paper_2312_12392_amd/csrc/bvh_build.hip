@@ -1492,6 +1492,7 @@ rcp_status ploc_build(int n, const float4* tlo, const float4* thi, uint32_t*& so
     RoundState fin{};
     RCP_HIP(hipMemcpyAsync(&fin, rs + round, sizeof(fin), hipMemcpyDeviceToHost, stream));
     RCP_HIP(hipStreamSynchronize(stream));
+    if (fin.m > 1) return RCP_ERR_NOT_READY;
     if (fin.m != 1 || fin.next_id != -1) {
         set_error("PLOC ended with %d clusters of %d and made %d inner nodes of %d", fin.m, m, n - 2 - fin.next_id, n - 1);
         return RCP_ERR_INTERNAL;

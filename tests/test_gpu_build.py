@@ -1,6 +1,6 @@
 """GPU tests of the scene build where its launches change: cluster counts
 around the merge kernels' tiles and around the size that one workgroup
-finishes, and inputs that only the device has looked at."""
+finishes, deep trees, and inputs that only the device has looked at."""
 import numpy as np
 import pytest
 
@@ -17,8 +17,17 @@ def say(*a):
     print("[case]", *a, flush=True)
 
 
+def chain_of_sizes(n):
+    """Triangles whose size and distance grow geometrically: a deep tree."""
+    k = np.arange(n, dtype=np.float64)[:, None, None] * (60.0 / n)
+    tri = np.array([[[0.0, 0.0, 0.0], [1.0, 0.1, 0.0], [0.1, 1.0, 0.3]]])
+    v = (2.0 ** (k - 60.0) * (1.0 + 0.05 * tri)).reshape(-1, 3).astype(np.float32)
+    return scenegen.Scene(verts=v, idx=np.arange(3 * n, dtype=np.uint32).reshape(-1, 3),
+                          rgb=np.full((n, 3), 0.5, np.float32))
+
+
 @pytest.mark.parametrize("n", [2, 5, 1023, 1024, 1025, 2048, 2049, 4095, 20481])
-@pytest.mark.parametrize("make", [lambda n: scenegen.soup_scene(3, n)], ids=["soup"])
+@pytest.mark.parametrize("make", [lambda n: scenegen.soup_scene(3, n), chain_of_sizes], ids=["soup", "deep"])
 @pytest.mark.parametrize("builder", [rcp.RCP_BUILDER_PLOC, rcp.RCP_BUILDER_LBVH], ids=["ploc", "lbvh"])
 @pytest.mark.parametrize("collapse", [rcp.RCP_COLLAPSE_SAH, rcp.RCP_COLLAPSE_GREEDY], ids=["sah", "greedy"])
 def test_build_sizes(n, make, builder, collapse):
