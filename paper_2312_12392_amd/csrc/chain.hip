@@ -126,7 +126,7 @@ constexpr uint32_t kDrainedRound = 8;
 // vector-memory path, which the traversal keeps busy.
 typedef __attribute__((address_space(4))) ViewDev ConstView;
 
-template <bool STATS, int MODE, bool ONE, bool ENTRY, int STACK, int BLOCK>
+template <bool STATS, int MODE, bool ONE, bool ENTRY, int STACK, int BLOCK, bool PAIR>
 __device__ inline void chain_body(const ChainArgs& a) {
     constexpr bool AUX = MODE != RCP_MODE_COLOR;
     // LDS: the waves' entry lists, or the staged top levels (128-byte nodes, as
@@ -457,7 +457,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
             // until the next setup round can start
             const uint32_t dead = popc_u32(wave_ballot(!alive));
             const uint32_t enough = drained && cur == end ? (dead + kDrainedRound < 64u ? dead + kDrainedRound : 64u) : (uint32_t)a.refill_min;
-            trav_queue<true>(tv, a.sc, st, wave_lds, a.exit_lanes, enough);
+            trav_queue<true, PAIR>(tv, a.sc, st, wave_lds, a.exit_lanes, enough);
         } else if (alive && tv.node != -1) {
             trav_step<STATS, false>(tv, a.sc, st, a.exit_lanes, cnt);
         }
@@ -482,14 +482,17 @@ __device__ inline void chain_body(const ChainArgs& a) {
 // and BLOCK (workgroup size) are launch parameters the autotuner chooses
 // among for the colour mode's timed kernel; the instrumented kernel and the
 // depth and normal modes use kStack and kBlock.
-template <bool STATS, bool ONE, bool ENTRY, int STACK, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void k_chain(ChainArgs a) {
-    chain_body<STATS, RCP_MODE_COLOR, ONE, ENTRY, STACK, BLOCK>(a);
+// PAIR (the launches that few_pixels names): the leaves' triangles are read in
+// pairs, which a chain waits for once instead of twice, and a wave fewer per
+// SIMD makes room for them.
+template <bool STATS, bool ONE, bool ENTRY, int STACK, int BLOCK, bool PAIR>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PAIR ? 5 : 6))) void k_chain(ChainArgs a) {
+    chain_body<STATS, RCP_MODE_COLOR, ONE, ENTRY, STACK, BLOCK, PAIR>(a);
 }
 
-template <bool STATS, int MODE, bool ONE, bool ENTRY>
+template <bool STATS, int MODE, bool ONE, bool ENTRY, bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_chain_aux(ChainArgs a) {
-    chain_body<STATS, MODE, ONE, ENTRY, ENTRY ? kEntryStack : kStack, kBlock>(a);
+    chain_body<STATS, MODE, ONE, ENTRY, ENTRY ? kEntryStack : kStack, kBlock, PAIR>(a);
 }
 
 // ---- Small scenes: every triangle tested ----------------------------------------
@@ -1007,29 +1010,25 @@ template <bool STATS, bool ONE, bool ENTRY>
 ChainKernel colour_kernel(int stack, int block) {
     constexpr int D = ENTRY ? kEntryStack : kStack;
     if constexpr (!STATS) {
-        if (stack == 8 && block == 512) return {(const void*)k_chain<false, ONE, ENTRY, 8, 512>, 512, 8, ENTRY};
-        if (stack == 8) return {(const void*)k_chain<false, ONE, ENTRY, 8, kBlock>, kBlock, 8, ENTRY};
-        if (block == 512) return {(const void*)k_chain<false, ONE, ENTRY, D, 512>, 512, D, ENTRY};
+        if (stack == 8 && block == 512) return {(const void*)k_chain<false, ONE, ENTRY, 8, 512, false>, 512, 8, ENTRY};
+        if (stack == 8) return {(const void*)k_chain<false, ONE, ENTRY, 8, kBlock, false>, kBlock, 8, ENTRY};
+        if (block == 512) return {(const void*)k_chain<false, ONE, ENTRY, D, 512, false>, 512, D, ENTRY};
     }
-    return {(const void*)k_chain<STATS, ONE, ENTRY, D, kBlock>, kBlock, D, ENTRY};
+    return {(const void*)k_chain<STATS, ONE, ENTRY, D, kBlock, false>, kBlock, D, ENTRY};
+}
+
+template <bool STATS, int MODE, bool ONE, bool ENTRY, bool PAIR>
+ChainKernel aux_kernel() {
+    return {(const void*)k_chain_aux<STATS, MODE, ONE, ENTRY, PAIR>, kBlock, ENTRY ? kEntryStack : kStack, ENTRY};
 }
 
 template <bool STATS, bool ONE, bool ENTRY>
 ChainKernel chain_kernel2(int mode, const Launch& lp) {
     switch (mode) {
-        case RCP_MODE_DEPTH:
-            return {(const void*)k_chain_aux<STATS, RCP_MODE_DEPTH, ONE, ENTRY>, kBlock, ENTRY ? kEntryStack : kStack,
-                    ENTRY};
-        case RCP_MODE_NORMAL:
-            return {(const void*)k_chain_aux<STATS, RCP_MODE_NORMAL, ONE, ENTRY>, kBlock, ENTRY ? kEntryStack : kStack,
-                    ENTRY};
+        case RCP_MODE_DEPTH: return aux_kernel<STATS, RCP_MODE_DEPTH, ONE, ENTRY, false>();
+        case RCP_MODE_NORMAL: return aux_kernel<STATS, RCP_MODE_NORMAL, ONE, ENTRY, false>();
         default: return colour_kernel<STATS, ONE, ENTRY>(lp.stack, lp.block);
     }
-}
-
-template <bool STATS, bool ONE>
-ChainKernel chain_kernel1(int mode, const Launch& lp, bool entry) {
-    return entry ? chain_kernel2<STATS, ONE, true>(mode, lp) : chain_kernel2<STATS, ONE, false>(mode, lp);
 }
 
 // The kernel of a launch over n_views views in `mode` (the single-view
@@ -1039,8 +1038,29 @@ ChainKernel chain_kernel(bool stats, int n_views, int mode, const Launch& lp, bo
     // those of the tree, the same in both engines.
     if (stats)
         return n_views == 1 ? chain_kernel2<true, true, false>(mode, lp) : chain_kernel2<true, false, false>(mode, lp);
-    return n_views == 1 ? chain_kernel1<false, true>(mode, lp, entry) : chain_kernel1<false, false>(mode, lp, entry);
+    if (entry) return n_views == 1 ? chain_kernel2<false, true, true>(mode, lp) : chain_kernel2<false, false, true>(mode, lp);
+    return n_views == 1 ? chain_kernel2<false, true, false>(mode, lp) : chain_kernel2<false, false, false>(mode, lp);
 }
+
+// The kernel that reads triangles in pairs, in place of one with entry lists
+// in workgroups of kBlock.
+template <bool ONE>
+ChainKernel pair_kernel(int mode) {
+    switch (mode) {
+        case RCP_MODE_DEPTH: return aux_kernel<false, RCP_MODE_DEPTH, ONE, true, true>();
+        case RCP_MODE_NORMAL: return aux_kernel<false, RCP_MODE_NORMAL, ONE, true, true>();
+        default: return {(const void*)k_chain<false, ONE, true, kEntryStack, kBlock, true>, kBlock, kEntryStack, true};
+    }
+}
+
+// A launch whose time is that of its longest chains rather than of its work:
+// up to four pixels per lane that the default kernel keeps resident (1.6M
+// pixels in the colour mode, 1.3M in the others).  (1M-triangle terrain, K = 6,
+// ms without / with pairs: colour 400 x 225 0.53 / 0.49, 640 x 360 0.60 / 0.55,
+// 1440 x 810 0.84 / 0.78, 1600 x 900 0.88 / 0.87, 1920 x 1080 1.06 / 1.06, 3840 x
+// 2160 K = 8 on 16M triangles 5.67 / 5.83; normal 560 x 315 0.62 / 0.58, 1440 x 810
+// 0.81 / 0.78, 1600 x 900 0.87 / 0.90, 1920 x 1080 1.07 / 1.10.)
+bool few_pixels(uint64_t items, uint32_t threads) { return items <= 4u * (uint64_t)threads; }
 
 // LDS of a workgroup: the waves' entry lists or the staged top levels, the
 // stack area and the view starts (and the stats).
@@ -1090,8 +1110,8 @@ struct ChainGrid {
     uint32_t threads() const { return (uint32_t)blocks * (uint32_t)k.block; }
 };
 
-rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool entry, ChainGrid& g) {
-    g.k = chain_kernel(stats, n_views, mode, lp, entry);
+// Workgroups of kernel g.k that stay resident.
+rcp_status resident_grid(const Launch& lp, bool stats, int n_views, ChainGrid& g) {
     g.smem = chain_smem(lp, g.k, stats, n_views);
     int per_cu = 0, cus = 0;
     const rcp_status st = resident_blocks(g.k.fn, g.k.block, g.smem, per_cu, cus);
@@ -1104,6 +1124,22 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
         if (cap < per_cu) per_cu = cap;
     }
     g.blocks = per_cu * cus;
+    return RCP_OK;
+}
+
+// The grid of a launch over `items` pixels (with their tiles' padding).  It
+// needs no more overflow area than one of more items: the kernel for few keeps
+// as many stack entries per lane, and no more lanes.
+rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool entry, uint64_t items, ChainGrid& g) {
+    g.k = chain_kernel(stats, n_views, mode, lp, entry);
+    RCP_TRY_STATUS(resident_grid(lp, stats, n_views, g));
+    if (!stats && entry && g.k.block == kBlock && g.k.stack == kEntryStack && few_pixels(items, g.threads())) {
+        ChainGrid p;
+        p.k = n_views == 1 ? pair_kernel<true>(mode) : pair_kernel<false>(mode);
+        RCP_TRY_STATUS(resident_grid(lp, stats, n_views, p));
+        p.blocks = std::min(p.blocks, g.blocks);
+        g = p;
+    }
     return RCP_OK;
 }
 
@@ -1200,10 +1236,12 @@ uint64_t view_items(const ViewDev& v) {
     return view_tile_items(v.W, v.H, v.tile_log2w, v.super_log2);
 }
 
-// Entries of a view's score and order buffer: two per tile.
-size_t order_entries(int W, int H, int tile_log2w) {
-    return 2 * (size_t)(view_tile_items(W, H, tile_log2w, super_log2_for(W, H, tile_log2w)) >> 6);
+uint64_t frame_items(int W, int H, int tile_log2w) {
+    return view_tile_items(W, H, tile_log2w, super_log2_for(W, H, tile_log2w));
 }
+
+// Entries of a view's score and order buffer: two per tile.
+size_t order_entries(int W, int H, int tile_log2w) { return 2 * (size_t)(frame_items(W, H, tile_log2w) >> 6); }
 
 }  // namespace
 
@@ -1212,7 +1250,7 @@ rcp_status prepare_chain(rcp_scene* s, Workspace& ws, int W, int H, int mode, hi
     size_t need = 0;
     for (const auto& [stats, entry] : {std::pair(false, false), std::pair(false, true), std::pair(true, false)}) {
         ChainGrid g;
-        RCP_TRY_STATUS(chain_grid(lp, stats, 1, mode, entry, g));
+        RCP_TRY_STATUS(chain_grid(lp, stats, 1, mode, entry, ~0ull, g));
         need = std::max(need, spill_depth_of(s, g.k) * g.threads());
     }
     rcp_status st = ensure_workspace(s, ws, 0, 0, need, stream);
@@ -1344,7 +1382,8 @@ rcp_status render_chain(rcp_scene* s, Workspace& w, const Camera& cam, int W, in
     rcp_status st = ensure_tiles(w, order_entries(W, H, lp.tile_log2w), n_entries, stream);
     if (st != RCP_OK) return st;
     ChainGrid g;
-    st = chain_grid(lp, stats, 1, disp.mode, !stats && entries_fit(s, w.entries, w.entry_cap, n_entries), g);
+    st = chain_grid(lp, stats, 1, disp.mode, !stats && entries_fit(s, w.entries, w.entry_cap, n_entries),
+                    frame_items(W, H, lp.tile_log2w), g);
     if (st != RCP_OK) return st;
     st = ensure_workspace(s, w, 0, 0, spill_depth_of(s, g.k) * g.threads(), stream);
     if (st != RCP_OK) return st;
@@ -1382,7 +1421,7 @@ rcp_status render_chain_fixed(rcp_scene* s, Workspace& w, const Camera& cam, int
             w.spill = (int32_t*)w.entries;
             w.spill_cap += w.entry_cap * (sizeof(float4) / sizeof(int32_t));
         }
-        RCP_TRY_STATUS(chain_grid(lp, false, 1, disp.mode, entry, g));
+        RCP_TRY_STATUS(chain_grid(lp, false, 1, disp.mode, entry, frame_items(W, H, lp.tile_log2w), g));
         per_block = spill_depth_of(s, g.k) * (size_t)g.k.block;
         fit = w.spill_cap / per_block;
         if (entry && fit * g.k.block >= 4 * (size_t)cus * kBlock) break;
@@ -1428,7 +1467,7 @@ rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views
         for (int nv : {1, 2})
             for (const bool entry : {false, true}) {
                 ChainGrid g;
-                RCP_TRY_STATUS(chain_grid(lp, false, nv, mode, entry, g));
+                RCP_TRY_STATUS(chain_grid(lp, false, nv, mode, entry, ~0ull, g));
                 spill_need = std::max(spill_need, spill_depth_of(s, g.k) * g.threads());
             }
     rcp_status st = RCP_OK;
@@ -1524,7 +1563,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     size_t spill_need = 0;
     std::vector<ChainGrid> grids(groups.size());
     for (size_t g = 0; g < groups.size(); ++g) {
-        rcp_status st = chain_grid(lp, false, groups[g].count, groups[g].mode, entry, grids[g]);
+        rcp_status st = chain_grid(lp, false, groups[g].count, groups[g].mode, entry, groups[g].items, grids[g]);
         if (st != RCP_OK) return st;
         spill_need = std::max(spill_need, spill_depth_of(s, grids[g].k) * grids[g].threads());
     }

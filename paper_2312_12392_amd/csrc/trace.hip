@@ -190,7 +190,8 @@ __global__ __launch_bounds__(kBlock) void k_pass(PassArgs a) {
         if (STATS) {
             if (alive && tv.node != -1) trav_step<true, false>(tv, a.sc, st, a.exit_lanes, cnt);
         } else {
-            trav_queue<false>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : (uint32_t)a.refill_min);
+            // (leaves' triangles in pairs: 356 -> 346 us for a 1920 x 1080 pass)
+            trav_queue<false, true>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : (uint32_t)a.refill_min);
         }
 
         // ---- finished rays: shade, write, compact ----------------------------
@@ -399,7 +400,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) voi
             if (drained) break;
             continue;
         }
-        trav_queue<false>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : a.refill_min);
+        // (leaves' triangles one at a time: in pairs 1M scattered rays take 1% longer)
+        trav_queue<false, false>(tv, a.sc, st, wave_lds, a.exit_lanes, drained ? 64u : a.refill_min);
         if (alive && tv.node == -1) {
             alive = false;
             ended = true;

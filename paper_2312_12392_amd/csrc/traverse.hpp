@@ -700,6 +700,11 @@ __device__ inline void recorded_hit(Hit& h, uint32_t wave) {
 }
 
 // Test the newest n (<= 64) queued leaves, one per lane; the whole wave.
+// PAIR: two triangles of a leaf are read at a time (most leaves hold two), one
+// trip to memory instead of two, for ten registers more; see the kernels.
+// (Queueing the triangles instead, one per lane, reads the rays' records twice
+// as often: 4-13% slower.)
+template <bool PAIR>
 __device__ inline void test_leaves(const DevScene& sc, uint32_t wave, uint32_t first, uint32_t n) {
     const uint32_t l = threadIdx.x & 63u;
     unsigned long long mine = ~0ull;
@@ -719,16 +724,41 @@ __device__ inline void test_leaves(const DevScene& sc, uint32_t wave, uint32_t f
         r.tri_base = base & 0x7FFFFFFFu;
         r.swap = (base >> 31) != 0u;
         const uint32_t tri = (link >> 3) & 0x0FFFFFFFu, count = (link & 7u) + 1u;
-        for (uint32_t j = 0; j < count; ++j) {
-            const float4* tp = sc.tris + 3 * (size_t)(r.tri_base + tri + j);
-            const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
-            float t;
-            bool front;
-            if (hit_triangle(r, v0, v1, v2, t, front)) {
-                const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | __float_as_uint(v0.w);
-                if (key < mine) {
-                    mine = key;
-                    slot = (tri + j) | (front ? 0x80000000u : 0u);
+        if constexpr (PAIR) {
+            const auto test = [&](const float4& v0, const float4& v1, const float4& v2, uint32_t j) {
+                float t;
+                bool front;
+                if (hit_triangle(r, v0, v1, v2, t, front)) {
+                    const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | __float_as_uint(v0.w);
+                    if (key < mine) {
+                        mine = key;
+                        slot = (tri + j) | (front ? 0x80000000u : 0u);
+                    }
+                }
+            };
+            for (uint32_t j = 0; j < count; j += 2) {
+                const float4* tp = sc.tris + 3 * (size_t)(r.tri_base + tri + j);
+                const float4* tq = tp + (j + 1u < count ? 3 : 0);
+                const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+                const float4 w0 = tq[0], w1 = tq[1], w2 = tq[2];
+                __asm__ volatile("" ::: "memory");   // (both are read before the first test)
+                test(v0, v1, v2, j);
+                if (j + 1u < count) test(w0, w1, w2, j + 1u);
+            }
+        } else {
+            // (written out: with the lambda the compiler spilled more and whole
+            // frames took 6-12% longer)
+            for (uint32_t j = 0; j < count; ++j) {
+                const float4* tp = sc.tris + 3 * (size_t)(r.tri_base + tri + j);
+                const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+                float t;
+                bool front;
+                if (hit_triangle(r, v0, v1, v2, t, front)) {
+                    const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | __float_as_uint(v0.w);
+                    if (key < mine) {
+                        mine = key;
+                        slot = (tri + j) | (front ? 0x80000000u : 0u);
+                    }
                 }
             }
         }
@@ -750,8 +780,8 @@ __device__ inline void test_leaves(const DevScene& sc, uint32_t wave, uint32_t f
 // leaves would let the rays go on past hits that end them).
 // The whole wave calls this; lanes without a ray have tv.node == -1.
 // ENTRY: rays may have entry lists; otherwise the tree's first sc.top_count
-// nodes are read from LDS.
-template <bool ENTRY, class Stack>
+// nodes are read from LDS.  PAIR: see test_leaves.
+template <bool ENTRY, bool PAIR, class Stack>
 __device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint32_t wave, uint32_t exit_lanes,
                                   uint32_t enough) {
     TravCount cnt;
@@ -778,7 +808,7 @@ __device__ inline void trav_queue(Trav& tv, const DevScene& sc, Stack& st, uint3
                 const uint32_t n = waiting < 64u ? waiting : 64u;
                 waiting -= n;
                 wave_lds_fence();
-                test_leaves(sc, wave, waiting, n);
+                test_leaves<PAIR>(sc, wave, waiting, n);
             } while (stop && waiting != 0u);
             tv.lim = lds_get_f(wave + kRecKey + 8u * l + 4u) * kSlack;
         }

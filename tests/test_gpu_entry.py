@@ -101,3 +101,32 @@ def test_repeating_chains(K, with_ids):
     if K >= 5:   # the case is there: pixels that come back after two passes without having settled
         assert np.any(np.any(a[2] != a[3], axis=-1) & np.all(a[2] == a[4], axis=-1))
     s.close()
+
+
+@pytest.mark.parametrize("max_leaf", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("mode", [rcp.RCP_MODE_COLOR, rcp.RCP_MODE_DEPTH, rcp.RCP_MODE_NORMAL])
+def test_leaves_of_all_sizes_in_pairs(max_leaf, mode):
+    """Leaves of odd and even counts where their triangles are read two at a
+    time (tests made cheap against nodes, so that leaves fill)."""
+    say("pairs", max_leaf, mode)
+    sc = scenegen.terrain_patch(seed=29, cells=60, n_boxes=40)
+    assert sc.n_tris > 5000
+    s = rcp.Scene(sc, rcp.build_options(max_leaf=max_leaf, c_isect=0.05))
+    assert s.info()["leaf_hist"][max_leaf - 1] > 0
+    cam = patch_camera((0.2, 0.5, -1.1))
+    W, H, K = 121, 67, 4
+    img, ids = both_engines(s, cam, W, H, K, 0.01, 0.05, mode, 0.9)
+    o_img, o_ids = oracle.OracleScene(sc, use_bvh=True).render(cam, W, H, K, 0.01, 0.05, mode=mode, z0=0.9)
+    assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
+
+
+# whole tiles around four pixels per resident lane, in the colour mode at six
+# waves per SIMD of 256 compute units and in the others at five
+@pytest.mark.parametrize("W", [1536, 1544])
+@pytest.mark.parametrize("H,mode", [(1024, rcp.RCP_MODE_COLOR), (848, rcp.RCP_MODE_NORMAL), (856, rcp.RCP_MODE_DEPTH)])
+def test_engines_agree_around_the_limit_of_few_pixels(W, H, mode):
+    say("few pixels", W, H, mode)
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=60, n_boxes=40))
+    both_engines(s, patch_camera((0.2, 0.5, -1.1)), W, H, 3, 0.01, 0.05, mode, 0.9)
+    s.close()
