@@ -114,7 +114,10 @@ def algorithmic_bytes(counts, engine="chain"):
 
 
 def algorithmic_ops(counts):
-    """VALU lane-operations of one frame the method needs (OPS_PER_*)."""
+    """VALU lane-operations of one frame (OPS_PER_*), counted by the instrumented
+    kernel: it starts every ray at the root and traces every changed pass.  The
+    timed kernel starts rays in entry lists and ends chains that repeat, so it
+    makes some of them unnecessary."""
     tot = counts[:, :3].astype("float64").sum(0)
     return OPS_PER_RAY * tot[0] + OPS_PER_NODE * tot[1] + OPS_PER_TRI * tot[2]
 
