@@ -1153,7 +1153,7 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
 // two handfuls.  (20,000-triangle terrain, K = 6, microseconds with 64 / the
 // choice: 64 x 64 353 / 223 with 1, 320 x 200 396 / 327 with 8, 512 x 512
 // 401 / 362 with 32; halving or doubling the choice is slower or the same.)
-void set_take(ChainArgs& a, const ChainGrid& g) {
+void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g) {
     const uint64_t waves = (uint64_t)g.threads() / 64u;
     a.take = 1u;
     while (a.take < 64u && (uint64_t)a.n_items > 2u * waves * a.take) a.take *= 2u;
@@ -1164,7 +1164,11 @@ void set_take(ChainArgs& a, const ChainGrid& g) {
     // per lane 1.69 / 1.53; 3840 x 2160, K = 8, 21 per lane 4.33 / 3.38; 4 mixed
     // views, 6 per lane 1.39 / 1.35.  Pieces of 8, 16 or 32 pixels gain nothing:
     // the tiles then lie across waves as much as with exact counts.)
-    a.whole = a.n_items >= 7u * (uint64_t)g.threads();
+    // Not where rays visit many nodes on each level of the tree: the fetches are
+    // then a small part, and what a wave keeps is long work (3840 x 2160, K = 3,
+    // exact / whole: soups of 635 triangles, 68 of SAH cost per level, 1.64 / 1.87,
+    // of 2500 4.41 / 5.40; a terrain of 20,000 1.00 / 0.83; terrains have 1 to 10).
+    a.whole = a.n_items >= 7u * (uint64_t)g.threads() && s->stats.sah_cost <= 20.0f * (float)s->dev.max_depth;
     // the refill threshold in idle lanes, in proportion
     a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
 }
@@ -1302,7 +1306,7 @@ rcp_status launch_one_view(rcp_scene* s, Workspace& w, const Launch& lp, const C
     a.n_items = (uint32_t)view_items(view);
     a.fetch = w.counters;
     a.refill_min = lp.refill_min;
-    set_take(a, g);
+    set_take(s, a, g);
     a.exit_lanes = (uint32_t)lp.exit_lanes;
     a.spill = w.spill;
     a.spill_stride = g.threads();
@@ -1646,7 +1650,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         a.n_items = groups[g].items;
         a.fetch = ws.fetch + kFetchWords * g;
         a.refill_min = lpr.refill_min;
-        set_take(a, grids[g]);
+        set_take(s, a, grids[g]);
         a.exit_lanes = (uint32_t)lpr.exit_lanes;
         a.spill = ws.spill;
         a.spill_stride = grids[g].threads();
