@@ -130,3 +130,15 @@ def test_engines_agree_around_the_limit_of_few_pixels(W, H, mode):
     s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=60, n_boxes=40))
     both_engines(s, patch_camera((0.2, 0.5, -1.1)), W, H, 3, 0.01, 0.05, mode, 0.9)
     s.close()
+
+
+# seven pixels per resident lane are 2.75M (colour mode): from there on a wave
+# takes whole tiles, where the tree's SAH cost is at most 20 per level
+@pytest.mark.parametrize("W,H", [(1601, 1701), (1703, 1699)])
+@pytest.mark.parametrize("scene,few_visits", [("terrain", True), ("soup", False)])
+def test_engines_agree_around_the_limit_of_whole_tiles(W, H, scene, few_visits):
+    say("whole tiles", W, H, scene)
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=60, n_boxes=40) if few_visits else scenegen.soup_scene(4, 700))
+    assert (s.info()["sah_cost"] <= 20.0 * s.info()["max_depth"]) == few_visits
+    both_engines(s, patch_camera((0.2, 0.5, -1.1)), W, H, 2, 0.0, 0.05)
+    s.close()
