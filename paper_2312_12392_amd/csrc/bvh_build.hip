@@ -910,45 +910,52 @@ __global__ void k_pack_single(int n, const float4* __restrict__ tlo, const float
 // level from one counter.
 // ---------------------------------------------------------------------------
 // Statistics of the emitted wide tree, accumulated exactly: leaf links, the
-// SAH cost relative to the root box in 2^-32 fixed point, and the leaves by
-// their triangle count (hist[c - 1] leaves of c triangles).
+// SAH cost relative to the root box in 2^-32 fixed point, the same with all
+// costs 1 (the work of a ray in nodes and triangles, whatever units the caller's
+// costs are in), and the leaves by their triangle count (hist[c - 1] leaves of
+// c triangles).
 struct WideStats {
     unsigned long long leaves;
     unsigned long long sah_fx;
+    unsigned long long work_fx;
     unsigned long long hist[8];
 };
 
 // A thread's share of them; leaf_sizes: a node's leaves by size in 4-bit
 // fields (field c counts the leaves of c + 1 triangles; a node has at most 4).
 struct WideAcc {
-    unsigned long long sah_fx = 0;
+    unsigned long long sah_fx = 0, work_fx = 0;
     uint32_t leaves = 0;
     uint32_t hist[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    __device__ inline void add(float node_area, float leaf_cost, uint32_t n_leaves, uint32_t leaf_sizes, float c_trav,
-                               float inv_root_area) {
+    __device__ inline void add(float node_area, float leaf_cost, float leaf_work, uint32_t n_leaves, uint32_t leaf_sizes,
+                               float c_trav, float inv_root_area) {
         const float rel = (c_trav * node_area + leaf_cost) * inv_root_area;
         sah_fx += (unsigned long long)((double)rel * 4294967296.0 + 0.5);
+        // (no node's share is above 1 + 4 leaves of 8 triangles; areas that
+        // overflowed must not leave the fixed point's range)
+        const float work = fminf((node_area + leaf_work) * inv_root_area, 64.0f);
+        work_fx += (unsigned long long)((double)work * 4294967296.0 + 0.5);
         leaves += n_leaves;
 #pragma unroll
         for (int c = 0; c < 8; ++c) hist[c] += (leaf_sizes >> (4 * c)) & 15u;
     }
-    // All threads of the workgroup: summed in LDS, ten memory atomics a
+    // All threads of the workgroup: summed in LDS, eleven memory atomics a
     // workgroup (ten a wave were half of an emission launch).
     __device__ inline void flush(WideStats* ws) const {
-        __shared__ unsigned long long sum[10];
-        if (threadIdx.x < 10) sum[threadIdx.x] = 0;
+        constexpr int N = sizeof(WideStats) / sizeof(unsigned long long);
+        __shared__ unsigned long long sum[N];
+        if (threadIdx.x < N) sum[threadIdx.x] = 0;
         __syncthreads();
-        if (leaves | (uint32_t)(sah_fx != 0)) {
+        if (leaves | (uint32_t)((sah_fx | work_fx) != 0)) {
             atomicAdd(&sum[0], (unsigned long long)leaves);
             atomicAdd(&sum[1], sah_fx);
+            atomicAdd(&sum[2], work_fx);
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                if (hist[c]) atomicAdd(&sum[2 + c], (unsigned long long)hist[c]);
+                if (hist[c]) atomicAdd(&sum[3 + c], (unsigned long long)hist[c]);
         }
         __syncthreads();
-        if (threadIdx.x < 10 && sum[threadIdx.x])
-            atomicAdd(threadIdx.x == 0 ? &ws->leaves : threadIdx.x == 1 ? &ws->sah_fx : &ws->hist[threadIdx.x - 2],
-                      sum[threadIdx.x]);
+        if (threadIdx.x < N && sum[threadIdx.x]) atomicAdd((unsigned long long*)ws + threadIdx.x, sum[threadIdx.x]);
     }
 };
 
@@ -1043,17 +1050,19 @@ __device__ inline void collapse4_node(const float4* __restrict__ n2, uint32_t sl
                        __uint_as_float(link[3]));
     o[7] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     WideCand u = c[0];
-    float leaf_cost = 0.0f;
+    float leaf_cost = 0.0f, leaf_work = 0.0f;
     uint32_t n_leaves = 0, leaf_sizes = 0;
     for (int i = 0; i < m; ++i) {
         for (int a = 0; a < 3; ++a) { u.lo[a] = fminf(u.lo[a], c[i].lo[a]); u.hi[a] = fmaxf(u.hi[a], c[i].hi[a]); }
         if (c[i].link & kLeafBit) {
-            leaf_cost += (c_isect * (float)((c[i].link & 7u) + 1u) + kLeafEntry * c_trav) * c[i].area;
+            const float tests = (float)((c[i].link & 7u) + 1u);
+            leaf_cost += (c_isect * tests + kLeafEntry * c_trav) * c[i].area;
+            leaf_work += (tests + kLeafEntry) * c[i].area;
             ++n_leaves;
             leaf_sizes += 1u << (4u * (c[i].link & 7u));
         }
     }
-    acc.add(half_area(u), leaf_cost, n_leaves, leaf_sizes, c_trav, inv_root_area);
+    acc.add(half_area(u), leaf_cost, leaf_work, n_leaves, leaf_sizes, c_trav, inv_root_area);
 }
 
 __global__ __launch_bounds__(kB) void k_collapse4(const float4* __restrict__ n2, uint32_t cap, uint32_t level,
@@ -1160,7 +1169,7 @@ __device__ inline void emit4_node(const BinTree& t, uint32_t slot, uint32_t end,
     uint32_t link[4];
     int32_t inner[4];
     int m = 0;
-    float leaf_cost = 0.0f;
+    float leaf_cost = 0.0f, leaf_work = 0.0f;
     uint32_t n_leaves = 0, leaf_sizes = 0;
     for (int guard = 0; sp > 0 && guard < 256; ++guard) {
         const int32_t c = wn[--sp];
@@ -1196,8 +1205,9 @@ __device__ inline void emit4_node(const BinTree& t, uint32_t slot, uint32_t end,
         }
         if (inner[m] < 0) {
             const uint32_t cnt = (link[m] & 7u) + 1u;
-            leaf_cost += (c_isect * (float)cnt + kLeafEntry * c_trav) *
-                         half_area(make_float3(a.x, a.y, a.z), make_float3(b.x, b.y, b.z));
+            const float area = half_area(make_float3(a.x, a.y, a.z), make_float3(b.x, b.y, b.z));
+            leaf_cost += (c_isect * (float)cnt + kLeafEntry * c_trav) * area;
+            leaf_work += ((float)cnt + kLeafEntry) * area;
             ++n_leaves;
             leaf_sizes += 1u << (4u * (cnt - 1u));
         }
@@ -1233,8 +1243,8 @@ __device__ inline void emit4_node(const BinTree& t, uint32_t slot, uint32_t end,
                        __uint_as_float(link[3]));
     o[7] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const float4 xa = nd.lo[x], xb = nd.hi[x];
-    acc.add(half_area(make_float3(xa.x, xa.y, xa.z), make_float3(xb.x, xb.y, xb.z)), leaf_cost, n_leaves, leaf_sizes,
-            c_trav, inv_root_area);
+    acc.add(half_area(make_float3(xa.x, xa.y, xa.z), make_float3(xb.x, xb.y, xb.z)), leaf_cost, leaf_work,
+            n_leaves, leaf_sizes, c_trav, inv_root_area);
 }
 
 // One level of the optimal collapse: slot s expands binary node src[s].
@@ -1811,8 +1821,12 @@ rcp_status build_scene(const rcp_scene_desc* desc, const rcp_build_options* opts
             RCP_HIP(hipStreamSynchronize(stream));
             n_leaves = (uint32_t)hst.leaves;
             sah = (float)((double)hst.sah_fx / 4294967296.0);
+            s->ray_work = (float)((double)hst.work_fx / 4294967296.0);
             for (int c = 0; c < 8; ++c) s->stats.leaf_hist[c] = (uint32_t)hst.hist[c];
-            if (single) sah = c_isect * (float)n;   // one leaf of every triangle, relative to its own box
+            if (single) {   // one leaf of every triangle, relative to its own box
+                sah = c_isect * (float)n;
+                s->ray_work = (float)n;
+            }
         }
         // three rotated copies of the triangles, two colours and the normal, in one allocation
         RCP_TRY(dalloc(&s->tris, 12 * (size_t)n));

@@ -1166,9 +1166,9 @@ void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g) {
     // the tiles then lie across waves as much as with exact counts.)
     // Not where rays visit many nodes on each level of the tree: the fetches are
     // then a small part, and what a wave keeps is long work (3840 x 2160, K = 3,
-    // exact / whole: soups of 635 triangles, 68 of SAH cost per level, 1.64 / 1.87,
+    // exact / whole: soups of 635 triangles, 68 of ray_work per level, 1.64 / 1.87,
     // of 2500 4.41 / 5.40; a terrain of 20,000 1.00 / 0.83; terrains have 1 to 10).
-    a.whole = a.n_items >= 7u * (uint64_t)g.threads() && s->stats.sah_cost <= 20.0f * (float)s->dev.max_depth;
+    a.whole = a.n_items >= 7u * (uint64_t)g.threads() && s->ray_work <= 20.0f * (float)s->dev.max_depth;
     // the refill threshold in idle lanes, in proportion
     a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
 }
@@ -1340,25 +1340,26 @@ void launch_direct_mode(const rcp_scene* s, const ViewDev& v, int lanes, hipStre
 // Lanes per pixel of the direct kernel, or 0 where the tree is faster.
 //
 // Its time is that of the pixels times triangles it tests; the tree's is a
-// chain of dependent loads per pass, the longer the higher the tree's SAH cost
-// (expected visits and tests per ray): 10-20 for a terrain of any size, about
-// three quarters of the triangle count for a soup of large triangles.  K = 6,
+// chain of dependent loads per pass, the longer the more nodes and triangles a
+// ray is expected to visit (ray_work, the SAH cost with all costs 1): 10-20 for
+// a terrain of up to 100,000 triangles, about three quarters of the triangle
+// count for a soup of large triangles.  K = 6,
 // microseconds, direct / tree:
-//   terrain, 1024 triangles (SAH cost 12): 64 x 64 42 / 190, 128 x 128 99 / 200,
+//   terrain, 1024 triangles (ray_work 12): 64 x 64 42 / 190, 128 x 128 99 / 200,
 //     320 x 200 246 / 200; 4096 triangles: 64 x 64 130 / 210, 128 x 128 375 / 230;
 //     256 triangles: 320 x 200 85 / 190, 640 x 400 224 / 190
 //   soup, 256 triangles (211): 64 x 64 21 / 733, 1280 x 720 412 / 779;
 //     2048 triangles (1547): 640 x 400 890 / 4200; 16384 (11959): 64 x 64 518 / 13700
-// so it is taken up to 20M tests per pass, or half a million per unit of SAH
-// cost, and for no more triangles than a group tests in the time the tree's
-// passes take at least (4096, or 16 per unit of SAH cost).
+// so it is taken up to 20M tests per pass, or half a million per unit of
+// ray_work, and for no more triangles than a group tests in the time the tree's
+// passes take at least (4096, or 16 per unit of ray_work).
 // 64 lanes per pixel leave few pixels per wave, which small frames want; 16
 // are faster from about 32K pixels on, 4 for large frames of few triangles
 // (128 triangles: 640 x 400 104 / 77 with 4 / 16 lanes, 1280 x 720 227 / 251).
 int direct_lanes(const rcp_scene* s, int W, int H) {
-    const double tris = s->dev.n_tris, pixels = (double)W * H, sah = s->stats.sah_cost;
-    if (tris < 1.0 || tris > std::max(4096.0, 16.0 * sah)) return 0;
-    if (pixels * tris > std::max(20e6, 0.5e6 * sah)) return 0;
+    const double tris = s->dev.n_tris, pixels = (double)W * H, work = s->ray_work;
+    if (tris < 1.0 || tris > std::max(4096.0, 16.0 * work)) return 0;
+    if (pixels * tris > std::max(20e6, 0.5e6 * work)) return 0;
     // (the test hooks reach the error paths of the traversal and its
     // workspace, which this kernel does not have)
     if (s->dev.step_budget < 5ull * s->dev.n_nodes + 16ull || alloc_hook_armed()) return 0;

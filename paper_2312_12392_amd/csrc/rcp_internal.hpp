@@ -253,6 +253,8 @@ struct rcp_scene {
     float4* shade = nullptr;     // within the allocation of tris
     float4* normals = nullptr;   // too
     rcp_scene_stats stats{};
+    float ray_work = 0.0f;       // expected node visits, triangle tests and two per leaf of a ray that meets the
+                                 // root box (the SAH cost with all costs 1), for the launch rules
     uint32_t top_nodes[rcp::kTopLevels + 1] = {};   // nodes in the tree's first L levels, L = 0..kTopLevels
     uint32_t* err_host = nullptr;   // pinned, device-mapped error flag (DevScene::err_flag)
     rcp::OccGrid occ;

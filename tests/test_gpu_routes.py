@@ -1,0 +1,58 @@
+"""GPU tests of which kernels a call launches (as the profiler names them):
+rules that choose by the scene must not depend on the units of its build's
+costs, nor reach past the sizes they were measured at."""
+import re
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+import oracle
+import scenegen
+from paper_2312_12392_amd import rcp
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+def launched(run):
+    """Names of the kernels and runtime calls that run() makes, in order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        torch.zeros(1, device="cuda")   # (seen in any case)
+        run()
+        torch.cuda.synchronize()
+    names = [e.name for e in p.events()]
+    if not any("elementwise" in n or "Fill" in n for n in names):
+        pytest.skip("the profiler reports no kernels here")
+    return [re.sub(r"^.*\(anonymous namespace\)::", "", n.split("(rcp::")[0]) if "rcp::" in n else n for n in names]
+
+
+def rendered(names):
+    """The rendering kernels among them: k_direct or k_chain."""
+    return {m.group(0) for n in names for m in [re.match(r"k_(direct|chain)", n)] if m}
+
+
+def patch_camera():
+    return scenegen.camera_look_at([0.2, 0.5, -1.1], [0, 0.05, 0], [0, 1, 0], 60.0)
+
+
+@pytest.mark.parametrize("scene,W,H", [("soup", 64, 64), ("soup", 640, 640), ("terrain", 120, 100)])
+def test_route_does_not_depend_on_the_units_of_the_costs(scene, W, H):
+    """The same tree, built with costs scaled by a power of two, takes the same
+    kernels (the tree itself depends on the costs' ratio only)."""
+    sc = scenegen.workload("soup256").scene if scene == "soup" else scenegen.terrain_patch(seed=8, cells=90, n_boxes=40)
+    routes, trees = [], []
+    for scale in (1.0, 2.0 ** -7, 2.0 ** 7):
+        say("units", scene, W, H, scale)
+        s = rcp.Scene(sc, rcp.build_options(c_trav=scale, c_isect=scale))
+        routes.append(rendered(launched(lambda: s.render(patch_camera(), W, H, 3, 0.0, 0.02))))
+        info = s.info()
+        trees.append((info["n_nodes"], info["n_leaves"], info["sah_cost"] / scale))
+        s.close()
+    assert trees[1][:2] == trees[0][:2] == trees[2][:2] and np.allclose([t[2] for t in trees], trees[0][2], rtol=1e-6)
+    assert routes[0] == routes[1] == routes[2] and len(routes[0]) == 1, routes
