@@ -513,13 +513,18 @@ __global__ __launch_bounds__(kBlock) void k_direct(DevScene sc, ViewDev v) {
     float prev[3] = {0.5f, 0.5f, 0.5f};
     float pa[4] = {INFINITY, 0.0f, 0.0f, 0.0f};
     int k = live ? 0 : v.K;    // the pixel's pass; v.K: its chain has ended
+    // a ray that tests every triangle takes as many steps as there are full
+    // leaves of them: more than its budget, and it ends as in the traversal
+    const bool spent = (sc.n_tris + (uint32_t)kMaxLeaf - 1u) / (uint32_t)kMaxLeaf > sc.step_budget;
+    if (spent && threadIdx.x == 0)
+        __hip_atomic_store(sc.err_flag, kErrStepBudget, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     while (wave_ballot(k < v.K) != 0ull) {
         float o[3], d[3];
         make_ray<MODE>(v.cam, v.hw, v.W, v.H, x, y, prev[0], prev[1], prev[2], pa, v.z0, v.le, v.ld, o, d);
         const RayW r = ray_setup(o, d, dominant_axis(d), sc.n_tris);
         unsigned long long best = ~0ull;
         uint32_t slot = 0;
-        if (k < v.K) {
+        if (k < v.K && !spent) {
             const float4* tp = sc.tris + 3 * (size_t)r.tri_base;
             const uint32_t last = sc.n_tris - 1u;
             uint32_t i = sub;
@@ -1339,30 +1344,37 @@ void launch_direct_mode(const rcp_scene* s, const ViewDev& v, int lanes, hipStre
 
 // Lanes per pixel of the direct kernel, or 0 where the tree is faster.
 //
-// Its time is that of the pixels times triangles it tests; the tree's is a
-// chain of dependent loads per pass, the longer the more nodes and triangles a
-// ray is expected to visit (ray_work, the SAH cost with all costs 1): 10-20 for
-// a terrain of up to 100,000 triangles, about three quarters of the triangle
-// count for a soup of large triangles.  K = 6,
-// microseconds, direct / tree:
-//   terrain, 1024 triangles (ray_work 12): 64 x 64 42 / 190, 128 x 128 99 / 200,
-//     320 x 200 246 / 200; 4096 triangles: 64 x 64 130 / 210, 128 x 128 375 / 230;
-//     256 triangles: 320 x 200 85 / 190, 640 x 400 224 / 190
-//   soup, 256 triangles (211): 64 x 64 21 / 733, 1280 x 720 412 / 779;
-//     2048 triangles (1547): 640 x 400 890 / 4200; 16384 (11959): 64 x 64 518 / 13700
-// so it is taken up to 20M tests per pass, or half a million per unit of
-// ray_work, and for no more triangles than a group tests in the time the tree's
-// passes take at least (4096, or 16 per unit of ray_work).
+// Its time is that of the pixels times triangles it tests in the first pass
+// (0.78 T tests/s; the later ones trace only what moves); the tree's is a chain
+// of dependent loads per pass, the longer the more nodes and triangles a ray is
+// expected to visit (ray_work, the SAH cost with all costs 1): 10-20 for a
+// terrain of up to 100,000 triangles, about three quarters of the triangle
+// count for a soup of large triangles.  Microseconds, direct / tree:
+//   terrain, 1024 triangles (ray_work 12), K = 6: 64 x 64 42 / 190, 128 x 128
+//     99 / 200, 320 x 200 246 / 200; 4096 triangles: 64 x 64 130 / 210, 128 x 128
+//     375 / 230; 256 triangles: 320 x 200 85 / 190, 640 x 400 224 / 190
+//   soup, 256 triangles (209), K = 6: 64 x 64 17 / 314, 720 x 480 156 / 668,
+//     1280 x 720 412 / 779; 2500 (1888), 720 x 480: K = 1 1116 / 756, K = 6 1418 / 3584;
+//     16384 (11959): 400 x 300 K = 1 2591 / 2585, 720 x 480 K = 2 7780 / 5981, K = 6
+//     9580 / 16650; 65536: 320 x 200 K = 1 6019 / 6324; 262144: 160 x 100 K = 1
+//     7947 / 11090, K = 6 16083 / 56382
+// so it is taken for no more triangles than a group tests in the time the tree's
+// passes take at least (4096, or 16 per unit of ray_work, up to the 262144 it was
+// measured at), up to 20M tests in the first pass or half a million per unit of
+// ray_work, and no more than the tree's K passes take: the last line, which
+// grows more slowly than the ray_work, because a ray's closest hit ends it
+// before most of the boxes that it would cross.
 // 64 lanes per pixel leave few pixels per wave, which small frames want; 16
 // are faster from about 32K pixels on, 4 for large frames of few triangles
 // (128 triangles: 640 x 400 104 / 77 with 4 / 16 lanes, 1280 x 720 227 / 251).
-int direct_lanes(const rcp_scene* s, int W, int H) {
+int direct_lanes(const rcp_scene* s, int W, int H, int K) {
     const double tris = s->dev.n_tris, pixels = (double)W * H, work = s->ray_work;
-    if (tris < 1.0 || tris > std::max(4096.0, 16.0 * work)) return 0;
-    if (pixels * tris > std::max(20e6, 0.5e6 * work)) return 0;
-    // (the test hooks reach the error paths of the traversal and its
-    // workspace, which this kernel does not have)
-    if (s->dev.step_budget < 5ull * s->dev.n_nodes + 16ull || alloc_hook_armed()) return 0;
+    if (tris < 1.0 || tris > std::min(std::max(4096.0, 16.0 * work), 262144.0)) return 0;
+    const double tests = pixels * tris;
+    if (tests > std::max(20e6, 0.5e6 * work) || tests > 6.5e9) return 0;
+    if (tests > K * std::min({0.125e9 + 0.19e6 * work, 1.2e9 + 0.065e6 * work, 5e9})) return 0;
+    // (the hook that fails allocations is there for the paths that make some)
+    if (alloc_hook_armed()) return 0;
     if (tris <= 64.0) return pixels <= 4e5 ? 16 : 4;
     return pixels <= 32768.0 ? 64 : (tris > 128.0 || pixels <= 4e5 ? 16 : 4);
 }
@@ -1384,7 +1396,7 @@ rcp_status launch_direct(const rcp_scene* s, const Camera& cam, int W, int H, in
 rcp_status render_chain(rcp_scene* s, Workspace& w, const Camera& cam, int W, int H, int K, const Disp& disp,
                         float* out_images, int32_t* out_ids, unsigned long long* host_counts, hipStream_t stream) {
     const bool stats = host_counts != nullptr;
-    const int lanes = stats ? 0 : direct_lanes(s, W, H);
+    const int lanes = stats ? 0 : direct_lanes(s, W, H, K);
     if (lanes > 0) return launch_direct(s, cam, W, H, K, disp, out_images, out_ids, lanes, stream);
     const Launch lp = launch_params(s, chain_ordered(s));
     const uint64_t n_entries = view_entries(W, H, lp.tile_log2w);
@@ -1441,7 +1453,7 @@ rcp_status render_chain_fixed(rcp_scene* s, Workspace& w, const Camera& cam, int
                   per_block * sizeof(int32_t), w.spill_cap * sizeof(int32_t), cus);
         return RCP_ERR_INVALID_ARGUMENT;
     }
-    if (const int lanes = direct_lanes(s, W, H))
+    if (const int lanes = direct_lanes(s, W, H, K))
         return launch_direct(s, cam, W, H, K, disp, out_images, out_ids, lanes, stream);
     if ((size_t)g.blocks > fit) g.blocks = (int)fit;
     return launch_one_view(s, w, lp, g, cam, W, H, K, disp, out_images, out_ids, false, stream);
@@ -1556,7 +1568,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     groups.back().items = (uint32_t)items;
 
     if (n_views == 1)
-        if (const int lanes = direct_lanes(s, views[0].W, views[0].H)) {
+        if (const int lanes = direct_lanes(s, views[0].W, views[0].H, views[0].K)) {
             const Disp d{views[0].disp.lambda_eye, views[0].disp.lambda_dir, views[0].disp.z0, views[0].disp.mode};
             return launch_direct(s, hv[0].cam, views[0].W, views[0].H, views[0].K, d, views[0].out_images,
                                  views[0].out_ids, lanes, stream);

@@ -85,3 +85,16 @@ def test_waves_with_few_pixels(W, H, refill):
     for mode in (rcp.RCP_MODE_COLOR, rcp.RCP_MODE_NORMAL):
         engines_agree(s, cam, W, H, 4, 0.0, 0.05, mode)
     s.close()
+
+
+@pytest.mark.parametrize("n,W,H", [(4097, 40, 30), (20001, 40, 30), (20001, 200, 180)])
+@pytest.mark.parametrize("mode", [rcp.RCP_MODE_COLOR, rcp.RCP_MODE_NORMAL])
+def test_direct_above_4096_triangles(n, W, H, mode):
+    say("direct, many triangles", n, W, H, mode)
+    sc = scenegen.soup_scene(seed=5, n=n)
+    s = rcp.Scene(sc)
+    img, ids = engines_agree(s, SOUP_CAM, W, H, 2, 0.0, 0.05, mode)
+    if W * H < 2000:
+        o_img, o_ids = oracle.OracleScene(sc, use_bvh=False).render(SOUP_CAM, W, H, 2, 0.0, 0.05, mode=mode)
+        assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()

@@ -56,3 +56,16 @@ def test_route_does_not_depend_on_the_units_of_the_costs(scene, W, H):
         s.close()
     assert trees[1][:2] == trees[0][:2] == trees[2][:2] and np.allclose([t[2] for t in trees], trees[0][2], rtol=1e-6)
     assert routes[0] == routes[1] == routes[2] and len(routes[0]) == 1, routes
+
+
+# soups of large triangles, where the direct kernel's share ends: K passes of
+# the tree take 0.7e9 tests' time each at 4096 triangles, and nothing was
+# measured beyond 262,144
+@pytest.mark.parametrize("n,W,H,K,direct", [(4096, 400, 300, 1, True), (4096, 720, 480, 1, False), (4096, 720, 480, 3, True),
+                                            (16384, 512, 512, 1, False), (262144, 32, 32, 1, True), (262145, 32, 32, 1, False)])
+def test_direct_kernel_only_where_it_was_measured_faster(n, W, H, K, direct):
+    say("direct limit", n, W, H, K)
+    s = rcp.Scene(scenegen.soup_scene(seed=3, n=n))
+    cam = scenegen.camera_look_at([0, 0.2, -2.5], [0, 0, 0], [0, 1, 0], 60.0)
+    assert rendered(launched(lambda: s.render(cam, W, H, K, 0.0, 0.02))) == {"k_direct" if direct else "k_chain"}
+    s.close()
