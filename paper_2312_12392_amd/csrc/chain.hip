@@ -1379,6 +1379,10 @@ int direct_lanes(const rcp_scene* s, int W, int H, int K) {
     return pixels <= 32768.0 ? 64 : (tris > 128.0 || pixels <= 4e5 ? 16 : 4);
 }
 
+// A direct launch of more tests than this is kept apart from a server's other
+// launches (BatchWorkspace::alone).
+constexpr double kAloneTests = 50e6;
+
 rcp_status launch_direct(const rcp_scene* s, const Camera& cam, int W, int H, int K, const Disp& disp, float* out_images,
                          int32_t* out_ids, int lanes, hipStream_t stream) {
     const ViewDev v = view_of(s, cam, W, H, K, disp, out_images, out_ids, 3);
@@ -1567,8 +1571,10 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     hb[bofs++] = (uint32_t)items;
     groups.back().items = (uint32_t)items;
 
+    ws.alone = false;
     if (n_views == 1)
         if (const int lanes = direct_lanes(s, views[0].W, views[0].H, views[0].K)) {
+            ws.alone = (double)views[0].W * views[0].H * s->dev.n_tris > kAloneTests;
             const Disp d{views[0].disp.lambda_eye, views[0].disp.lambda_dir, views[0].disp.z0, views[0].disp.mode};
             return launch_direct(s, hv[0].cam, views[0].W, views[0].H, views[0].K, d, views[0].out_images,
                                  views[0].out_ids, lanes, stream);

@@ -215,6 +215,7 @@ struct BatchWorkspace {
     size_t order_cap = 0;         // uint32 entries
     float4* entries = nullptr;    // entry lists
     size_t entry_cap = 0;         // float4 entries
+    bool alone = false;           // the last launch keeps the whole chip busy: others start after it
 };
 
 // Tiles of the largest one-view batch a server slot hands out in cost order

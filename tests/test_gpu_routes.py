@@ -2,6 +2,7 @@
 rules that choose by the scene must not depend on the units of its build's
 costs, nor reach past the sizes they were measured at."""
 import re
+import time
 
 import numpy as np
 import pytest
@@ -68,4 +69,33 @@ def test_direct_kernel_only_where_it_was_measured_faster(n, W, H, K, direct):
     s = rcp.Scene(scenegen.soup_scene(seed=3, n=n))
     cam = scenegen.camera_look_at([0, 0.2, -2.5], [0, 0, 0], [0, 1, 0], 60.0)
     assert rendered(launched(lambda: s.render(cam, W, H, K, 0.0, 0.02))) == {"k_direct" if direct else "k_chain"}
+    s.close()
+
+
+def test_server_launches_start_after_a_long_direct_launch():
+    """A direct launch that keeps the chip busy is not run beside others; every
+    request's images are those of rcp_render."""
+    say("server beside a direct launch")
+    s = rcp.Scene(scenegen.soup_scene(seed=12, n=4000))
+    cam = scenegen.camera_look_at([0, 0.2, -2.5], [0, 0, 0], [0, 1, 0], 60.0)
+    d = rcp.make_displacement(0.0, 0.02)
+    sizes = [(512, 512, 8), (64, 64, 1), (1280, 720, 1)]   # the first one runs for milliseconds
+    ref = [s.render(cam, w, h, k, 0.0, 0.02) for w, h, k in sizes]
+    srv = rcp.rcp_server_create(s.handle, 1 << 30, max_inflight=3)
+    for _ in range(5):
+        tickets, done = [], []
+        for w, h, k in sizes:
+            tickets.append(rcp.rcp_submit(srv, cam, w, h, k, d, with_ids=True))
+            time.sleep(0.0003)   # a launch each
+        for t, (img, ids) in zip(tickets, ref):
+            while (p := rcp.rcp_poll(srv, t))[0] not in (rcp.RCP_REQ_DONE, rcp.RCP_REQ_FAILED):
+                pass
+            done.append(p[1][2])
+            a, b = torch.empty_like(img), torch.empty_like(ids)
+            rcp.rcp_result_copy(srv, t, a, b)
+            torch.cuda.synchronize()
+            assert torch.equal(a, img) and torch.equal(b, ids)
+            rcp.rcp_release(srv, t)
+        assert done[0] <= min(done[1:]), done
+    rcp.rcp_server_destroy(srv)
     s.close()
