@@ -1116,6 +1116,7 @@ struct ChainGrid {
     ChainKernel k;
     int blocks = 0;
     size_t smem = 0;
+    uint32_t lanes = 0;   // threads of a full grid
     uint32_t threads() const { return (uint32_t)blocks * (uint32_t)k.block; }
 };
 
@@ -1133,6 +1134,7 @@ rcp_status resident_grid(const Launch& lp, bool stats, int n_views, ChainGrid& g
         if (cap < per_cu) per_cu = cap;
     }
     g.blocks = per_cu * cus;
+    g.lanes = g.threads();
     return RCP_OK;
 }
 
@@ -1147,10 +1149,16 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
         p.k = n_views == 1 ? pair_kernel<true>(mode) : pair_kernel<false>(mode);
         RCP_TRY_STATUS(resident_grid(lp, stats, n_views, p));
         p.blocks = std::min(p.blocks, g.blocks);
+        p.lanes = p.threads();
         g = p;
     }
     return RCP_OK;
 }
+
+// Whether a ray visits a large part of the scene's triangles (a soup of large
+// triangles about three quarters of their number in nodes and tests, a terrain
+// 1 / 80 of it at 1000 triangles and less above).
+bool visits_much(const rcp_scene* s) { return s->ray_work > (float)s->dev.n_tris / 16.0f; }
 
 // Pixels a wave holds at once.  A launch of few pixels would leave most of
 // the chip's waves without any while the others' rays wait for the slowest of
@@ -1158,7 +1166,7 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
 // two handfuls.  (20,000-triangle terrain, K = 6, microseconds with 64 / the
 // choice: 64 x 64 353 / 223 with 1, 320 x 200 396 / 327 with 8, 512 x 512
 // 401 / 362 with 32; halving or doubling the choice is slower or the same.)
-void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g) {
+void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g, int K) {
     const uint64_t waves = (uint64_t)g.threads() / 64u;
     a.take = 1u;
     while (a.take < 64u && (uint64_t)a.n_items > 2u * waves * a.take) a.take *= 2u;
@@ -1168,12 +1176,20 @@ void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g) {
     // exact / whole: 1920 x 1080, K = 6, 5 per lane 1.06 / 1.09; 2560 x 1440, 9
     // per lane 1.69 / 1.53; 3840 x 2160, K = 8, 21 per lane 4.33 / 3.38; 4 mixed
     // views, 6 per lane 1.39 / 1.35.  Pieces of 8, 16 or 32 pixels gain nothing:
-    // the tiles then lie across waves as much as with exact counts.)
-    // Not where rays visit many nodes on each level of the tree: the fetches are
-    // then a small part, and what a wave keeps is long work (3840 x 2160, K = 3,
-    // exact / whole: soups of 635 triangles, 68 of ray_work per level, 1.64 / 1.87,
-    // of 2500 4.41 / 5.40; a terrain of 20,000 1.00 / 0.83; terrains have 1 to 10).
-    a.whole = a.n_items >= 7u * (uint64_t)g.threads() && s->ray_work <= 20.0f * (float)s->dev.max_depth;
+    // the tiles then lie across waves as much as with exact counts.  The lanes are
+    // those of a full grid: one cut down to its stack overflow area has more
+    // pixels per lane and no more time to lose: 16M triangles, 1080p, K = 3 on
+    // four workgroups per CU 1.66 / 1.83.)
+    // Not where a ray visits much of the scene: the fetches are then a small part,
+    // and what a wave keeps is long work (3840 x 2160, exact / whole: soups of 64
+    // triangles, K = 8, 0.89 / 1.01, of 128 1.16 / 1.31, of 635, K = 3, 1.64 / 1.87, of
+    // 2500 4.41 / 5.40; terrains of
+    // 20,000 1.00 / 0.83, of 16M, K = 8, 4.33 / 3.38).
+    // And from the root not in frames of one pass, nor in trees whose rays' work
+    // is long (without lists, 3840 x 2160, exact / whole: K = 1, 20,000 triangles 0.51 /
+    // 0.55, 1M 0.80 / 0.88; K = 2, 20,000 0.84 / 0.76, 1M 1.57 / 1.55, 4M, 74 of
+    // ray_work, 1.94 / 2.03).
+    a.whole = a.n_items >= 7u * (uint64_t)g.lanes && !visits_much(s) && (g.k.entry || (K >= 2 && s->ray_work <= 50.0f));
     // the refill threshold in idle lanes, in proportion
     a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
 }
@@ -1311,7 +1327,7 @@ rcp_status launch_one_view(rcp_scene* s, Workspace& w, const Launch& lp, const C
     a.n_items = (uint32_t)view_items(view);
     a.fetch = w.counters;
     a.refill_min = lp.refill_min;
-    set_take(s, a, g);
+    set_take(s, a, g, K);
     a.exit_lanes = (uint32_t)lp.exit_lanes;
     a.spill = w.spill;
     a.spill_stride = g.threads();
@@ -1533,7 +1549,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
                      [&](int p, int q) { return views[p].disp.mode < views[q].disp.mode; });
     std::vector<ViewDev> hv((size_t)n_views);
     std::vector<uint32_t> hb((size_t)n_views + 3);   // begin arrays of the groups, back to back
-    struct Group { int mode, first, count; size_t bofs; uint32_t items; };
+    struct Group { int mode, first, count; size_t bofs; uint32_t items; int passes; };   // passes: the most of any view
     std::vector<Group> groups;
     uint64_t items = 0, n_entries = 0;
     size_t bofs = 0;
@@ -1544,7 +1560,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
                 hb[bofs++] = (uint32_t)items;
                 groups.back().items = (uint32_t)items;
             }
-            groups.push_back(Group{vi.disp.mode, j, 0, bofs, 0});
+            groups.push_back(Group{vi.disp.mode, j, 0, bofs, 0, 0});
             items = 0;
         }
         Camera c{};
@@ -1567,6 +1583,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
             return RCP_ERR_INVALID_ARGUMENT;
         }
         groups.back().count++;
+        groups.back().passes = std::max(groups.back().passes, vi.K);
     }
     hb[bofs++] = (uint32_t)items;
     groups.back().items = (uint32_t)items;
@@ -1669,7 +1686,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         a.n_items = groups[g].items;
         a.fetch = ws.fetch + kFetchWords * g;
         a.refill_min = lpr.refill_min;
-        set_take(s, a, grids[g]);
+        set_take(s, a, grids[g], groups[g].passes);
         a.exit_lanes = (uint32_t)lpr.exit_lanes;
         a.spill = ws.spill;
         a.spill_stride = grids[g].threads();

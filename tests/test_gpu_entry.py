@@ -142,3 +142,28 @@ def test_engines_agree_around_the_limit_of_whole_tiles(W, H, scene, few_visits):
     assert (s.info()["sah_cost"] <= 20.0 * s.info()["max_depth"]) == few_visits
     both_engines(s, patch_camera((0.2, 0.5, -1.1)), W, H, 2, 0.0, 0.05)
     s.close()
+
+
+# the same where the rays start at the root (a view beyond the allocation-free
+# area's lists), of one pass (exact counts) and of two (whole tiles), and where
+# a deep tree leaves that call a smaller grid
+@pytest.mark.parametrize("scene", ["terrain", "soup", "stack"])
+@pytest.mark.parametrize("W,H,K", [(2600, 1900, 1), (2600, 1900, 2), (1500, 1100, 3)])
+def test_whole_tiles_of_the_allocation_free_render(scene, W, H, K):
+    say("whole tiles, noalloc", scene, W, H, K)
+    if scene == "stack":   # a chain of triangles that halve in size: many levels
+        n = 6000
+        k = np.arange(n, dtype=np.float64)[:, None, None] * (40.0 / n)
+        tri = np.array([[[0.0, 0.0, 0.0], [1.0, 0.1, 0.0], [0.1, 1.0, 0.3]]])
+        sc = scenegen.Scene(verts=(2.0 ** (k - 40.0) * (1.0 + 0.05 * tri)).reshape(-1, 3), idx=np.arange(3 * n).reshape(n, 3),
+                            rgb=np.random.default_rng(1).uniform(0, 1, (n, 3)))
+    else:
+        sc = scenegen.terrain_patch(seed=8, cells=60, n_boxes=40) if scene == "terrain" else scenegen.soup_scene(4, 100)
+    s = rcp.Scene(sc)
+    cam = patch_camera((0.2, 0.5, -1.1))
+    a, ia = s.render(cam, W, H, K, 0.0, 0.05)
+    b, ib = torch.empty_like(a), torch.empty_like(ia)
+    rcp.rcp_render_noalloc(s.handle, cam, W, H, K, rcp.make_displacement(0.0, 0.05), b, ib)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and torch.equal(ia, ib)
+    s.close()
