@@ -1116,7 +1116,7 @@ struct ChainGrid {
     ChainKernel k;
     int blocks = 0;
     size_t smem = 0;
-    uint32_t lanes = 0;   // threads of a full grid
+    uint32_t lanes = 0;   // threads of a full grid of the default kernel
     uint32_t threads() const { return (uint32_t)blocks * (uint32_t)k.block; }
 };
 
@@ -1138,6 +1138,54 @@ rcp_status resident_grid(const Launch& lp, bool stats, int n_views, ChainGrid& g
     return RCP_OK;
 }
 
+// Whether a ray visits a large part of the scene's triangles (a soup of large
+// triangles about three quarters of their number in nodes and tests, a terrain
+// 1 / 80 of it at 1000 triangles and less above).
+bool visits_much(const rcp_scene* s) { return s->ray_work > (float)s->dev.n_tris / 16.0f; }
+
+// Whether a launch's rays are better off in entry lists than at the root.  A ray
+// that has a list tests its 16 boxes, whatever it meets of them, and saves the
+// levels of the tree above them; how much that is depends on how narrow the
+// groups' pyramids are (`spread`: the displacement in radians or so, see below)
+// and on how many levels there are.  Terrains, colour mode, speed against the
+// root start for spreads 0.01 / 0.03 / 0.05 / 0.1 / 0.2:
+//   1920 x 1080, K = 6: 5000 triangles (9 levels) 1.13 / 1.03 / 0.96 / 0.89 / 0.87, 20,000
+//     1.10 / 0.99 / 0.95 / 0.92 / 0.89, 100,000 (12) 1.11 / 1.00 / 0.96 / 0.94 / 0.95,
+//     300,000 (14) 1.07 / 1.01 / 1.01 / 1.01 / 1.00, 1M 1.13 / 1.07 / 1.05 / 1.04 / 1.02;
+//     K = 3: 5000 1.07 / 1.05 / 1.02 / 0.99 / 0.98, 100,000 1.05 / 1.04 / 1.03 / 1.02 / 0.97
+//   1280 x 720, K = 6: 5000 1.15 / 1.04 / 0.99 / 0.90 / 0.88, 100,000 1.20 / 1.08 / 1.03 /
+//     0.98 / 0.95, 1M 1.20 / 1.20 / 1.05 / 1.01 / 1.02; K = 3 more throughout
+//   3840 x 2160, K = 6: 5000 1.22 / 1.16 / 1.11 / 1.03 / 0.94, 100,000 1.36 / 1.17 / 1.08 /
+//     0.97 / 0.91, 1M 1.40 / 1.20 / 1.11 / 1.03 / 0.99
+// The depth and normal modes lose less by wide pyramids: nothing up to 0.2, but
+// for 1280 x 720 frames of 5000 triangles in the depth mode (0.04 1.00, 0.08 0.97,
+// 0.12 0.94).
+// Where a ray visits much of the scene most boxes are met; the lists pay by what
+// comes with them, the leaf queue, and that for long chains and small frames
+// (soups of 200 to 4000 triangles, six views: 3840 x 2160, K = 1 0.92-1.11, K = 3
+// 0.93-1.16, K = 8 1.05-1.6; 1920 x 1080, K = 1 and 3 0.93-1.19, K = 6 1.2-1.6; 1280 x
+// 720, all 1.1-1.8): a frame of up to three passes is no slower only from the root,
+// but for the depth and normal modes from 635 triangles on (3840 x 2160, K = 2 and
+// 3: 64 0.96, 256 1.00, 635 1.05, 1200 1.13, 2500 1.33).
+bool lists_pay(const rcp_scene* s, int mode, double spread, int K, uint64_t items, uint32_t lanes) {
+    const bool few = few_pixels(items, lanes), many = items >= 7u * (uint64_t)lanes;
+    if (visits_much(s)) return few || K > 3 || (mode != RCP_MODE_COLOR && s->ray_work >= 400.0f);
+    const uint32_t levels = s->dev.max_depth;
+    double most = 0.2;
+    if (mode != RCP_MODE_COLOR) {
+        if (few && levels <= 9u) most = 0.06;
+    } else if (many) {
+        most = 0.1;
+    } else if (levels > 12u || (few && K <= 3)) {
+        return true;
+    } else if (few) {
+        most = levels > 10u ? 0.09 : 0.04;
+    } else {
+        most = K <= 3 ? 0.06 : 0.032;
+    }
+    return spread <= most;
+}
+
 // The grid of a launch over `items` pixels (with their tiles' padding).  It
 // needs no more overflow area than one of more items: the kernel for few keeps
 // as many stack entries per lane, and no more lanes.
@@ -1149,16 +1197,11 @@ rcp_status chain_grid(const Launch& lp, bool stats, int n_views, int mode, bool 
         p.k = n_views == 1 ? pair_kernel<true>(mode) : pair_kernel<false>(mode);
         RCP_TRY_STATUS(resident_grid(lp, stats, n_views, p));
         p.blocks = std::min(p.blocks, g.blocks);
-        p.lanes = p.threads();
+        p.lanes = g.lanes;
         g = p;
     }
     return RCP_OK;
 }
-
-// Whether a ray visits a large part of the scene's triangles (a soup of large
-// triangles about three quarters of their number in nodes and tests, a terrain
-// 1 / 80 of it at 1000 triangles and less above).
-bool visits_much(const rcp_scene* s) { return s->ray_work > (float)s->dev.n_tris / 16.0f; }
 
 // Pixels a wave holds at once.  A launch of few pixels would leave most of
 // the chip's waves without any while the others' rays wait for the slowest of
@@ -1188,8 +1231,9 @@ void set_take(const rcp_scene* s, ChainArgs& a, const ChainGrid& g, int K) {
     // And from the root not in frames of one pass, nor in trees whose rays' work
     // is long (without lists, 3840 x 2160, exact / whole: K = 1, 20,000 triangles 0.51 /
     // 0.55, 1M 0.80 / 0.88; K = 2, 20,000 0.84 / 0.76, 1M 1.57 / 1.55, 4M, 74 of
-    // ray_work, 1.94 / 2.03).
-    a.whole = a.n_items >= 7u * (uint64_t)g.lanes && !visits_much(s) && (g.k.entry || (K >= 2 && s->ray_work <= 50.0f));
+    // ray_work, 1.94 / 2.03; 16 views, 5000 1.36 / 1.20, 1M, 36 of ray_work, 4.51 / 4.53, spread
+    // 0.2 4.80 / 5.04).
+    a.whole = a.n_items >= 7u * (uint64_t)g.lanes && !visits_much(s) && (g.k.entry || (K >= 2 && s->ray_work <= (a.n_views == 1 ? 50.0f : 30.0f)));
     // the refill threshold in idle lanes, in proportion
     a.refill_min = 64 - (int)a.take + (a.refill_min * (int)a.take + 63) / 64;
 }
@@ -1242,6 +1286,22 @@ void view_spread(const rcp_scene* s, const Camera& cam, float hw, const Disp& d,
     eye = fine ? (float)we : 0.0f;
 }
 
+// The same as one number: how far a ray of the view may be turned, with the
+// eye's displacement seen from half the scene's longest extent (which is about
+// where a view of the whole scene is taken from).
+double spread_angle(const rcp_scene* s, float dir, float eye) {
+    if (dir < 0.0f) return HUGE_VAL;
+    double extent = 1e-30;
+    for (int a = 0; a < 3; ++a) extent = std::max(extent, 0.5 * s->occ.cell[a] * s->occ.n[a]);
+    return dir + eye / extent;
+}
+
+double view_spread_angle(const rcp_scene* s, const Camera& cam, int W, int H, const Disp& d) {
+    float dir, eye;
+    view_spread(s, cam, half_width(cam.th, W, H), d, dir, eye);
+    return spread_angle(s, dir, eye);
+}
+
 ViewDev view_of(const rcp_scene* s, const Camera& cam, int W, int H, int K, const Disp& d, float* out, int32_t* ids,
                 int tile_log2w) {
     ViewDev v{};
@@ -1284,7 +1344,8 @@ rcp_status prepare_chain(rcp_scene* s, Workspace& ws, int W, int H, int mode, hi
     }
     rcp_status st = ensure_workspace(s, ws, 0, 0, need, stream);
     if (st != RCP_OK) return st;
-    return ensure_tiles(ws, order_entries(W, H, lp.tile_log2w), view_entries(W, H, lp.tile_log2w), stream);
+    const uint64_t lists = view_entries(W, H, lp.tile_log2w);
+    return ensure_tiles(ws, order_entries(W, H, lp.tile_log2w), lists <= kMaxBatchEntries ? lists : 0, stream);
 }
 
 namespace {
@@ -1419,13 +1480,17 @@ rcp_status render_chain(rcp_scene* s, Workspace& w, const Camera& cam, int W, in
     const int lanes = stats ? 0 : direct_lanes(s, W, H, K);
     if (lanes > 0) return launch_direct(s, cam, W, H, K, disp, out_images, out_ids, lanes, stream);
     const Launch lp = launch_params(s, chain_ordered(s));
-    const uint64_t n_entries = view_entries(W, H, lp.tile_log2w);
-    rcp_status st = ensure_tiles(w, order_entries(W, H, lp.tile_log2w), n_entries, stream);
-    if (st != RCP_OK) return st;
+    const uint64_t n_entries = view_entries(W, H, lp.tile_log2w), items = frame_items(W, H, lp.tile_log2w);
     ChainGrid g;
-    st = chain_grid(lp, stats, 1, disp.mode, !stats && entries_fit(s, w.entries, w.entry_cap, n_entries),
-                    frame_items(W, H, lp.tile_log2w), g);
+    bool entry = !stats && s->dev.n_nodes > 0 && n_entries <= kMaxBatchEntries;
+    if (entry) {
+        RCP_TRY_STATUS(chain_grid(lp, stats, 1, disp.mode, true, items, g));
+        entry = lists_pay(s, disp.mode, view_spread_angle(s, cam, W, H, disp), K, items, g.lanes);
+    }
+    rcp_status st = ensure_tiles(w, order_entries(W, H, lp.tile_log2w), entry ? n_entries : 0, stream);
     if (st != RCP_OK) return st;
+    if (!entry || !entries_fit(s, w.entries, w.entry_cap, n_entries))
+        RCP_TRY_STATUS(chain_grid(lp, stats, 1, disp.mode, false, items, g));
     st = ensure_workspace(s, w, 0, 0, spill_depth_of(s, g.k) * g.threads(), stream);
     if (st != RCP_OK) return st;
     st = launch_one_view(s, w, lp, g, cam, W, H, K, disp, out_images, out_ids, stats, stream);
@@ -1456,13 +1521,15 @@ rcp_status render_chain_fixed(rcp_scene* s, Workspace& w, const Camera& cam, int
     // added to it when there are none.)
     ChainGrid g;
     size_t per_block = 0, fit = 0;
+    const uint64_t items = frame_items(W, H, lp.tile_log2w);
     for (const bool entry : {true, false}) {
         if (entry && !entries_fit(s, w.entries, w.entry_cap, view_entries(W, H, lp.tile_log2w))) continue;
         if (!entry && w.entries) {
             w.spill = (int32_t*)w.entries;
             w.spill_cap += w.entry_cap * (sizeof(float4) / sizeof(int32_t));
         }
-        RCP_TRY_STATUS(chain_grid(lp, false, 1, disp.mode, entry, frame_items(W, H, lp.tile_log2w), g));
+        RCP_TRY_STATUS(chain_grid(lp, false, 1, disp.mode, entry, items, g));
+        if (entry && !lists_pay(s, disp.mode, view_spread_angle(s, cam, W, H, disp), K, items, g.lanes)) continue;
         per_block = spill_depth_of(s, g.k) * (size_t)g.k.block;
         fit = w.spill_cap / per_block;
         if (entry && fit * g.k.block >= 4 * (size_t)cus * kBlock) break;
@@ -1598,12 +1665,31 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
         }
 
     // entry lists for all views, up to kMaxBatchEntries (a server slot: as many
-    // as it was sized for); without room for them the rays start at the root
-    if (!ws.staging && n_entries <= kMaxBatchEntries && ws.entry_cap < kEntryStride * n_entries) {
+    // as it was sized for); without room for them the rays start at the root, and
+    // so they do where the lists of none would pay (several views share a launch,
+    // which lists make faster even where a single one's do not: soups 1.1-2.2
+    // times; 16 views of a terrain of 5000 triangles at a spread of 0.05 1.15, at
+    // 0.2 1.02 with lists and 1.13 from the root, of 100,000 1.16, 0.99 and 0.98;
+    // 4 views 0.97, 0.85 and 0.97, 0.96, 0.93 and 0.97)
+    bool want = s->dev.n_nodes > 0;
+    if (n_views == 1 && want) {
+        ChainGrid one;
+        RCP_TRY_STATUS(chain_grid(lp, false, 1, groups[0].mode, true, groups[0].items, one));
+        want = lists_pay(s, groups[0].mode, spread_angle(s, hv[0].spread_dir, hv[0].spread_eye), hv[0].K, groups[0].items,
+                         one.lanes);
+    } else if (want && !visits_much(s) && s->dev.max_depth <= 12u) {
+        want = false;
+        for (const ViewDev& v : hv) want = want || spread_angle(s, v.spread_dir, v.spread_eye) <= 0.1;
+    }
+    if (want && !ws.staging && n_entries <= kMaxBatchEntries && ws.entry_cap < kEntryStride * n_entries) {
         const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * (size_t)n_entries, sizeof(float4), stream);
         if (se != RCP_OK && se != RCP_ERR_OUT_OF_MEMORY) return se;
     }
-    const bool entry = entries_fit(s, ws.entries, ws.entry_cap, n_entries);
+    const bool entry = want && entries_fit(s, ws.entries, ws.entry_cap, n_entries);
+    // From the root the views go out row by row.  (16 views of 1M triangles 4.50
+    // ms against 4.68 by columns, of 4M 5.44 and 5.80.)
+    if (!entry)
+        for (ViewDev& v : hv) v.super_rows = 0;
     size_t spill_need = 0;
     std::vector<ChainGrid> grids(groups.size());
     for (size_t g = 0; g < groups.size(); ++g) {

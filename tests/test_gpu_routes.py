@@ -59,6 +59,59 @@ def test_route_does_not_depend_on_the_units_of_the_costs(scene, W, H):
     assert routes[0] == routes[1] == routes[2] and len(routes[0]) == 1, routes
 
 
+def with_lists(names):
+    """Whether the chain kernel among them starts rays in entry lists."""
+    k, = (n for n in names if n.startswith("k_chain"))
+    args = re.search("<(.*)>", k).group(1).split(", ")
+    return args[3 if k.startswith("k_chain_aux") else 2] == "true"
+
+
+# lists where they can save levels of the tree: narrow pyramids (a spread of 0.02,
+# not of 0.2, whether by the direction, a lambda that no pyramid bounds, or the
+# eye), and where most of their boxes are not met anyway (soups: long chains)
+@pytest.mark.parametrize("scene,W,H,K,le,ld,mode,lists", [
+    ("terrain", 1920, 1080, 6, 0.0, 0.02, "color", True), ("terrain", 1920, 1080, 6, 0.0, 0.2, "color", False),
+    ("terrain", 1920, 1080, 6, 0.0, 0.6, "color", False), ("terrain", 1920, 1080, 6, 0.2, 0.01, "color", False),
+    ("terrain", 1280, 720, 6, 0.0, 0.2, "color", False), ("terrain", 1280, 720, 3, 0.0, 0.2, "color", True),
+    ("terrain", 3840, 2160, 2, 0.0, 0.05, "color", True), ("terrain", 3840, 2160, 2, 0.0, 0.2, "color", False),
+    ("terrain", 1920, 1080, 6, 0.0, 0.1, "normal", True), ("terrain", 1920, 1080, 6, 0.0, 0.4, "normal", False),
+    ("soup", 3840, 2160, 1, 0.0, 0.01, "color", False), ("soup", 1920, 1080, 3, 0.0, 0.01, "color", False),
+    ("soup", 1920, 1080, 6, 0.0, 0.01, "color", True), ("soup", 1280, 720, 1, 0.0, 0.01, "color", True),
+    ("soup", 1920, 1080, 2, 0.0, 0.01, "normal", True)])
+def test_entry_lists_where_they_pay(scene, W, H, K, le, ld, mode, lists):
+    say("lists", scene, W, H, K, le, ld, mode)
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=90, n_boxes=40) if scene == "terrain" else scenegen.soup_scene(4, 800))
+    cam = patch_camera() if scene == "terrain" else scenegen.camera_look_at([0, 0.2, -2.5], [0, 0, 0], [0, 1, 0], 60.0)
+    m = {"color": rcp.RCP_MODE_COLOR, "normal": rcp.RCP_MODE_NORMAL}[mode]
+    d = rcp.make_displacement(le, ld, m)
+    out = [(torch.empty((K, H, W, 3), device="cuda"), torch.empty((K, H, W), dtype=torch.int32, device="cuda")) for _ in range(2)]
+    assert with_lists(launched(lambda: rcp.rcp_render(s.handle, cam, W, H, K, d, *out[0]))) == lists
+    # a batch of one takes the same kernel, and the images are the per-pass engine's
+    assert with_lists(launched(lambda: rcp.rcp_render_batch(s.handle, [(cam, W, H, K, d, *out[1])]))) == lists
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    s.set_engine(rcp.RCP_ENGINE_PASSES)
+    rcp.rcp_render(s.handle, cam, W, H, K, d, *out[1])
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    s.close()
+
+
+def test_batches_with_and_without_lists():
+    """Views of narrow pyramids bring their lists for all; wide ones alone start
+    at the root, row by row."""
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=90, n_boxes=40))
+    sizes = [(300, 200, 3), (257, 513, 2), (640, 480, 4)]
+    for spreads, lists in (([0.2, 0.02, 0.3], True), ([0.2, 0.3, 0.6], False)):
+        say("batch lists", spreads)
+        ref = [s.render(patch_camera(), w, h, k, 0.0, ld) for (w, h, k), ld in zip(sizes, spreads)]
+        out = [(torch.empty_like(a), torch.empty_like(i)) for a, i in ref]
+        views = [(patch_camera(), w, h, k, rcp.make_displacement(0.0, ld), *o) for (w, h, k), ld, o in zip(sizes, spreads, out)]
+        assert with_lists(launched(lambda: rcp.rcp_render_batch(s.handle, views))) == lists
+        for (a, i), (b, j) in zip(ref, out):
+            assert torch.equal(a, b) and torch.equal(i, j)
+    s.close()
+
+
 # soups of large triangles, where the direct kernel's share ends: K passes of
 # the tree take 0.7e9 tests' time each at 4096 triangles, and nothing was
 # measured beyond 262,144
