@@ -59,6 +59,7 @@ struct ViewDev {
     uint32_t entries_x;    // groups per row
     float spread_dir;      // bounds of lambda_dir w and lambda_eye w along each camera axis over
     float spread_eye;      // all passes; spread_dir < 0: no useful bound, the lists cull nothing
+    float z_reach;         // the largest |z - z0| they hold for (depth mode)
 };
 
 static_assert(sizeof(ViewDev) + 2 * sizeof(uint32_t) + 64 <= kViewBytes, "one-entry view table");
@@ -239,6 +240,15 @@ __device__ inline void chain_body(const ChainArgs& a) {
                                     (P3[2] - vw.cam.eye[2]) * vw.cam.forward[2];
                             const float4 nv = a.sc.normals[tv.h.slot];
                             na[1] = nv.x; na[2] = nv.y; na[3] = nv.z;
+                            // The lists hold for displacements within the view's bounds.  The
+                            // test's t of a triangle seen edge on is rounding error, and may put
+                            // the hit outside the scene's box; the normal of one whose area is
+                            // near the least float may be longer than 1: then the pixel's next
+                            // rays start at the root.
+                            if (ENTRY && (MODE == RCP_MODE_DEPTH
+                                              ? !(fabsf(na[0] - vw.z0) <= vw.z_reach)
+                                              : !((na[1] * na[1] + na[2] * na[2]) + na[3] * na[3] <= 1.0001f)))
+                                slot = kEntrySlots;
                         }
                     } else {
                         rgb[0] = a.sc.bg[0]; rgb[1] = a.sc.bg[1]; rgb[2] = a.sc.bg[2];
@@ -1263,7 +1273,10 @@ uint64_t view_entries(int W, int H, int tile_log2w, uint32_t* per_row = nullptr)
 // product of unit vectors).  spread_dir < 0 where the rays' pyramid would not
 // be one (lambda_dir w as long as the focal distance) or the numbers leave
 // the range in which single precision holds the test's margins.
-void view_spread(const rcp_scene* s, const Camera& cam, float hw, const Disp& d, float& dir, float& eye) {
+// z_reach: the |z - z0| that is bounded by; a hit beyond it (see the kernel) ends
+// the use of the lists.
+void view_spread(const rcp_scene* s, const Camera& cam, float hw, const Disp& d, float& dir, float& eye,
+                 float& z_reach) {
     double w = 1.0;
     if (d.mode != RCP_MODE_NORMAL)
         for (int a = 0; a < 3; ++a) w = std::max(w, std::fabs(2.0 * s->dev.bg[a] - 1.0));
@@ -1277,7 +1290,9 @@ void view_spread(const rcp_scene* s, const Camera& cam, float hw, const Disp& d,
             lo += std::min(p * cam.forward[a], q * cam.forward[a]);
             hi += std::max(p * cam.forward[a], q * cam.forward[a]);
         }
-        w *= std::max(std::fabs(lo - d.z0), std::fabs(hi - d.z0)) * 1.0001 + 1e-4 * far;
+        const double reach = std::max(std::fabs(lo - d.z0), std::fabs(hi - d.z0)) * 1.0001 + 1e-4 * far;
+        z_reach = (float)reach;
+        w *= reach;
     }
     w *= 1.0001;
     const double wd = w * d.ld, we = w * d.le;
@@ -1297,8 +1312,8 @@ double spread_angle(const rcp_scene* s, float dir, float eye) {
 }
 
 double view_spread_angle(const rcp_scene* s, const Camera& cam, int W, int H, const Disp& d) {
-    float dir, eye;
-    view_spread(s, cam, half_width(cam.th, W, H), d, dir, eye);
+    float dir, eye, reach;
+    view_spread(s, cam, half_width(cam.th, W, H), d, dir, eye, reach);
     return spread_angle(s, dir, eye);
 }
 
@@ -1317,7 +1332,7 @@ ViewDev view_of(const rcp_scene* s, const Camera& cam, int W, int H, int K, cons
     v.out = out;
     v.ids = ids;
     (void)view_entries(W, H, tile_log2w, &v.entries_x);
-    view_spread(s, cam, v.hw, d, v.spread_dir, v.spread_eye);
+    view_spread(s, cam, v.hw, d, v.spread_dir, v.spread_eye, v.z_reach);
     return v;
 }
 

@@ -47,6 +47,40 @@ def test_entry_lists_against_the_root(W, H, mode, le, ld, z0):
     s.close()
 
 
+def test_hit_beyond_the_scene_box():
+    """A triangle in the plane of one pixel's ray: the test accepts it at a t
+    made of rounding errors, here a quarter beyond the depth of the scene's box,
+    and the pixel is displaced by so much more.  Its second ray meets a small
+    triangle that no ray within the box's bound would."""
+    say("hit beyond the box")
+    eye = np.array([0.7027498394741156, -0.7871441872242755, 0.9608831410291954])
+    cam = scenegen.camera_look_at(eye, eye + np.array([np.sin(3.8597546948284363), -0.16773908087293254,
+                                                       np.cos(3.8597546948284363)]), [0, 1, 0], 60.0)
+    e, f, u, r = (np.asarray(getattr(cam, n), np.float64) for n in ("eye", "forward", "up", "right"))
+    a = np.array([1.2095455179417622, 1.5800046433206831, 1.8998096262026594])
+    b = np.array([-2.512781526229155, 0.05199082791927978, -2.9019254816302706])
+    big = e + a[:, None] * f + b[:, None] * u
+    W, H, row, lam = 1, 601, 592, 0.02
+    t = (1 - (2 * row + 1) / H) * float(cam.tan_half_fovy)
+    p = e + 1.28 * (f + t * u + lam * 2.6299365 * r)
+    small = p + 0.003 * np.array([r, -r + u, -r - u])
+    rng = np.random.default_rng(0)   # the rest, off to the sides: a tree too large for the direct kernel
+    c = rng.uniform(big.min(0) + 0.02, big.max(0) - 0.02, (200000, 3))
+    c = c[np.abs((c - e) @ r) / np.maximum((c - e) @ f, 1e-3) > 0.15][:5000]
+    verts = np.concatenate([big[None], small[None], c[:, None] + rng.uniform(-0.005, 0.005, (len(c), 3, 3))]).reshape(-1, 3)
+    n = len(verts) // 3
+    rgb = rng.uniform(0, 1, (n, 3))
+    rgb[0] = (1.0, 0.5, 0.5)   # one to the right
+    sc = scenegen.Scene(verts=verts, idx=np.arange(3 * n).reshape(n, 3), rgb=rgb)
+    sc.k_a, sc.k_d = 1.0, 0.0
+    o_img, o_ids = oracle.OracleScene(sc, use_bvh=True).render(cam, W, H, 3, 0.0, lam, mode=rcp.RCP_MODE_DEPTH, z0=0.0)
+    assert n > 5000 and list(o_ids[:2, row, 0]) == [0, 1]   # the case is there
+    s = rcp.Scene(sc, rcp.build_options(max_leaf=1))
+    img, ids = both_engines(s, cam, W, H, 3, 0.0, lam, rcp.RCP_MODE_DEPTH, 0.0)
+    assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
+
+
 @pytest.mark.parametrize("fov,background", [(4.0, 0.5), (150.0, 0.5), (60.0, 3.0)])
 def test_entry_lists_lens_and_background(fov, background):
     """Narrow and very wide lenses; a background above 1, which displaces by
