@@ -147,6 +147,8 @@ struct Workspace {
     size_t order_cap = 0;                      // uint32 entries
     float4* entries = nullptr;                 // chain engine: entry lists (kEntryStride float4 each)
     size_t entry_cap = 0;                      // float4 entries
+    void* tiles = nullptr;                     // the allocation that holds both
+    size_t lists_refused = SIZE_MAX;           // there was no memory for this many lists
     size_t aux_cap = 0;
     size_t state_cap = 0;                      // entries per list
     uint32_t* counters = nullptr;              // kCounterWords
@@ -162,6 +164,8 @@ struct Workspace {
 void free_workspace(Workspace& w, hipStream_t stream);
 // Room for `order` uint32 of tile scores and order and for `lists` entry lists
 // in a growable workspace (fixed and external workspaces are left as they are).
+// Neither part ever shrinks.  Without memory for the lists the order alone is
+// kept (renders then start their rays at the root).
 rcp_status ensure_tiles(Workspace& w, size_t order, size_t lists, hipStream_t stream);
 
 constexpr size_t kViewBytes = 512;

@@ -476,17 +476,29 @@ rcp_status ensure_workspace(rcp_scene* s, Workspace& w, size_t n_state, size_t n
 
 rcp_status ensure_tiles(Workspace& w, size_t order, size_t lists, hipStream_t stream) {
     if (w.fixed || w.external) return RCP_OK;   // renders use what fits
-    if (w.entries && order <= w.order_cap && kEntryStride * lists <= w.entry_cap) return RCP_OK;
-    // one allocation, the lists first
-    stream_free(w.entries, stream);
+    if (lists >= w.lists_refused) lists = 0;
+    size_t entry_f4 = kEntryStride * lists;
+    if (w.tiles && order <= w.order_cap && entry_f4 <= w.entry_cap) return RCP_OK;
+    // one allocation, the lists first; each part as large as any render so far
+    // needed (views whose needs cross would be given new buffers by every call)
+    order = std::max(order, w.order_cap);
+    entry_f4 = std::max(entry_f4, w.entry_cap);
+    stream_free(w.tiles, stream);
+    w.tiles = nullptr;
     w.entries = nullptr;
     w.order = nullptr;
     w.entry_cap = w.order_cap = 0;
-    void* p = nullptr;
-    RCP_TRY_STATUS(stream_alloc(&p, sizeof(float4) * kEntryStride * lists + sizeof(uint32_t) * order, stream));
-    w.entries = (float4*)p;
-    w.entry_cap = kEntryStride * lists;
-    w.order = (uint32_t*)(w.entries + w.entry_cap);
+    rcp_status st = stream_alloc(&w.tiles, sizeof(float4) * entry_f4 + sizeof(uint32_t) * order, stream);
+    if (st == RCP_ERR_OUT_OF_MEMORY && entry_f4 > 0) {
+        clear_error();
+        if (lists > 0) w.lists_refused = lists;
+        entry_f4 = 0;
+        st = stream_alloc(&w.tiles, sizeof(uint32_t) * order, stream);
+    }
+    if (st != RCP_OK) return st;
+    w.entries = entry_f4 > 0 ? (float4*)w.tiles : nullptr;
+    w.entry_cap = entry_f4;
+    w.order = (uint32_t*)((float4*)w.tiles + entry_f4);
     w.order_cap = order;
     return RCP_OK;
 }
@@ -504,7 +516,7 @@ void free_workspace(Workspace& w, hipStream_t stream) {
     stream_free(w.spill, stream);
     stream_free(w.stats, stream);
     stream_free(w.view, stream);
-    stream_free(w.entries, stream);   // and the order
+    stream_free(w.tiles, stream);
     w = Workspace{};
 }
 

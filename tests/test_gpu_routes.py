@@ -152,3 +152,45 @@ def test_server_launches_start_after_a_long_direct_launch():
         assert done[0] <= min(done[1:]), done
     rcp.rcp_server_destroy(srv)
     s.close()
+
+
+def test_views_of_crossing_needs_share_one_workspace():
+    """1290 x 720 takes more tiles (padded), 1024 x 1024 more groups: rendered in
+    turn, only the first two frames allocate."""
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=90, n_boxes=40))
+    sizes = [(1290, 720), (1024, 1024)]
+    out = [torch.empty((2, h, w, 3), device="cuda") for w, h in sizes]
+    d = rcp.make_displacement(0.0, 0.02)
+
+    def both():
+        for (w, h), o in zip(sizes, out):
+            rcp.rcp_render(s.handle, patch_camera(), w, h, 2, d, o, None)
+
+    both()
+    both()
+    say("alternating views")
+    names = launched(lambda: [both() for _ in range(3)])
+    assert sum(n.startswith("k_chain") for n in names) == 6
+    assert not any("Malloc" in n for n in names if n != "hipStreamIsCapturing"), names
+    s.close()
+
+
+def test_views_beyond_the_most_lists():
+    """Views one pixel wide under tiles 64 wide have a list per four pixels: from
+    2^20 lists on (the bound of batches and, now, of single renders) rays start
+    at the root.  The same images come from tiles 8 wide."""
+    s = rcp.Scene(scenegen.terrain_patch(seed=8, cells=90, n_boxes=40))
+    cam = scenegen.camera_look_at([0.2, 0.5, -1.1], [0, 0.05, 0], [0, 1, 0], 100.0)
+    W, H, K = 1, (1 << 22) + 8, 2
+    d = rcp.make_displacement(0.0, 0.02)
+    out = [(torch.empty((K, H, W, 3), device="cuda"), torch.empty((K, H, W), dtype=torch.int32, device="cuda")) for _ in range(3)]
+    say("beyond the most lists")
+    rcp.rcp_render(s.handle, cam, W, H, K, d, *out[0])
+    rcp.rcp_set_tuning(s.handle, tile_log2w=6)
+    assert not with_lists(launched(lambda: rcp.rcp_render(s.handle, cam, W, H, K, d, *out[1])))
+    small = (torch.empty((1, 40, 30, 3), device="cuda"), None)
+    views = [(cam, W, H, K, d, *out[2]), (cam, 30, 40, 1, d, *small)]
+    assert not with_lists(launched(lambda: rcp.rcp_render_batch(s.handle, views)))
+    for a, b in out[1:]:
+        assert torch.equal(a, out[0][0]) and torch.equal(b, out[0][1])
+    s.close()
