@@ -1582,8 +1582,8 @@ size_t view_table_bytes(size_t n_views) {
 
 }  // namespace
 
-rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views, bool with_staging,
-                                   hipStream_t stream) {
+rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views, size_t lists, hipStream_t stream) {
+    const bool with_staging = lists > 0;
     const Launch lp = launch_params(s);
     size_t spill_need = 0;
     for (int mode = 0; mode < 3; ++mode)
@@ -1614,9 +1614,9 @@ rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views
         }
         RCP_HIP(hipHostMalloc(&ws.staging, view_table_bytes((size_t)n_views), hipHostMallocDefault));
     }
-    if (st == RCP_OK && with_staging && ws.entry_cap < kEntryStride * kServerEntries) {
+    if (st == RCP_OK && with_staging && ws.entry_cap < kEntryStride * lists) {
         // without room for entry lists the rays start at the root
-        const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * kServerEntries, sizeof(float4), stream);
+        const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * lists, sizeof(float4), stream);
         if (se != RCP_OK && se != RCP_ERR_OUT_OF_MEMORY) st = se;
     }
     return st;

@@ -227,13 +227,18 @@ struct BatchWorkspace {
 // the screen order, since a slot's buffers never grow.
 constexpr size_t kServerOrderTiles = size_t(1) << 18;
 
-// Entry lists of the chain engine (float4 each): one per 1024 pixels.  A server
-// slot holds kServerEntries (34 MB, 67M pixels in one launch); a batch allocates
-// what it needs, up to kMaxBatchEntries (537 MB, 10^9 pixels).  Larger
-// launches start their rays at the scene's root.
+// Entry lists of the chain engine (float4 each): one per 1024 pixels.  Renders and
+// batches allocate what they need, up to kMaxBatchEntries (537 MB, 10^9 pixels).
+// A server slot holds kServerEntries (34 MB, 67M pixels in one launch), or as
+// many as the requests that the pool admits together need at three passes with
+// hit IDs (1% of the pool).  Larger launches start their rays at the scene's root.
 constexpr size_t kEntryStride = 32;
 constexpr size_t kServerEntries = size_t(1) << 16;
 constexpr uint64_t kMaxBatchEntries = uint64_t(1) << 20;
+inline size_t server_lists(size_t pool_bytes) {
+    const size_t n = pool_bytes / (3 * 16 * 1024);
+    return n < kServerEntries ? kServerEntries : (n > kMaxBatchEntries ? (size_t)kMaxBatchEntries : n);
+}
 
 struct Tuning {
     int refill_min = -1;          // < 0: the library default for the launch
@@ -309,11 +314,10 @@ rcp_status gather_passes(const float* in, int W, int H, int n, float smudge, int
                          hipStream_t stream);
 
 rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchWorkspace& ws, hipStream_t stream);
-// Size a batch workspace for up to n_views views in every mode (no
-// allocation in render_batch afterwards); with_staging adds the pinned view
-// table the server copies from.
-rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views, bool with_staging,
-                                   hipStream_t stream);
+// Size a server slot's batch workspace for up to n_views views in every mode (no
+// allocation in render_batch afterwards), with `lists` entry lists and the
+// pinned view table the server copies from.
+rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views, size_t lists, hipStream_t stream);
 // The chain engine for a whole render from the seed: one launch, no pass barrier.
 rcp_status prepare_chain(rcp_scene* s, Workspace& ws, int W, int H, int mode, hipStream_t stream);
 rcp_status render_chain(rcp_scene* s, Workspace& ws, const Camera& cam, int W, int H, int K, const Disp& disp,

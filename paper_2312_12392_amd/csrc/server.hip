@@ -295,7 +295,7 @@ rcp_status server_create(rcp_scene* scene, size_t pool_bytes, int max_inflight, 
             return hip_status(e, "server stream", __FILE__, __LINE__);
         }
         // every buffer a launch of this slot uses, sized for the largest batch
-        st = prepare_batch_workspace(scene, sl.ws, kMaxBatch, true, sl.stream);
+        st = prepare_batch_workspace(scene, sl.ws, kMaxBatch, server_lists(pool_bytes), sl.stream);
         if (st == RCP_OK && hipStreamSynchronize(sl.stream) != hipSuccess) st = RCP_ERR_DEVICE;
         if (st != RCP_OK) {
             const std::string msg = rcp_last_error();

@@ -223,3 +223,28 @@ def test_destroy_with_requests_in_flight(scene):
         rcp.rcp_submit(srv, cam, W, H, K, d)
     rcp.rcp_server_destroy(srv)                       # running launches finish, nothing leaks or hangs
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("pool_gib", [3, 4])
+def test_launch_of_more_groups_than_a_small_pool_holds_lists_for(pool_gib):
+    """A burst of 4K requests, all but the first in one launch: ten of them have
+    more tile groups than the lists of a slot at 3 GiB, fewer than at 4."""
+    W, H, K, n = 3840, 2160, 2, 11
+    s = rcp.Scene(scenegen.terrain_patch(8, 60, 40))
+    cam = scenegen.camera_look_at([0.2, 0.5, -1.1], [0, 0.05, 0], [0, 1, 0], 60.0)
+    d = rcp.make_displacement(0.0, 0.02)
+    ref, _ = s.render(cam, W, H, K, 0.0, 0.02, with_ids=False)
+    torch.cuda.synchronize()
+    srv = rcp.rcp_server_create(s.handle, pool_gib << 30, 2, 64)
+    out = torch.empty_like(ref)
+    tickets = [rcp.rcp_submit(srv, cam, W, H, K, d) for _ in range(n)]
+    for t in tickets:
+        while rcp.rcp_poll(srv, t)[0] not in (rcp.RCP_REQ_DONE, rcp.RCP_REQ_FAILED):
+            pass
+        out.zero_()
+        rcp.rcp_result_copy(srv, t, out, None)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        rcp.rcp_release(srv, t)
+    rcp.rcp_server_destroy(srv)
+    s.close()
