@@ -35,7 +35,7 @@ struct GatherArgs {
     const float* in;     // the image the first pass reads
     float* out;          // the first pass's image; the next ones follow
     int W, H;
-    uint32_t tiles_x, n_tiles;
+    uint32_t tiles_x, n_tiles;   // tiles_x 0: workgroups take the pixels in a row, whatever the image's width
     uint32_t band;       // workgroups of an XCD's band; 0: workgroups in row order
     float smudge;
     int edge, centred;
@@ -120,15 +120,27 @@ template <int F, int N, bool STREAM>
 __global__ __launch_bounds__(kB) void k_gather(GatherArgs a) {
     const uint32_t tile = a.band ? (blockIdx.x % kXcds) * a.band + blockIdx.x / kXcds : blockIdx.x;
     if (tile >= a.n_tiles) return;
-    const int x0 = (int)(tile % a.tiles_x) * kTileW + (int)(threadIdx.x % kTileW);
-    const int y0 = (int)(tile / a.tiles_x) * kTileH * N + (int)(threadIdx.x / kTileW);
-    if (x0 >= a.W || y0 >= a.H) return;
     int x[N], y[N], live = 0;
+    if (a.tiles_x != 0u) {
+        const int x0 = (int)(tile % a.tiles_x) * kTileW + (int)(threadIdx.x % kTileW);
+        const int y0 = (int)(tile / a.tiles_x) * kTileH * N + (int)(threadIdx.x / kTileW);
+        if (x0 >= a.W || y0 >= a.H) return;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        x[i] = x0;
-        y[i] = min(y0 + i * kTileH, a.H - 1);
-        live += y0 + i * kTileH < a.H ? 1 : 0;
+        for (int i = 0; i < N; ++i) {
+            x[i] = x0;
+            y[i] = min(y0 + i * kTileH, a.H - 1);
+            live += y0 + i * kTileH < a.H ? 1 : 0;
+        }
+    } else {
+        const uint32_t P = (uint32_t)a.W * (uint32_t)a.H, p0 = tile * (uint32_t)(kB * N) + threadIdx.x;
+        if (p0 >= P) return;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t p = min(p0 + (uint32_t)(i * kB), P - 1u);
+            y[i] = (int)(p / (uint32_t)a.W);
+            x[i] = (int)(p - (uint32_t)y[i] * (uint32_t)a.W);
+            live += p0 + (uint32_t)(i * kB) < P ? 1 : 0;
+        }
     }
     Colour c[N];
     image<0, N>(a, x, y, c);
@@ -141,8 +153,16 @@ namespace {
 
 template <int F, int N, bool STREAM>
 rcp_status launch(GatherArgs a, bool bands, hipStream_t stream) {
+    // Tiles 64 pixels wide, a wave per row, but not where an eighth of their lanes
+    // or more would lie beyond the image's side: such narrow images are taken
+    // pixel by pixel (5 passes, 6 px, us, tiles / in a row: 65 x 200,000 540 / 336, 1
+    // x 4M 2163 / 65, 9 x 4M 2481 / 783).
     a.tiles_x = (uint32_t)((a.W + kTileW - 1) / kTileW);
     a.n_tiles = a.tiles_x * (uint32_t)((a.H + kTileH * N - 1) / (kTileH * N));
+    if (8 * ((int)a.tiles_x * kTileW - a.W) >= a.W) {
+        a.tiles_x = 0u;
+        a.n_tiles = ((uint32_t)a.W * (uint32_t)a.H + (uint32_t)(kB * N) - 1u) / (uint32_t)(kB * N);
+    }
     a.band = bands ? (a.n_tiles + kXcds - 1) / kXcds : 0u;
     hipLaunchKernelGGL((k_gather<F, N, STREAM>), dim3(bands ? a.band * kXcds : a.n_tiles), dim3(kB), 0, stream, a);
     RCP_CHECK_LAUNCH();

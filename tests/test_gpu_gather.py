@@ -77,3 +77,16 @@ def test_gather_launch_shapes(W, H, smudge, n):
     img = rng.uniform(0.0, 1.0, size=(H, W, 3)).astype(np.float32)
     for edge in (rcp.RCP_EDGE_CLAMP, rcp.RCP_EDGE_WRAP, rcp.RCP_EDGE_MIRROR):
         assert np.array_equal(run_gather(img, n, smudge, edge, True), oracle.gather(img, n, smudge, edge=edge, centred=True))
+
+
+# images narrower than a wave, and of widths that 64 do not divide by far:
+# workgroups from one pixel wide on
+@pytest.mark.parametrize("W,H", [(1, 1), (1, 5000), (2, 129), (3, 700), (9, 70000), (17, 33), (40, 12001), (65, 7001), (100, 100),
+                                 (129, 65)])
+@pytest.mark.parametrize("smudge", [0.7, 40.0])
+def test_gather_narrow_images(W, H, smudge):
+    say("gather narrow", W, H, smudge)
+    img = np.random.default_rng(W + H).uniform(0.0, 1.0, size=(H, W, 3)).astype(np.float32)
+    for edge in (rcp.RCP_EDGE_CLAMP, rcp.RCP_EDGE_WRAP, rcp.RCP_EDGE_MIRROR):
+        for n in (1, 4):
+            assert np.array_equal(run_gather(img, n, smudge, edge, True), oracle.gather(img, n, smudge, edge=edge, centred=True))
