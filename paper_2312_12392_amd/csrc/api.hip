@@ -271,9 +271,14 @@ rcp_status rcp_build_scene(const rcp_scene_desc* desc, const rcp_build_options* 
         st = build_scene(desc, opts, (hipStream_t)hip_stream, out);
     } catch (const std::bad_alloc&) {
         set_error("host allocation failed");
-        return RCP_ERR_OUT_OF_MEMORY;
+        st = RCP_ERR_OUT_OF_MEMORY;
     }
-    if (st == RCP_ERR_INVALID_ARGUMENT) (void)check_arrays(desc);   // names the entry
+    // a bad entry is the error, and is named, whatever else the build failed on
+    // (it may not have come as far as its check)
+    if (st != RCP_OK) {
+        const rcp_status bad = check_arrays(desc);
+        if (bad != RCP_OK) return bad;
+    }
     const char* log = std::getenv("RCP_LOG");
     if (st == RCP_OK && log && std::strcmp(log, "1") == 0) {
         const rcp_scene_stats& t = (*out)->stats;

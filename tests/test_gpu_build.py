@@ -74,3 +74,19 @@ def test_bad_entry_is_refused_and_named(n, what, value):
     s = rcp.Scene(good)
     assert s.info()["n_tris"] == n
     s.close()
+
+
+@pytest.mark.parametrize("what,value", [("idx", 0xFFFFFFFF), ("verts", np.nan), ("rgb", np.inf)])
+@pytest.mark.parametrize("after", [0, 1, 3])
+def test_bad_entry_is_the_error_when_memory_fails_too(what, value, after):
+    say("bad entry without memory", what, after)
+    good = scenegen.soup_scene(4, 50)
+    arrays = {"verts": good.verts.copy(), "idx": good.idx.copy(), "rgb": good.rgb.copy()}
+    arrays[what][-1, -1] = value
+    rcp.rcp_debug_set(rcp.RCP_DEBUG_FAIL_ALLOC_AFTER, after)
+    try:
+        with pytest.raises(rcp.RcpError) as e:
+            rcp.Scene(scenegen.Scene(**arrays))
+    finally:
+        rcp.rcp_debug_set(rcp.RCP_DEBUG_FAIL_ALLOC_AFTER, -1)
+    assert e.value.status == rcp.RCP_ERR_INVALID_ARGUMENT and str(arrays[what].size - 1) in str(e.value)
