@@ -380,8 +380,9 @@ rcp_status rcp_set_tuning(rcp_scene* scene, const rcp_tuning* tuning);
  * HIP events on hip_stream) and descends over the rcp_tuning fields, one
  * field at a time with the others fixed, twice over: refill_min, exit_lanes,
  * blocks_per_cu, tile_log2w, engine, top_levels, stack_entries, block_size.
- * Sets the fastest on the scene and returns it with its time.  The outputs
- * receive a valid render.  Synchronous. */
+ * A candidate is kept if it is 2% faster or more; fields that this workload's
+ * launches do not read stay as they are.  Sets the result on the scene and
+ * returns it with its time.  The outputs receive a valid render.  Synchronous. */
 rcp_status rcp_autotune(rcp_scene* scene, const rcp_camera* base_camera, int W, int H, int K,
                         const rcp_displacement* disp, float* out_images, int32_t* out_ids, int repeats,
                         rcp_tuning* best, float* best_ms, void* hip_stream);

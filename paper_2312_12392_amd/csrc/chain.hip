@@ -1622,6 +1622,52 @@ rcp_status prepare_batch_workspace(rcp_scene* s, BatchWorkspace& ws, int n_views
     return st;
 }
 
+namespace {
+
+Camera camera_of(const rcp_view& v) {
+    Camera c{};
+    for (int a = 0; a < 3; ++a) {
+        c.eye[a] = v.camera.eye[a];
+        c.right[a] = v.camera.right[a];
+        c.up[a] = v.camera.up[a];
+        c.forward[a] = v.camera.forward[a];
+    }
+    c.th = v.camera.tan_half_fovy;
+    return c;
+}
+
+Disp disp_of(const rcp_view& v) { return Disp{v.disp.lambda_eye, v.disp.lambda_dir, v.disp.z0, v.disp.mode}; }
+
+// Whether the rays of a batch are better off in entry lists (see render_batch).
+rcp_status views_want_lists(const rcp_scene* s, const Launch& lp, const rcp_view* views, int n_views, bool& want) {
+    want = s->dev.n_nodes > 0;
+    if (!want) return RCP_OK;
+    const auto spread = [&](const rcp_view& v) { return view_spread_angle(s, camera_of(v), v.W, v.H, disp_of(v)); };
+    if (n_views == 1) {
+        const uint64_t items = frame_items(views->W, views->H, lp.tile_log2w);
+        ChainGrid g;
+        RCP_TRY_STATUS(chain_grid(lp, false, 1, views->disp.mode, true, items, g));
+        want = lists_pay(s, views->disp.mode, spread(*views), views->K, items, g.lanes);
+    } else if (!visits_much(s) && s->dev.max_depth <= 12u) {
+        want = false;
+        for (int i = 0; i < n_views && !want; ++i) want = spread(views[i]) <= 0.1;
+    }
+    return RCP_OK;
+}
+
+}  // namespace
+
+rcp_status batch_route(const rcp_scene* s, const rcp_view* views, int n_views, Route& r) {
+    if (n_views == 1 && direct_lanes(s, views->W, views->H, views->K) > 0) {
+        r = Route::direct;
+        return RCP_OK;
+    }
+    bool lists = false;
+    RCP_TRY_STATUS(views_want_lists(s, launch_params(s), views, n_views, lists));
+    r = lists ? Route::lists : Route::root;
+    return RCP_OK;
+}
+
 rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchWorkspace& ws, hipStream_t stream) {
     const Launch lp = launch_params(s);
     // views grouped by displacement mode, one launch per mode present
@@ -1645,16 +1691,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
             groups.push_back(Group{vi.disp.mode, j, 0, bofs, 0, 0});
             items = 0;
         }
-        Camera c{};
-        for (int a = 0; a < 3; ++a) {
-            c.eye[a] = vi.camera.eye[a];
-            c.right[a] = vi.camera.right[a];
-            c.up[a] = vi.camera.up[a];
-            c.forward[a] = vi.camera.forward[a];
-        }
-        c.th = vi.camera.tan_half_fovy;
-        const Disp d{vi.disp.lambda_eye, vi.disp.lambda_dir, vi.disp.z0, vi.disp.mode};
-        hv[(size_t)j] = view_of(s, c, vi.W, vi.H, vi.K, d, vi.out_images, vi.out_ids, lp.tile_log2w);
+        hv[(size_t)j] = view_of(s, camera_of(vi), vi.W, vi.H, vi.K, disp_of(vi), vi.out_images, vi.out_ids, lp.tile_log2w);
         hv[(size_t)j].entry_base = (uint32_t)std::min<uint64_t>(n_entries, 0xFFFFFFFFull);
         n_entries += view_entries(vi.W, vi.H, lp.tile_log2w);
         hb[bofs++] = (uint32_t)items;
@@ -1674,8 +1711,7 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     if (n_views == 1)
         if (const int lanes = direct_lanes(s, views[0].W, views[0].H, views[0].K)) {
             ws.alone = (double)views[0].W * views[0].H * s->dev.n_tris > kAloneTests;
-            const Disp d{views[0].disp.lambda_eye, views[0].disp.lambda_dir, views[0].disp.z0, views[0].disp.mode};
-            return launch_direct(s, hv[0].cam, views[0].W, views[0].H, views[0].K, d, views[0].out_images,
+            return launch_direct(s, hv[0].cam, views[0].W, views[0].H, views[0].K, disp_of(views[0]), views[0].out_images,
                                  views[0].out_ids, lanes, stream);
         }
 
@@ -1686,16 +1722,8 @@ rcp_status render_batch(rcp_scene* s, const rcp_view* views, int n_views, BatchW
     // times; 16 views of a terrain of 5000 triangles at a spread of 0.05 1.15, at
     // 0.2 1.02 with lists and 1.13 from the root, of 100,000 1.16, 0.99 and 0.98;
     // 4 views 0.97, 0.85 and 0.97, 0.96, 0.93 and 0.97)
-    bool want = s->dev.n_nodes > 0;
-    if (n_views == 1 && want) {
-        ChainGrid one;
-        RCP_TRY_STATUS(chain_grid(lp, false, 1, groups[0].mode, true, groups[0].items, one));
-        want = lists_pay(s, groups[0].mode, spread_angle(s, hv[0].spread_dir, hv[0].spread_eye), hv[0].K, groups[0].items,
-                         one.lanes);
-    } else if (want && !visits_much(s) && s->dev.max_depth <= 12u) {
-        want = false;
-        for (const ViewDev& v : hv) want = want || spread_angle(s, v.spread_dir, v.spread_eye) <= 0.1;
-    }
+    bool want = false;
+    RCP_TRY_STATUS(views_want_lists(s, lp, views, n_views, want));
     if (want && !ws.staging && n_entries <= kMaxBatchEntries && ws.entry_cap < kEntryStride * n_entries) {
         const rcp_status se = grow(&ws.entries, ws.entry_cap, kEntryStride * (size_t)n_entries, sizeof(float4), stream);
         if (se != RCP_OK && se != RCP_ERR_OUT_OF_MEMORY) return se;

@@ -327,6 +327,9 @@ rcp_status render_chain(rcp_scene* s, Workspace& ws, const Camera& cam, int W, i
 rcp_status render_chain_fixed(rcp_scene* s, Workspace& ws, const Camera& cam, int W, int H, int K,
                               const Disp& disp, float* out_images, int32_t* out_ids, hipStream_t stream);
 void free_batch_workspace(BatchWorkspace& ws, hipStream_t stream);
+// How the chain engine renders a view or a batch, given room for entry lists.
+enum class Route { direct, lists, root };
+rcp_status batch_route(const rcp_scene* s, const rcp_view* views, int n_views, Route& r);
 // Report (and clear) a ray that ran out of its step budget since the last
 // check, as RCP_ERR_INTERNAL.  Reads the host-mapped flag: the work that may
 // have set it must be complete.

@@ -89,16 +89,35 @@ rcp_status time_runs(Run&& run, int repeats, hipStream_t stream, hipEvent_t e0, 
     return RCP_OK;
 }
 
+// The parameters of the descent, in the order in which it tries them.
+enum Param { kRefill, kExit, kBlocks, kTile, kEngine, kStagedLevels, kStackEntries, kBlockSize, kTileOrder, kParams };
+
+// Whether a parameter reaches the launches of a workload that the chain engine
+// would render by `route` (colour: some of it in the colour mode, whose kernels
+// alone come in several stack depths and workgroup sizes).
+bool acts(Param p, int engine, Route route, bool colour) {
+    if (p == kEngine) return true;
+    if (engine == RCP_ENGINE_PASSES) return p <= kStagedLevels;
+    if (route == Route::direct) return false;
+    if (p == kStagedLevels || p == kStackEntries) return route == Route::root && (p == kStagedLevels || colour);
+    return p != kBlockSize || colour;
+}
+
+// What a candidate has to gain to be kept: runs of the same parameters differ by
+// this much, and a parameter kept for less would stay on the scene for launches
+// that it slows down.
+constexpr float kTuneGain = 0.98f;
+
 // Coordinate descent over the launch parameters: each round tries every
-// candidate of one parameter with the others fixed and keeps the fastest.
-// The parameters: refill threshold, early-exit lanes, workgroups per CU,
-// tile width, engine and tile order (single renders only; batches always run
-// the chain engine in screen order), LDS-staged tree levels, LDS stack depth
+// candidate of one parameter with the others fixed and keeps the fastest that
+// gains enough.  The parameters: refill threshold, early-exit lanes, workgroups
+// per CU, tile width, engine and tile order (single renders only; batches always
+// run the chain engine in screen order), LDS-staged tree levels, LDS stack depth
 // and workgroup size (the last two select among instantiations of the chain
-// kernel).
-template <class Run>
-rcp_status descend(rcp_scene* s, Run&& run, bool tune_engine, int repeats, Tuning& best, float& best_ms,
-                   hipStream_t stream) {
+// kernel); of these the ones that the workload's launches read.
+template <class Run, class RouteOf>
+rcp_status descend(rcp_scene* s, Run&& run, RouteOf&& route_of, bool colour, bool tune_engine, int repeats, Tuning& best,
+                   float& best_ms, hipStream_t stream) {
     hipEvent_t e0, e1;
     RCP_HIP(hipEventCreate(&e0));
     RCP_HIP(hipEventCreate(&e1));
@@ -124,8 +143,11 @@ rcp_status descend(rcp_scene* s, Run&& run, bool tune_engine, int repeats, Tunin
     rcp_status st = time_runs(run, repeats, stream, e0, e1, cur_ms);
     if (st != RCP_OK) return st;
     for (int round = 0; round < 2; ++round) {
-        for (int param = 0; param < 9; ++param) {
-            if ((param == 4 || param == 8) && !tune_engine) continue;
+        for (int param = 0; param < kParams; ++param) {
+            if ((param == kEngine || param == kTileOrder) && !tune_engine) continue;
+            Route route = Route::root;
+            if ((st = route_of(route)) != RCP_OK) return st;
+            if (!acts((Param)param, cur.engine, route, colour)) continue;
             const std::vector<int>& cands = param == 0   ? refill
                                             : param == 1 ? exits
                                             : param == 2 ? blocks
@@ -152,7 +174,7 @@ rcp_status descend(rcp_scene* s, Run&& run, bool tune_engine, int repeats, Tunin
                 float ms = 0.0f;
                 st = time_runs(run, repeats, stream, e0, e1, ms);
                 if (st != RCP_OK) { s->tuning = cur; return st; }
-                if (ms < cur_ms) { cur = t; cur_ms = ms; }
+                if (ms < kTuneGain * cur_ms) { cur = t; cur_ms = ms; }
             }
             s->tuning = cur;
         }
@@ -174,13 +196,31 @@ rcp_status autotune(rcp_scene* s, const Camera& cam, int W, int H, int K, const 
     auto run = [&]() -> rcp_status {
         return render(s, s->ws, cam, W, H, K, d, out, ids, nullptr, nullptr, nullptr, nullptr, stream);
     };
-    return descend(s, run, true, repeats, best, best_ms, stream);
+    rcp_view v{};
+    for (int a = 0; a < 3; ++a) {
+        v.camera.eye[a] = cam.eye[a];
+        v.camera.right[a] = cam.right[a];
+        v.camera.up[a] = cam.up[a];
+        v.camera.forward[a] = cam.forward[a];
+    }
+    v.camera.tan_half_fovy = cam.th;
+    v.W = W;
+    v.H = H;
+    v.K = K;
+    v.disp.lambda_eye = d.le;
+    v.disp.lambda_dir = d.ld;
+    v.disp.z0 = d.z0;
+    v.disp.mode = d.mode;
+    return descend(s, run, [&](Route& r) { return batch_route(s, &v, 1, r); }, d.mode == RCP_MODE_COLOR, true, repeats, best,
+                   best_ms, stream);
 }
 
 rcp_status autotune_batch(rcp_scene* s, const rcp_view* views, int n_views, int repeats, Tuning& best,
                           float& best_ms, hipStream_t stream) {
     auto run = [&]() -> rcp_status { return render_batch(s, views, n_views, s->bws, stream); };
-    return descend(s, run, false, repeats, best, best_ms, stream);
+    const bool colour = std::any_of(views, views + n_views, [](const rcp_view& v) { return v.disp.mode == RCP_MODE_COLOR; });
+    return descend(s, run, [&](Route& r) { return batch_route(s, views, n_views, r); }, colour, false, repeats, best, best_ms,
+                   stream);
 }
 
 }  // namespace rcp

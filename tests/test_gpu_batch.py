@@ -278,6 +278,26 @@ def test_autotune_and_cache(tmp_path):
     s.close()
 
 
+@pytest.mark.parametrize("repeats", [1, 2])
+def test_autotune_leaves_what_the_launches_do_not_read(repeats):
+    """A frame of the direct kernel reads none of the parameters, one with entry
+    lists neither the staged levels nor the stack depth: they are not chosen by
+    which of two equal runs was faster."""
+    say("autotune, unread parameters")
+    w = scenegen.workload("soup256")
+    s = rcp.Scene(w.scene)
+    out = torch.empty((6, 64, 64, 3), device="cuda")
+    t, _ = rcp.rcp_autotune(s.handle, w.camera, 64, 64, 6, rcp.make_displacement(0.0, 0.02), out, None, repeats=repeats)
+    assert t == dict(refill_min=64, exit_lanes=32, blocks_per_cu=0, tile_log2w=3, engine=0, top_levels=4, stack_entries=16,
+                     block_size=256, tile_order=1)
+    s.close()
+    s = rcp.Scene(scenegen.terrain_patch(8, 90, 40))
+    out = torch.empty((3, 300, 400, 3), device="cuda")
+    t, _ = rcp.rcp_autotune(s.handle, PATCH_CAM, 400, 300, 3, rcp.make_displacement(0.0, 0.02), out, None, repeats=repeats)
+    assert t["engine"] == rcp.RCP_ENGINE_PASSES or (t["top_levels"], t["stack_entries"]) == (4, 16)
+    s.close()
+
+
 def test_autotune_batch():
     """The autotuner on a batch picks valid parameters (the engine stays the
     chain engine) and leaves the batch's images in the outputs."""
