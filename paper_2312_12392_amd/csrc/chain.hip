@@ -23,8 +23,9 @@
 //
 // Between setup rounds the wave's rays start in their tile group's entry list
 // (below) and put the leaves they reach into a queue that all lanes work off
-// (trav_queue).  The instrumented kernel, and launches without room for the
-// lists, start at the root and test each leaf in its ray's lane (trav_step).
+// (trav_queue).  The instrumented kernel, and launches that have no room for the
+// lists or would not gain by them, start at the root and test each leaf in its
+// ray's lane (trav_step).
 //
 // The same kernel serves rcp_render and rcp_render_batch.  Views are read
 // from a device table, by each lane, or with scalar loads when the launch
@@ -100,13 +101,13 @@ struct ChainArgs {
 // meets, and takes its next subtree from the mask whenever its stack is
 // empty.  The items' boxes are the exact boxes of the tree's nodes, and only
 // boxes that no ray of the group can meet are left out, so the closest hit
-// stays the same.
+// stays the same.  (A pixel whose displacement turns out beyond the bound goes
+// on from the root; see the kernel.)  Which launches have lists: lists_pay.
 //
-// On the 1080p terrain frame (1M triangles, K = 6) a ray visits 9.4 nodes and
-// tests 16 items, against 18 nodes from the root.  Measured (frame ms): 16
-// items 1.09; 32 items 1.18 (fewer visits, 7.6, but twice the tests, and a
-// workgroup less per CU); groups of 2 x 2 tiles 1.09, one tile 1.14, 8 x 8
-// tiles 1.10; two lists per wave 1.11 (more rays without one).
+// Measured on the 1080p terrain frame (1M triangles, K = 6; ms): 16 items 1.09; 32
+// items 1.18 (twice the tests, and a workgroup less per CU); groups of 2 x 2
+// tiles 1.09, one tile 1.14, 8 x 8 tiles 1.10; two lists per wave 1.11 (more
+// rays without one).
 constexpr int kEntryItems = 16;
 // A list in HBM (kEntryStride float4): the six planes of four items (as in a
 // node) each, the links, then the number of used quads of items.
@@ -247,7 +248,7 @@ __device__ inline void chain_body(const ChainArgs& a) {
                             // rays start at the root.
                             if (ENTRY && (MODE == RCP_MODE_DEPTH
                                               ? !(fabsf(na[0] - vw.z0) <= vw.z_reach)
-                                              : !((na[1] * na[1] + na[2] * na[2]) + na[3] * na[3] <= 1.0001f)))
+                                              : nv.w != 0.0f))
                                 slot = kEntrySlots;
                         }
                     } else {
@@ -382,8 +383,9 @@ __device__ inline void chain_body(const ChainArgs& a) {
                 }
             }
             if (ENTRY) {
-                // the entry lists of the new pixels' groups (two at most: the
-                // items are consecutive): already in a slot, or copied into
+                // the entry lists of the new pixels' groups (the tiles of a round
+                // may come from anywhere in the band, when they go out by cost or
+                // what was left is topped up): already in a slot, or copied into
                 // one that no live lane uses.  Without a free slot the pixels
                 // start at the scene's root.
                 unsigned long long todo = wave_ballot(group != 0xFFFFFFFFu);
@@ -616,8 +618,7 @@ __global__ void k_clear_chain(uint32_t* fetch, int n, unsigned long long* stats)
 }
 
 // Setup of a one-view launch (a single render, or a batch of one view): its
-// one-entry view table, item range, band counters and stats.
-// A single render's one-entry view table, zeroed band counters (and stats).
+// one-entry view table, item range, zeroed band counters and stats.
 __device__ inline void setup_single(const ViewDev& v, ViewDev* table, uint32_t* begin, uint32_t n_items,
                                     uint32_t* fetch, unsigned long long* stats) {
     if (threadIdx.x == 0) {
@@ -978,7 +979,7 @@ __global__ __launch_bounds__(kScoreBlock) void k_batch_entries(const ViewDev* __
 // score (order within a score is the order of arrival, which only moves
 // work in time).  Every tile of the band lands in exactly one slot of the
 // band's range, so order[] is a permutation of the tiles.  One more
-// workgroup does the launch's setup (the work of k_setup_single).
+// workgroup does the launch's setup.
 __global__ __launch_bounds__(1024) void k_band_order(const uint32_t* __restrict__ score, uint32_t n_items,
                                                      uint32_t* __restrict__ order, ViewDev v, ViewDev* table,
                                                      uint32_t* begin, uint32_t* fetch, unsigned long long* stats) {

@@ -7,7 +7,8 @@
 //                               (x[c+1], x[c+2], x[c]) (indices mod 3): v0 +
 //                               original index bits in w, v1, v2
 //   shade  float4[n_tris][2]    shaded RGB seen from the front / back side
-//   normal float4[n_tris]       unit geometric normal (read by the normal mapping)
+//   normal float4[n_tris]       unit geometric normal (read by the normal mapping);
+//                               w: 0, or 1 where it is none
 // Nodes are in level order from the root; the inner children of a node sit in
 // consecutive slots.
 #pragma once

@@ -342,7 +342,11 @@ struct RayArgs {
     int32_t* spill;
     uint32_t spill_stride;
     uint32_t chunk;                    // <= 64
-    uint32_t refill_min, exit_lanes;   // refill_min: idle lanes, more than 64 - chunk
+    // refill_min: idle lanes that end a traversal call.  Any number from 1 on ends:
+    // before each call the idle lanes take the rest of a chunk, or the wave moves
+    // on to its next one (a call that finds refill_min lanes idle already returns
+    // at once), and once the chunks are used up a call runs until all rays have ended.
+    uint32_t refill_min, exit_lanes;
 };
 
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_trace_rays(RayArgs a) {

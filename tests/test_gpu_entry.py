@@ -81,6 +81,22 @@ def test_hit_beyond_the_scene_box():
     s.close()
 
 
+@pytest.mark.parametrize("scale", [2.0 ** -31, 2.0 ** -33, 2.0 ** -34])
+@pytest.mark.parametrize("mode", [rcp.RCP_MODE_NORMAL, rcp.RCP_MODE_DEPTH])
+def test_scenes_whose_areas_are_near_the_least_float(scale, mode):
+    """Squares of the triangles' normals lie among the denormals: the normals come
+    out shorter and longer than 1, and displace by as much."""
+    say("least areas", scale, mode)
+    sc = scenegen.terrain_patch(seed=8, cells=60, n_boxes=40)
+    sc.verts = (sc.verts * np.float32(scale)).astype(np.float32)
+    cam = patch_camera(np.array([0.2, 0.5, -1.1]) * scale, np.array([0.0, 0.05, 0.0]) * scale)
+    s = rcp.Scene(sc)
+    img, ids = both_engines(s, cam, 121, 83, 4, 0.0, 0.2, mode, 0.0)
+    o_img, o_ids = oracle.OracleScene(sc, use_bvh=True).render(cam, 121, 83, 4, 0.0, 0.2, mode=mode, z0=0.0)
+    assert np.array_equal(img.cpu().numpy(), o_img) and np.array_equal(ids.cpu().numpy(), o_ids)
+    s.close()
+
+
 @pytest.mark.parametrize("fov,background", [(4.0, 0.5), (150.0, 0.5), (60.0, 3.0)])
 def test_entry_lists_lens_and_background(fov, background):
     """Narrow and very wide lenses; a background above 1, which displaces by
