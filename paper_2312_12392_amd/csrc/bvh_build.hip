@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(kB) void k_pack_tris(uint32_t n, const float* __res
     ny = ny / len;
     nz = nz / len;
     // (marked in w: no unit vector, from an area near the least or largest float)
-    normals[j] = make_float4(nx, ny, nz, (nx * nx + ny * ny) + nz * nz <= 1.0001f ? 0.0f : 1.0f);
+    normals[j] = make_float4(nx, ny, nz, (nx * nx + ny * ny) + nz * nz <= 1.0001f ? 0.0f : __uint_as_float(kNoUnitNormal));
     const float3 alb = ld3(albedo, t);
     for (int side = 0; side < 2; ++side) {
         const float sx = side ? -nx : nx, sy = side ? -ny : ny, sz = side ? -nz : nz;

@@ -8,7 +8,7 @@
 //                               original index bits in w, v1, v2
 //   shade  float4[n_tris][2]    shaded RGB seen from the front / back side
 //   normal float4[n_tris]       unit geometric normal (read by the normal mapping);
-//                               w: 0, or 1 where it is none
+//                               w: bits 0, or kNoUnitNormal where it is none
 // Nodes are in level order from the root; the inner children of a node sit in
 // consecutive slots.
 #pragma once
@@ -32,6 +32,7 @@ constexpr size_t kNodeBytes = 128;           // one 4-wide BVH node
 constexpr uint32_t kLeafBit = 0x80000000u;
 constexpr int kMaxLeaf = 8;                // 3 bits of count
 constexpr uint32_t kMaxTris = 1u << 28;    // 28 bits of first triangle
+constexpr uint32_t kNoUnitNormal = 4u;     // mark of a normal longer than 1, or NaN
 // Unused child slot of a 4-wide node: NaN planes, which fail every box test,
 // and a link to the one-triangle leaf of triangle 0, so that even a slot
 // that were entered could only repeat a test (never change the closest hit).
