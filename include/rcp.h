@@ -339,8 +339,8 @@ void rcp_graph_destroy(rcp_graph* graph);
  *   top_levels     levels of the 4-wide BVH that launches whose rays start at
  *                  the root copy into each workgroup's LDS and read from
  *                  there (0..4, default 4; at most 80 nodes): the
- *                  instrumented kernel and launches without room for entry
- *                  lists
+ *                  instrumented kernel, the per-pass engine and launches
+ *                  that have no room for entry lists or do not gain by them
  *   stack_entries  traversal stack entries per lane that those launches keep
  *                  in LDS in the colour mode (8 or 16, default 16; launches
  *                  with entry lists keep 8); deeper entries go to a global
